@@ -46,8 +46,13 @@ struct Outs {
   uint32_t *pool;
   int64_t pool_cap;
   unsigned long long *pool_top;
-  int64_t *pool_off;
+  int64_t *pool_off;   // -1 before the aligners run (launch_pair_flags)
 };
+// A walk that meets a pair's runs first op first writes them from the end of
+// the pair's slot (pool_off = POOL_OFF_TAIL) or of one pool reservation
+// (POOL_OFF_WHOLE plus the offset of the last op's run) backwards: nruns runs,
+// last op first, as in the other cases.
+constexpr int64_t POOL_OFF_TAIL = -3, POOL_OFF_WHOLE = (int64_t)1 << 62;
 
 // Appends runs of one pair (last op first) to its slot, then to the pool.
 struct RunSink {
@@ -113,7 +118,8 @@ struct Work {
 // ---- host-side launchers (each enqueues on `stream`) ----------------------
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
-                             const int8_t *pf, const int8_t *tf, int8_t *flags, hipStream_t s);
+                             const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off,
+                             hipStream_t s);
 hipError_t launch_pack(int64_t n, int32_t enc, const uint8_t *seq, const int64_t *off,
                        const int32_t *len, int32_t max_len, uint64_t *words, int64_t words_cap,
                        int64_t *out_off, int8_t *flags, int64_t *scan_tmp, hipStream_t s);
@@ -293,6 +299,45 @@ size_t wfa_lds_bytes(int32_t W, int32_t MG, int32_t R, int32_t e, int32_t seq_wo
 // threads: 64, 128, 256 or 512
 hipError_t launch_wfa_lds(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, const WfaLds &L,
                           int32_t threads, int32_t nslots, hipStream_t s);
+
+// The first pass for narrow pairs with unit gap extension (k_wfa_group):
+// groups of `lanes` lanes with `words` words of two diagonals a lane, 64 / lanes
+// pairs per wavefront.
+struct WfaGroup {
+  int32_t R;           // ring rows of M: max(x, o + 1) + 1
+  int32_t seq_words;   // words of LDS staging per sequence
+  int32_t s_cap;       // scores a pair may take here
+  int32_t nslots;      // workgroups of one wavefront
+  int32_t as_steps;    // steps the ring of origin codes holds (a power of two, at least 64)
+  int64_t slot_words;  // 32-bit words of codes per workgroup: 16 words as_steps
+  uint32_t *codes;
+  // pairs that leave the pass: to over_list (a wider group or the general
+  // adaptive kernel), or, without one, to the window classes by predicted extent
+  int32_t *over_list, *over_count;
+  WfaRoute route;
+  // the full-store fallback of a failed walk, as in WfaLaunch
+  int64_t need_cap[4];
+  int32_t *need_list[4];
+  int32_t *need_count[4];
+  int32_t *need_max[4];
+  int64_t *need;
+  int32_t *walk_fail;
+  int32_t *long_list, *long_count;
+  int32_t ad_min, ad_max;  // WFA-adaptive, as in WfaLds
+  unsigned long long *ad_dropped;
+};
+struct WfaGroupArgs {
+  Seqs S;
+  Outs O;
+  Scoring P;
+  Work Wk;
+  WfaGroup L;
+};
+// Longest sequence (its offsets and absent marks fit 16 bits for s_cap scores)
+constexpr int32_t WFA_GROUP_MAX_LEN = 16000;
+size_t wfa_group_lds(int32_t lanes, int32_t words, bool adaptive, int32_t R, int32_t seq_words);
+hipError_t launch_wfa_group(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, const WfaGroup &L,
+                            int32_t lanes, int32_t words, bool adaptive, hipStream_t s);
 
 struct WfaPlan {
   int32_t R, wcap, wcap_lds, seq_words, lds_score_bytes, ring_slots, ring_threads, lds_arena_words;

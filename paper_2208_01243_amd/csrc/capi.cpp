@@ -268,6 +268,7 @@ enum Counter {
   C_W1, C_W1G, C_RL, C_FAIL, C_N0, C_N1, C_N2, C_N3, C_P0, C_P1, C_P2, C_P3, C_TB, C_DTB,
   C_M0, C_M1, C_M2, C_M3, C_WF, C_WS, C_FL, C_FR, C_LL, C_LW, C_LF,
   C_CL = 32,  // WFA window classes 1..4: list lengths, then their work counters (C_CL + 4)
+  C_GL = 40,  // WFA group passes: pairs passed on (C_GL + k), then their work counters (C_GL + 4)
   C_N = 48
 };
 
@@ -286,6 +287,8 @@ constexpr int32_t SMALL_BATCH_LEN = 128;
 constexpr int32_t WFA_MAX_STEP = 1024;
 // WFA-adaptive runs on 16-bit offsets over a window of every diagonal
 constexpr int32_t WFA_ADAPTIVE_MAX_LEN = 16000;
+// Resident wavefronts of the WFA group pass per CU (registers allow 16)
+constexpr int64_t WFA_GROUP_WAVES = 16;
 
 aim_status check_pen(int32_t alg, const aim_penalties &pen) {
   if (alg < AIM_NW_LINEAR || alg > AIM_GENASM) return fail(AIM_ERR_INVALID_ARG, "unknown algorithm %d", alg);
@@ -388,6 +391,43 @@ aim::Scoring wfa_scoring(const aim::Scoring &P) {
 // WFA-adaptive: every pair through the packed wavefront kernel with its
 // ring in a global slot and a window of every diagonal the batch can reach,
 // plus the reduction step.  Wk lists the pairs (a re-run when Wk.direct).
+
+// The group pass (k_wfa_group) takes unit gap extension, and sequences whose
+// offsets and absent marks fit 16 bits.
+bool wfa_group_fits(int32_t L, const aim::Scoring &P) {
+  return P.e == 1 && std::max(P.x, P.o + 1) <= 31 && L > 0 && L <= aim::WFA_GROUP_MAX_LEN;
+}
+
+// Launch shape of one group pass over at most n pairs: workgroups by what a CU
+// holds, each with a ring of origin codes of at least `steps` steps when
+// `share` bytes allow (a pair of more scores goes to the next pass).
+aim_status wfa_group_plan(aim_context *c, int32_t L, const aim::Scoring &P, int64_t n, int32_t lanes, int32_t words,
+                          bool adaptive, int64_t steps, int64_t share, aim::WfaGroup &D) {
+  D.R = std::max(P.x, P.o + 1) + 1;
+  D.seq_words = (L + 31) / 32;
+  D.s_cap = 16000;
+  const size_t lds = aim::wfa_group_lds(lanes, words, adaptive, D.R, D.seq_words);
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / lds, WFA_GROUP_WAVES));
+  const int64_t groups = 64 / lanes;
+  int64_t slots = std::min<int64_t>((n + groups - 1) / groups, (int64_t)c->cus * per_cu);
+  D.as_steps = 64;
+  D.slot_words = 0;
+  D.codes = nullptr;
+  if (P.want_cigar) {
+    int64_t as = 512;
+    while (as < steps) as *= 2;
+    while (as > 512 && as * 64 * words * slots > share) as /= 2;
+    slots = std::max<int64_t>(1, std::min<int64_t>(slots, share / (as * 64 * words)));
+    D.as_steps = (int32_t)as;
+    D.slot_words = as * 16 * words;
+    aim_status st = ensure(c, c->sc->wbits, (size_t)(slots * D.slot_words * 4));
+    if (st) return st;
+    D.codes = static_cast<uint32_t *>(c->sc->wbits.p);
+  }
+  D.nslots = (int32_t)slots;
+  return AIM_OK;
+}
+
 aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                             int64_t n, int32_t L, int32_t *cnt, const aim::Work &Wk, const Tune &tu,
                             hipStream_t s) {
@@ -406,6 +446,35 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   D.walk_fail = cnt + C_WF;
   D.walk_skip = cnt + C_WS;
   const int32_t threads = tu.wfa_cls_threads[0];
+  // Narrow wavefronts first, several pairs per wavefront: the reduction keeps
+  // a wavefront's recent range within about max_dist diagonals, so groups of
+  // 32 lanes (16 for short reads, which end before theirs grows) hold nearly
+  // every pair at max_dist 50, and 64 lanes nearly all of the rest; what
+  // leaves those goes on to the kernel below, with every diagonal.
+  aim::Work WG = Wk;
+  if (!Wk.direct && wfa_group_fits(L, P) && c->ad_min <= 50 && c->ad_max <= 100) {
+    const int32_t first = c->ad_max > 50 ? 64 : L <= 192 ? 16 : 32;
+    int32_t *lists[2] = {as<int32_t>(c->sc->list2), as<int32_t>(c->sc->list3)};
+    int k = 0;
+    for (int32_t lanes = first; lanes <= 64; lanes = lanes < 64 ? 64 : 128, ++k) {
+      aim::WfaGroup G{};
+      aim_status st = wfa_group_plan(c, L, P, n, lanes, 1, true, std::max<int64_t>(2048, (int64_t)L * 3 / 4),
+                                     c->limit() / 24, G);
+      if (st) return st;
+      G.over_list = lists[k];
+      G.over_count = cnt + C_GL + k;
+      G.walk_fail = cnt + C_WF;
+      G.ad_min = c->ad_min;
+      G.ad_max = c->ad_max;
+      G.ad_dropped = D.ad_dropped;
+      WG.counter = cnt + C_GL + 4 + k;
+      Phase ph(c, s, "wfa_adaptive");
+      HIP_TRY(aim::launch_wfa_group(S, O, P, WG, G, lanes, 1, true, s));
+      WG.idx = G.over_list;
+      WG.count = G.over_count;
+    }
+    WG.counter = Wk.counter;
+  }
   // the ring in LDS when a window of every diagonal is small (short reads:
   // no global round trips per score, and the walk's tokens in LDS too),
   // else in a global slot
@@ -415,10 +484,10 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds, 2048 / threads));
   int32_t nslots = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * per_cu);
   // per workgroup slot: the ring (with its guard word) and, with CIGARs, the
-  // score table and the origin codes of every kept score, within a third of
+  // score table and the origin codes of every kept score, within 5/16 of
   // the budget each way (fewer workgroups when they do not fit)
   D.gring_slot = lds_ring ? 0 : (aim::wfa_ring_words(D.W, D.MG, D.R, P.e) + 1 + 63) / 64 * 64;
-  const int64_t share = c->limit() / 3;
+  const int64_t share = c->limit() * 5 / 16;
   if (!lds_ring) nslots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nslots, share / (D.gring_slot * 4)));
   // scores kept: up to what any alignment of the batch can cost (2 L ops at
   // the dearest step), at most s_cap; codes: up to the widest row at every
@@ -437,8 +506,8 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   D.gring = lds_ring ? nullptr : as<uint32_t>(c->sc->wgring);
   D.codes = as<uint8_t>(c->sc->wlds);
   c->last_class_window[0] = D.W;
-  Phase ph(c, s, Wk.direct ? "wfa_adaptive_rerun" : "wfa_adaptive");
-  HIP_TRY(aim::launch_wfa_lds(S, O, P, Wk, D, threads, nslots, s));
+  Phase ph(c, s, Wk.direct ? "wfa_adaptive_rerun" : WG.idx != Wk.idx ? "wfa_adaptive_wide" : "wfa_adaptive");
+  HIP_TRY(aim::launch_wfa_lds(S, O, P, WG, D, threads, nslots, s));
   return AIM_OK;
 }
 
@@ -530,6 +599,10 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   if (tu.wfa_c16 > 0) C16 = std::min(C16, tu.wfa_c16);
   const bool w16 = !plain && L <= aim::WFA16_MAX_LEN && pl.R <= 32 && pl.seq_words > 0 &&
                    aim::wfa_score16_lds(WL, P.e, C16) <= 48 * 1024;
+  // ... or, with unit gap extension, groups of 64 lanes with one word of two
+  // diagonals a lane (two when the tune asks for a window past 128 diagonals)
+  const bool group = w16 && wfa_group_fits(L, P);
+  const int32_t gwords = tu.wfa_c16 > 2 ? 2 : 1;
   WL.store16 = w16;  // the full store of the fallback pass holds 16-bit offsets
   // Window classes for the pairs that leave the one-wavefront window: LDS
   // windows of growing width, each pair routed to the first that holds its
@@ -553,7 +626,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     // bound only picks the workgroup size.
     const int32_t full = (int32_t)std::min<int64_t>(32768, (2 * (int64_t)L + 2 + 3) / 4 * 4 + 4);
     const int32_t bound[3] = {512, 1536, INT32_MAX};
-    int32_t prev_half = 32 * C16;
+    int32_t prev_half = group ? 64 * gwords : 32 * C16;
     for (int k = 0; k < 3; ++k) {
       // this class's own tune, if one is kept for its length bucket
       const int32_t cb = len_bucket_host(k < 2 ? bound[k] : L);
@@ -589,7 +662,27 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     route.count[route.nclass] = cnt + C_RL;
     route.pred = lists + (int64_t)n * 10;
   }
-  if (w16) {
+  if (group) {
+    aim::WfaGroup G{};
+    if ((st = wfa_group_plan(c, L, P, n, 64, gwords, false, 2048, c->limit() / 8, G))) return st;
+    for (int k = 0; k < 4; ++k) {
+      G.need_cap[k] = WL.need_cap[k];
+      G.need_list[k] = WL.need_list[k];
+      G.need_count[k] = WL.need_count[k];
+      G.need_max[k] = WL.need_max[k];
+    }
+    G.need = WL.need;
+    G.walk_fail = WL.walk_fail;
+    G.long_list = WL.long_list;
+    G.long_count = WL.long_count;
+    G.route = route;
+    aim::Work W{order, order_count, n, cnt + C_W1, nullptr, nullptr, 0};
+    {
+      Phase ph(c, s, "wfa_score");
+      HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, 64, gwords, false, s));
+    }
+    c->last_window = 128 * gwords;
+  } else if (w16) {
     const int32_t nslots16 = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * 28);
     aim::WfaLaunch A = WL;
     if (P.want_cigar) {
@@ -611,6 +704,8 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       HIP_TRY(aim::launch_wfa_score16(S, O, P, W, A, C16, nslots16, s));
     }
     c->last_window = 64 * C16;
+  }
+  if (w16) {
     // the LDS-window classes, narrowest first; origin codes in one buffer
     // the classes share (they run one after the other on this stream)
     std::vector<aim::WfaLds> LL(cls.size());
@@ -880,7 +975,9 @@ static aim_status check_batch(const aim_batch *B) {
 
 // The batch as 2-bit words (packed into scratch unless it already is) and
 // the per-pair validity flags in c->sc->flags.
-static aim_status prep_inputs(aim_context *c, const aim_batch *B, hipStream_t s, aim::Seqs &S) {
+// pool_off non-null: set to -1 for every pair on the way.
+static aim_status prep_inputs(aim_context *c, const aim_batch *B, hipStream_t s, aim::Seqs &S,
+                              int64_t *pool_off = nullptr) {
   aim_status st;
   const int64_t n = B->n_pairs;
   const int32_t L = B->max_len;
@@ -912,7 +1009,7 @@ static aim_status prep_inputs(aim_context *c, const aim_batch *B, hipStream_t s,
     pf = as<int8_t>(c->sc->pflag);
     tf = as<int8_t>(c->sc->tflag);
   }
-  HIP_TRY(aim::launch_pair_flags(n, L, B->pat_len, B->txt_len, pf, tf, as<int8_t>(c->sc->flags), s));
+  HIP_TRY(aim::launch_pair_flags(n, L, B->pat_len, B->txt_len, pf, tf, as<int8_t>(c->sc->flags), pool_off, s));
   return AIM_OK;
 }
 
@@ -976,7 +1073,8 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
 
   // ---- input encoding ----
   aim::Seqs S;
-  if ((st = prep_inputs(c, B, s, S))) return st;
+  if ((st = ensure(c, c->sc->pooloff, (size_t)n * 8))) return st;
+  if ((st = prep_inputs(c, B, s, S, as<int64_t>(c->sc->pooloff)))) return st;
 
   // pool for runs beyond the per-pair slot (reset every call)
   // sized from the batch (a quarter of the worst-case run count per pair),
@@ -988,7 +1086,6 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
                                                           n * std::min<int64_t>(2 * (int64_t)L + 1, 8192) / 4))
                     : 1;
   if ((st = ensure(c, c->sc->pool, (size_t)pool_cap * 4))) return st;
-  if ((st = ensure(c, c->sc->pooloff, (size_t)n * 8))) return st;
   HIP_TRY(aim::launch_fill_i32(as<int32_t>(c->sc->total) + 2, 0, 2, s));
   // a2: length buckets, longest first (LPT order for the persistent queues)
   const Tune tu = tune_for(c, alg, L);

@@ -13,7 +13,7 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
 }
 
 __global__ void k_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
-                             const int8_t *pf, const int8_t *tf, int8_t *flags) {
+                             const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t a = pl[i], b = tl[i];
@@ -21,6 +21,7 @@ __global__ void k_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, cons
     if (pf && pf[i]) f = 1;
     if (tf && tf[i]) f = 1;
     flags[i] = f;
+    if (pool_off) pool_off[i] = -1;
   }
 }
 
@@ -172,46 +173,77 @@ __global__ void k_cut(int64_t n, const int64_t *excl, int64_t cap, unsigned long
   }
 }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// One pair per thread.  Slots hold a pair's runs last-op-first; slot_cap is a
-// multiple of 4 and slots are 16-byte aligned, so each 16-byte load stays in
-// the pair's slot.
-__global__ __launch_bounds__(256) void k_scatter(
-    int64_t n, const int64_t *__restrict__ excl, const unsigned long long *__restrict__ tw_p,
+// One wavefront per `per` pairs (a power of two, at most 64), whose runs are
+// one range of the output: lane by lane over the range's runs, each finding
+// its pair by bisection of the pairs' offsets in LDS.  The output is written
+// in order and no run waits for another, where a thread per pair copied its
+// runs one by one (10,000 pairs of a thousand runs each: 10,000 serial
+// chains, 0.66 ms; 1,000,000 pairs of 26 runs: 0.20 ms, now 0.08).
+constexpr int SCATTER_AHEAD = 4;  // runs a lane has in flight
+__global__ __launch_bounds__(64) void k_scatter(
+    int64_t n, int32_t per, const int64_t *__restrict__ excl, const unsigned long long *__restrict__ tw_p,
     const int32_t *__restrict__ nruns, const uint32_t *__restrict__ slot, int32_t slot_cap,
     const uint32_t *__restrict__ pool, const int64_t *__restrict__ pool_off,
     int64_t *__restrict__ cigar_off, uint32_t *__restrict__ cigar, int32_t *spill_idx,
     int32_t *spill_count, int8_t *__restrict__ status) {
+  // per pair: where its runs begin in the range, and where they lie, last op
+  // first: run k at src[k], for k >= the slot's capacity at src2[k].  (64
+  // pairs have fewer than 2^28 runs: at most 2 max_len + 1 each)
+  __shared__ int32_t off[65];
+  __shared__ const uint32_t *src[64], *src2[64];
+  const int lane = threadIdx.x;
   const int64_t tw = (int64_t)*tw_p;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t a = excl[i], b = excl[i + 1];
+  const int64_t i0 = (int64_t)blockIdx.x * per, i = i0 + lane;
+  const bool mine = lane < per && i < n;
+  const int64_t base = excl[i0];
+  const int64_t a = excl[i < n ? i : n], b = excl[i < n ? i + 1 : n];
+  if (mine) {
     cigar_off[i] = a < tw ? a : tw;
     if (i + 1 == n) cigar_off[n] = tw;
-    const int32_t r = nruns[i];
-    if (r == 0) continue;
+  }
+  const int32_t r = mine ? nruns[i] : 0;
+  const uint32_t *s1 = nullptr, *s2 = nullptr;
+  if (r > 0) {
+    const int64_t pb = pool_off[i];
     if (b > tw) {
       status[i] = ST_OVERFLOW;
-      continue;
-    }
-    const int64_t pb = r > slot_cap ? pool_off[i] : -1;
-    if (r > slot_cap && pb < 0) {
+    } else if (pb >= POOL_OFF_WHOLE) {
+      s1 = s2 = pool + (pb - POOL_OFF_WHOLE);
+    } else if (pb <= POOL_OFF_TAIL) {
+      s1 = s2 = slot + (i + 1) * (int64_t)slot_cap - r;
+    } else if (r <= slot_cap || pb >= 0) {
+      s1 = slot + i * (int64_t)slot_cap;
+      s2 = r > slot_cap ? pool + pb - slot_cap : s1;
+    } else {
       const int32_t k = atomicAdd(spill_count, 1);
       spill_idx[k] = (int32_t)i;
-      continue;
     }
-    const uint32_t *src = slot + i * (int64_t)slot_cap;
-    uint32_t *dst = cigar + a + r - 1;  // run k goes to dst[-k]
-    const int32_t r0 = r < slot_cap ? r : slot_cap;
-    for (int32_t k = 0; k < r0; k += 4) {
-      const u32x4 v = *reinterpret_cast<const u32x4 *>(src + k);
-      dst[-k] = v.x;
-      if (k + 1 < r0) dst[-k - 1] = v.y;
-      if (k + 2 < r0) dst[-k - 2] = v.z;
-      if (k + 3 < r0) dst[-k - 3] = v.w;
+  }
+  if (lane < per) {
+    src[lane] = s1;
+    src2[lane] = s2;
+    off[lane] = (int32_t)(a - base);
+    if (lane == per - 1) off[per] = (int32_t)(b - base);
+  }
+  __syncthreads();
+  const int32_t end = off[per];
+  for (int32_t e0 = lane; e0 < end; e0 += 64 * SCATTER_AHEAD) {
+    uint32_t v[SCATTER_AHEAD];
+    bool have[SCATTER_AHEAD];
+#pragma unroll
+    for (int u = 0; u < SCATTER_AHEAD; ++u) {
+      const int32_t e = min(e0 + 64 * u, end - 1);
+      int p = 0;  // the last pair that begins at or before e
+      for (int w = per >> 1; w > 0; w >>= 1)
+        if (off[p + w] <= e) p += w;
+      const int32_t k = off[p + 1] - 1 - e;
+      const uint32_t *s = k < slot_cap ? src[p] : src2[p];
+      have[u] = s != nullptr && e0 + 64 * u < end;
+      if (have[u]) v[u] = s[k];
     }
-    for (int32_t k = r0; k < r; ++k) dst[-k] = pool[pb + (k - slot_cap)];
+#pragma unroll
+    for (int u = 0; u < SCATTER_AHEAD; ++u)
+      if (have[u]) cigar[base + e0 + 64 * u] = v[u];
   }
 }
 
@@ -301,10 +333,11 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
 }
 
 hipError_t launch_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
-                             const int8_t *pf, const int8_t *tf, int8_t *flags, hipStream_t s) {
+                             const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off,
+                             hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pair_flags, grid_for(n, 256), dim3(256), 0, s, n, max_len, pl, tl, pf, tf,
-                     flags);
+                     flags, pool_off);
   return hipGetLastError();
 }
 
@@ -365,7 +398,11 @@ hipError_t launch_compact(int64_t n, const Outs &O, int64_t *cigar_off, uint32_t
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, tw);
   if (n > 0) {
     hipLaunchKernelGGL(k_cut, grid_for(n, 256), dim3(256), 0, s, n, excl, cigar_cap, tw);
-    hipLaunchKernelGGL(k_scatter, grid_for(n, 256), dim3(256), 0, s, n, excl,
+    // 64 pairs per wavefront, fewer where that would leave the chip short of
+    // wavefronts (under 4,096)
+    int32_t per = 64;
+    while (per > 1 && n / per < 4096) per /= 2;
+    hipLaunchKernelGGL(k_scatter, dim3((unsigned)((n + per - 1) / per)), dim3(64), 0, s, n, per, excl,
                        (const unsigned long long *)tw, O.nruns, O.slot, O.slot_cap, O.pool,
                        O.pool_off, cigar_off, cigar, spill_idx, spill_count, status);
   } else {

@@ -10,7 +10,21 @@ constexpr int ENTRY = 4;                // table entry: lo, hi, base, present-bi
 constexpr int TAB16 = 8;                // one-wavefront score pass: ranges of I, D, M
 constexpr int32_t EMPTY_LO = 0x3fffffff, EMPTY_HI = -0x3fffffff;  // an empty range
 
+// Two 16-bit offsets in one register, packed arithmetic.
+constexpr uint32_t ABSENT2 = 0x80008000u;
 
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ s16x2 as2(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
+__device__ __forceinline__ uint32_t as1(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
+// Index of the lowest set bit, all ones for 0 (the instruction's own result;
+// the C builtins leave 0 undefined or add a select for it).
+__device__ __forceinline__ uint32_t ffbl_raw(uint32_t d) {
+  uint32_t r;
+  asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(d));
+  return r;
+}
 
 __device__ __forceinline__ uint64_t seq_window(const uint64_t *w, int64_t nw, int64_t t) {
   // 32 bases starting at base t (t >= 0); words past the end read as zero

@@ -37,13 +37,6 @@ namespace {
 #include "wfa_common.h"
 
 constexpr int ENTRY_WORDS = 4;  // full-store table entry, as counted by the other passes
-constexpr uint32_t ABSENT2 = 0x80008000u;
-
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ s16x2 as2(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
-__device__ __forceinline__ uint32_t as1(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
-
 // c where c <= lim, else exactly the absent mark; an absent c stays negative.
 // The sign mask is one packed arithmetic shift (written out: left to itself
 // the compiler turns the shift-and-mask into a select, which it does half by
@@ -69,14 +62,6 @@ __device__ __forceinline__ uint32_t codes2(s16x2 X, s16x2 I, s16x2 Mv, s16x2 Mo_
   const uint32_t c = (~sio >> 15) & 0x10001u, d = (~sdo >> 15) & 0x10001u;
   const uint32_t nib = (a & ~b) | ((a & b) << 1) | (c << 2) | (d << 3);
   return (nib | (nib >> 12)) & 0xffu;
-}
-
-// Index of the lowest set bit, all ones for 0 (the instruction's own result;
-// the C builtins leave 0 undefined or add a select for it).
-__device__ __forceinline__ uint32_t ffbl_raw(uint32_t d) {
-  uint32_t r;
-  asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(d));
-  return r;
 }
 
 // Equal bases (at most 16, at most le) from pattern base i and text base j.
