@@ -178,7 +178,7 @@ int64_t full_slot_words(int32_t max_len);
 // 1..nclass, each with a wider window (half-width half[c] diagonals around
 // diagonal 0; the last class, the HBM-ring pass, has no bound); the pair
 // joins the first later class whose window holds its predicted extent.
-constexpr int WFA_MAX_CLASSES = 6;
+constexpr int WFA_MAX_CLASSES = 8;
 struct WfaRoute {
   int32_t nclass;
   int32_t half[WFA_MAX_CLASSES];
@@ -311,9 +311,10 @@ struct WfaGroup {
   int32_t as_steps;    // steps the ring of origin codes holds (a power of two, at least 64)
   int64_t slot_words;  // 32-bit words of codes per workgroup: 16 words as_steps
   uint32_t *codes;
-  // pairs that leave the pass: to over_list (a wider group or the general
-  // adaptive kernel), or, without one, to the window classes by predicted extent
-  int32_t *over_list, *over_count;
+  // pairs that leave the pass: by predicted extent to a later class (a wider
+  // group, a window class); adaptive ones to class 1
+  int32_t by_length; // leaving pairs keep the queue's order
+  int32_t my_class;  // this pass's index in the route (0: the first pass)
   WfaRoute route;
   // the full-store fallback of a failed walk, as in WfaLaunch
   int64_t need_cap[4];
@@ -335,6 +336,8 @@ struct WfaGroupArgs {
 };
 // Longest sequence (its offsets and absent marks fit 16 bits for s_cap scores)
 constexpr int32_t WFA_GROUP_MAX_LEN = 16000;
+// int32 work counters of one launch (Work::counter), zeroed before it
+constexpr int32_t WFA_GROUP_COUNTERS = 64 * 32;
 size_t wfa_group_lds(int32_t lanes, int32_t words, bool adaptive, int32_t R, int32_t seq_words);
 hipError_t launch_wfa_group(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, const WfaGroup &L,
                             int32_t lanes, int32_t words, bool adaptive, hipStream_t s);

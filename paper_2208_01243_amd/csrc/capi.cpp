@@ -268,9 +268,12 @@ enum Counter {
   C_W1, C_W1G, C_RL, C_FAIL, C_N0, C_N1, C_N2, C_N3, C_P0, C_P1, C_P2, C_P3, C_TB, C_DTB,
   C_M0, C_M1, C_M2, C_M3, C_WF, C_WS, C_FL, C_FR, C_LL, C_LW, C_LF,
   C_CL = 32,  // WFA window classes 1..4: list lengths, then their work counters (C_CL + 4)
-  C_GL = 40,  // WFA group passes: pairs passed on (C_GL + k), then their work counters (C_GL + 4)
-  C_N = 48
+  C_GL = 40,  // WFA group passes: pairs passed on
+  C_N = 48,   // (then the 64-bit adaptive drop count)
+  C_GQ = 64,  // work counters of up to four WFA group passes
+  C_ALL = C_GQ + 4 * aim::WFA_GROUP_COUNTERS
 };
+int32_t *group_counter(int32_t *cnt, int pass) { return cnt + C_GQ + pass * aim::WFA_GROUP_COUNTERS; }
 
 // Smallest batch for which the packed band tier's traceback is walked by a
 // separate kernel beside the escalation tiers by default.
@@ -285,10 +288,18 @@ constexpr int32_t SMALL_BATCH_LEN = 128;
 
 // WFA requires a bounded ring of past wavefronts: max(x, o + e) <= this.
 constexpr int32_t WFA_MAX_STEP = 1024;
+// NW/SWG batches below SPLIT_MIN_PAIRS pairs, or of reads over WFA_BAND_LEN,
+// take the wavefront passes at once: their time grows with the score, where
+// the band's first tier walks every row of every pair one lane each, and what
+// it escalates again.  Band / wavefront on MI355X: 4,096 x 100-1,000 bp affine at
+// 1-8 % 4.1 / 1.0 ms, 2,048 x 100-1,000 bp edit distance 2.1 / 0.3, 8,192 x
+// 100 bp 0.20 / 0.10, 65,536 x 150 bp affine at 1-8 % 0.82 / 0.43, 262,144 x
+// 100-300 bp 3.4 / 1.8.  Short reads in larger batches fill the band's lanes and
+// overlap its walks: 1,000,000 x 100 bp at 8 % 2.2 / 3.6 ms (at 2 % 1.6 / 1.4),
+// 1,000,000 x 150 bp at 4 % the same.
+constexpr int32_t WFA_BAND_LEN = 192;
 // WFA-adaptive runs on 16-bit offsets over a window of every diagonal
 constexpr int32_t WFA_ADAPTIVE_MAX_LEN = 16000;
-// Resident wavefronts of the WFA group pass per CU (registers allow 16)
-constexpr int64_t WFA_GROUP_WAVES = 16;
 
 aim_status check_pen(int32_t alg, const aim_penalties &pen) {
   if (alg < AIM_NW_LINEAR || alg > AIM_GENASM) return fail(AIM_ERR_INVALID_ARG, "unknown algorithm %d", alg);
@@ -398,25 +409,34 @@ bool wfa_group_fits(int32_t L, const aim::Scoring &P) {
   return P.e == 1 && std::max(P.x, P.o + 1) <= 31 && L > 0 && L <= aim::WFA_GROUP_MAX_LEN;
 }
 
+// Whether a NW/SWG batch goes to the wavefront passes at once rather than
+// through the band tiers.
+bool band_by_wfa(const aim::Scoring &P, const Tune &tu, int64_t n, int32_t L) {
+  return tu.band_w0 == 32 && tu.band16 == 3 && (n < SPLIT_MIN_PAIRS || L > WFA_BAND_LEN) &&
+         wfa_group_fits(L, wfa_scoring(P)) && L <= 10240;
+}
+
 // Launch shape of one group pass over at most n pairs: workgroups by what a CU
-// holds, each with a ring of origin codes of at least `steps` steps when
-// `share` bytes allow (a pair of more scores goes to the next pass).
+// holds (registers: 16 wavefronts, 12 at four words a lane), each with a ring of
+// origin codes of `steps` steps, fewer (but at least `least`) where that takes
+// more than `share` bytes, then fewer workgroups (a pair of more scores than
+// the ring holds goes to the next pass).
 aim_status wfa_group_plan(aim_context *c, int32_t L, const aim::Scoring &P, int64_t n, int32_t lanes, int32_t words,
-                          bool adaptive, int64_t steps, int64_t share, aim::WfaGroup &D) {
+                          bool adaptive, int64_t steps, int64_t least, int64_t share, aim::WfaGroup &D) {
   D.R = std::max(P.x, P.o + 1) + 1;
   D.seq_words = (L + 31) / 32;
   D.s_cap = 16000;
   const size_t lds = aim::wfa_group_lds(lanes, words, adaptive, D.R, D.seq_words);
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / lds, WFA_GROUP_WAVES));
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / lds, words == 4 ? 12 : 16));
   const int64_t groups = 64 / lanes;
   int64_t slots = std::min<int64_t>((n + groups - 1) / groups, (int64_t)c->cus * per_cu);
   D.as_steps = 64;
   D.slot_words = 0;
   D.codes = nullptr;
   if (P.want_cigar) {
-    int64_t as = 512;
+    int64_t as = 64;
     while (as < steps) as *= 2;
-    while (as > 512 && as * 64 * words * slots > share) as /= 2;
+    while (as / 2 >= least && as * 64 * words * slots > share) as /= 2;
     slots = std::max<int64_t>(1, std::min<int64_t>(slots, share / (as * 64 * words)));
     D.as_steps = (int32_t)as;
     D.slot_words = as * 16 * words;
@@ -458,20 +478,21 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
     int k = 0;
     for (int32_t lanes = first; lanes <= 64; lanes = lanes < 64 ? 64 : 128, ++k) {
       aim::WfaGroup G{};
-      aim_status st = wfa_group_plan(c, L, P, n, lanes, 1, true, std::max<int64_t>(2048, (int64_t)L * 3 / 4),
+      aim_status st = wfa_group_plan(c, L, P, n, lanes, 1, true, std::max<int64_t>(2048, (int64_t)L * 3 / 4), 512,
                                      c->limit() / 24, G);
       if (st) return st;
-      G.over_list = lists[k];
-      G.over_count = cnt + C_GL + k;
+      G.route.nclass = 1;
+      G.route.list[1] = lists[k];
+      G.route.count[1] = cnt + C_GL + k;
       G.walk_fail = cnt + C_WF;
       G.ad_min = c->ad_min;
       G.ad_max = c->ad_max;
       G.ad_dropped = D.ad_dropped;
-      WG.counter = cnt + C_GL + 4 + k;
-      Phase ph(c, s, "wfa_adaptive");
+      WG.counter = group_counter(cnt, k);
+      Phase ph(c, s, k == 0 ? "wfa_adaptive" : "wfa_adaptive_b");
       HIP_TRY(aim::launch_wfa_group(S, O, P, WG, G, lanes, 1, true, s));
-      WG.idx = G.over_list;
-      WG.count = G.over_count;
+      WG.idx = G.route.list[1];
+      WG.count = G.route.count[1];
     }
     WG.counter = Wk.counter;
   }
@@ -492,13 +513,15 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   // scores kept: up to what any alignment of the batch can cost (2 L ops at
   // the dearest step), at most s_cap; codes: up to the widest row at every
   // kept score, at most 4 MiB per slot (a pair needing more gets no CIGAR)
-  const int64_t steps = std::min<int64_t>(D.s_cap, 2 * (int64_t)L * std::max(P.x, P.o + P.e) + 1) + 1;
+  // (gap runs over both sequences bound every score)
+  const int64_t steps =
+      std::min<int64_t>(D.s_cap, std::min<int64_t>(2 * (int64_t)L * std::max(P.x, P.o + P.e), 2 * ((int64_t)P.o + (int64_t)L * P.e)) + 1) + 1;
   D.steps_cap = P.want_cigar ? (int32_t)steps : 0;
   if (P.want_cigar) {
     const int64_t fixed = (int64_t)D.steps_cap * 12;
     nslots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nslots, share / (fixed + (256 << 10))));
     const int64_t most = std::min<int64_t>(steps * (D.W / 2 + 1), (int64_t)4 << 20);
-    D.code_cap = std::max<int64_t>(std::min<int64_t>(share / nslots - fixed, most), 256 << 10);
+    D.code_cap = std::min<int64_t>(most, std::max<int64_t>(share / nslots - fixed, 256 << 10));
   }
   D.code_slot = ((int64_t)D.steps_cap * 12 + D.code_cap + 255) / 256 * 256;
   if (!lds_ring && (st = ensure(c, c->sc->wgring, (size_t)D.gring_slot * 4 * nslots))) return st;
@@ -545,6 +568,9 @@ aim_status wfa_long_plan(aim_context *c, int32_t L, const aim::Scoring &P, const
   LG.wt_cap = std::min(LG.sw_cap, 1 << 16);
   LG.tok_cap = 2 * (2 * L + 1) + 8;
   LG.code_cap = std::max<int64_t>(1 << 20, std::min<int64_t>(16 << 20, c->limit() / 64)) / 16 * 16;
+  // (no more than every score of a pair at its widest)
+  const int64_t most = ((int64_t)LG.sw_cap + 1) * (L + 1);
+  LG.code_cap = std::min<int64_t>(LG.code_cap, std::max<int64_t>(4096, (most + 15) / 16 * 16));
   LG.slot_words = aim::wfa_long_slot_words(LG, i16);
   const int64_t fit = c->limit() / 16 / (LG.slot_words * 4);
   if (fit < 1) return AIM_OK;
@@ -555,17 +581,130 @@ aim_status wfa_long_plan(aim_context *c, int32_t L, const aim::Scoring &P, const
   return AIM_OK;
 }
 
+// The group passes of a WFA call, narrowest first: a pair starts in the first
+// and goes on by its predicted extent.
+struct GroupPass {
+  int32_t lanes, words;  // words of two diagonals a lane
+  int32_t reach() const { return lanes * words - 3; }
+};
+// The furthest diagonal that a pair of the batch can reach before it is
+// aligned or rejected, and the highest score it can take (unit gap extension:
+// a score reaches score - o; gap runs over both sequences bound the optimum).
+int32_t wfa_reach(const aim::Scoring &P, int32_t L) {
+  return P.max_score >= 0 ? std::min(L, std::max(0, P.max_score - P.o)) : L;
+}
+int32_t wfa_most_scores(const aim::Scoring &P, int32_t L) {
+  const int32_t most = 2 * (P.o + L);
+  return P.max_score >= 0 ? std::min(most, P.max_score) : most;
+}
+// Where pairs start.  Too narrow a first pass is time spent twice, too wide a
+// one lanes without cells.  The reach expected of a batch is a sixth of its
+// reads' length under gap-affine penalties (5 % errors; a third in small
+// batches, whose time is that of their slowest pair, so that it starts where
+// it ends) and a tenth under linear ones; reads whose expected reach passes the
+// widest group start narrow, to leave it early.  Measured on MI355X, starting
+// in 32 / 64 / 128 / 256 lane words: 262,144 x 100 bp affine at 2 % 0.46 / 0.54 /
+// - / - ms; 32,768 x 100-300 bp at 1-8 % 0.57 / 0.49 / 0.42 / 0.64; 32,768 x
+// 1 kbp at 1-8 % 4.8 / 4.9 / 4.2 / 3.7; 2,048 x 100-300 bp at 8 % 0.35 / 0.32 /
+// 0.15 / 0.18; 32,768 x 1 kbp linear at 8 % 1.8 / 1.6 / 1.0 / 1.5.
+std::vector<GroupPass> wfa_group_passes(const aim::Scoring &P, int32_t L, bool small, const Tune &tu) {
+  static const GroupPass all[5] = {{16, 1}, {32, 1}, {64, 1}, {64, 2}, {64, 4}};
+  const int32_t reach = wfa_reach(P, L);
+  const int32_t want = std::min(reach, P.o == 0 ? L / 10 : small ? L / 3 : L / 6);
+  int k = 1;
+  if (tu.wfa_c16 > 0) {
+    k = tu.wfa_c16 == 1 ? 2 : tu.wfa_c16 == 2 ? 3 : 4;
+  } else {
+    while (k < 4 && all[k].reach() < want) ++k;
+    if (!small && want > all[4].reach()) k = 2;
+  }
+  while (k > 0 && all[k - 1].reach() >= reach) --k;  // no wider than any pair needs
+  std::vector<GroupPass> passes;
+  for (; k < 5; ++k) {
+    passes.push_back(all[k]);
+    if (all[k].reach() >= reach) break;  // no pair leaves it
+  }
+  return passes;
+}
+constexpr int64_t WFA_RING_STEPS = 2048;  // steps of codes a wavefront keeps (more if a pair can need them)
+
+// The passes' launches over the listed pairs; pass k > 0 takes the pairs of
+// route class k.  G: what they share.
+aim_status launch_group_passes(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
+                               int32_t L, int32_t *cnt, const int32_t *order, const int32_t *order_count,
+                               const std::vector<GroupPass> &passes, int64_t least, int64_t share, aim::WfaGroup G,
+                               hipStream_t s) {
+  static const char *names[4] = {"wfa_score", "wfa_score_b", "wfa_score_c", "wfa_score_d"};
+  for (size_t k = 0; k < passes.size(); ++k) {
+    const GroupPass &gp = passes[k];
+    aim_status st = wfa_group_plan(c, L, P, n, gp.lanes, gp.words, false, std::max<int64_t>(WFA_RING_STEPS, least), least, share, G);
+    if (st) return st;
+    G.my_class = (int32_t)k;
+    aim::Work W{order, order_count, n, group_counter(cnt, (int)k), nullptr, nullptr, 0};
+    if (k > 0) {
+      W.idx = G.route.list[k];
+      W.count = G.route.count[k];
+    }
+    Phase ph(c, s, names[k]);
+    HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, gp.lanes, gp.words, false, s));
+  }
+  c->last_window = 2 * passes[0].lanes * passes[0].words;
+  return AIM_OK;
+}
+
+// Batches whose pairs all stay in the group passes (short reads, or a low
+// threshold): those passes alone, with no list, ring or store of the others.
+// (A walk cannot fail on codes that were kept; if one did its pair would get
+// CIGAR_OVERFLOW.)  `done` false: not such a batch, nothing launched.
+aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n, int32_t L,
+                         int32_t *cnt, const int32_t *order, const int32_t *order_count,
+                         const std::vector<GroupPass> &passes, hipStream_t s, bool &done) {
+  done = false;
+  const int32_t most = wfa_most_scores(P, L);
+  if (passes.back().reach() < wfa_reach(P, L) || most > 16000) return AIM_OK;
+  const int64_t share = c->limit() / 8;
+  if (P.want_cigar) {
+    // every pass must hold the codes of any pair, in 64 workgroups at least
+    for (const GroupPass &gp : passes)
+      if (share < 2 * ((int64_t)most + 8) * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
+  }
+  aim_status st;
+  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * (passes.size() > 1 ? passes.size() : 1)))) return st;
+  int32_t *lists = as<int32_t>(c->sc->wlists);
+  aim::WfaGroup G{};
+  G.walk_fail = cnt + C_WF;
+  G.route.nclass = (int32_t)passes.size() - 1;
+  for (size_t k = 1; k < passes.size(); ++k) {
+    G.route.half[k] = passes[k].reach();
+    G.route.list[k] = lists + (int64_t)n * k;
+    G.route.count[k] = cnt + C_GL + (int32_t)k - 1;
+  }
+  G.route.pred = lists;
+  done = true;
+  return launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, (int64_t)most + 8, share, G, s);
+}
+
 aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                    int64_t n, int32_t L, bool plain, int32_t *cnt, const int32_t *order,
                    const int32_t *order_count, const Tune &tu, hipStream_t s) {
   aim_status st;
   const aim::Scoring P = wfa_scoring(Pin);
+  const bool small = n <= (int64_t)c->cus * 16;
+  const bool group = !plain && wfa_group_fits(L, P) && L <= 10240;
+  std::vector<GroupPass> passes;
+  if (group) {
+    passes = wfa_group_passes(P, L, small, tu);
+    bool done = false;
+    if ((st = run_wfa_short(c, S, O, P, n, L, cnt, order, order_count, passes, s, done))) return st;
+    if (done) return AIM_OK;
+  }
   const aim::WfaPlan pl = aim::wfa_plan(L, P, c->limit(), c->cus, plain, tu.wfa_ring_kb,
                                         tu.wfa_trace_kb, tu.wfa_long_threads, c->strict());
   if ((st = ensure(c, c->sc->wneed, (size_t)n * 8))) return st;
   // lists: [0] the HBM-ring pass, [1-4] full-store classes, [5] unused,
-  // [6-9] LDS-window classes, [10] predicted extents
-  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * 12))) return st;
+  // [6-9] LDS-window classes, [10] predicted extents, [11] long pairs, [12-15]
+  // wider group passes
+  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * 16))) return st;
   int32_t *lists = as<int32_t>(c->sc->wlists);
   aim::WfaLaunch WL{};
   WL.R = pl.R;
@@ -597,12 +736,8 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   // one wavefront per pair with 16-bit offsets over a window of 64 C diagonals
   int32_t C16 = (int32_t)std::min<int64_t>(4, std::max<int64_t>(1, (pl.wcap + 63) / 64));
   if (tu.wfa_c16 > 0) C16 = std::min(C16, tu.wfa_c16);
-  const bool w16 = !plain && L <= aim::WFA16_MAX_LEN && pl.R <= 32 && pl.seq_words > 0 &&
-                   aim::wfa_score16_lds(WL, P.e, C16) <= 48 * 1024;
-  // ... or, with unit gap extension, groups of 64 lanes with one word of two
-  // diagonals a lane (two when the tune asks for a window past 128 diagonals)
-  const bool group = w16 && wfa_group_fits(L, P);
-  const int32_t gwords = tu.wfa_c16 > 2 ? 2 : 1;
+  const bool w16 = group || (!plain && L <= aim::WFA16_MAX_LEN && pl.R <= 32 && pl.seq_words > 0 &&
+                             aim::wfa_score16_lds(WL, P.e, C16) <= 48 * 1024);
   WL.store16 = w16;  // the full store of the fallback pass holds 16-bit offsets
   // Window classes for the pairs that leave the one-wavefront window: LDS
   // windows of growing width, each pair routed to the first that holds its
@@ -626,19 +761,22 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     // bound only picks the workgroup size.
     const int32_t full = (int32_t)std::min<int64_t>(32768, (2 * (int64_t)L + 2 + 3) / 4 * 4 + 4);
     const int32_t bound[3] = {512, 1536, INT32_MAX};
-    int32_t prev_half = group ? 64 * gwords : 32 * C16;
+    int32_t prev_half = group ? passes.back().reach() - 1 : 32 * C16;
     for (int k = 0; k < 3; ++k) {
       // this class's own tune, if one is kept for its length bucket
       const int32_t cb = len_bucket_host(k < 2 ? bound[k] : L);
       const auto ct = c->class_tunes.find({AIM_WFA_AFFINE, cb});
       const ClassTune *ctp = ct == c->class_tunes.end() ? nullptr : &ct->second;
-      const bool glob = (ctp && ctp->global >= 0) ? ctp->global != 0 : ((tu.wfa_cls_global >> k) & 1) != 0;
-      const int32_t w = glob ? full : std::min<int64_t>((int64_t)2 * std::min(bound[k], wmax / 2), wmax);
+      const bool fits = aim::wfa_lds_bytes(full, MG, pl.R, P.e, pl.seq_words, false) <= 64 * 1024;
+      const bool glob = (ctp && ctp->global >= 0) ? ctp->global != 0
+                        : small && fits            ? false
+                                                   : ((tu.wfa_cls_global >> k) & 1) != 0;
+      const int32_t w = glob || (small && fits) ? full : std::min<int64_t>((int64_t)2 * std::min(bound[k], wmax / 2), wmax);
       const int32_t half = glob ? bound[k] : w / 2;
       if (std::min(half, w / 2) <= prev_half) continue;
       const size_t lds = aim::wfa_lds_bytes(w, MG, pl.R, P.e, pl.seq_words, glob);
       if (lds > lds_cap) continue;
-      const int32_t th = (ctp && ctp->threads > 0) ? ctp->threads : tu.wfa_cls_threads[k];
+      const int32_t th = (ctp && ctp->threads > 0) ? ctp->threads : small ? 256 : tu.wfa_cls_threads[k];
       c->last_class_bucket[cls.size()] = cb;
       const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(lds_cap / lds, 2048 / th));
       cls.push_back({w, th, (int32_t)std::min<int64_t>(n, (int64_t)c->cus * per_cu), glob, half});
@@ -650,12 +788,18 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     if (!cls.empty() && cls.back().W >= 2 * L + 2) cls.back().half = INT32_MAX;
   }
   aim::WfaRoute route{};
+  const int32_t ng = std::max<int32_t>(0, (int32_t)passes.size() - 1);
   if (!plain && w16) {
-    route.nclass = (int32_t)cls.size() + 1;
+    route.nclass = ng + (int32_t)cls.size() + 1;
+    for (int32_t k = 0; k < ng; ++k) {
+      route.half[k + 1] = passes[k + 1].reach();
+      route.list[k + 1] = lists + (int64_t)n * (12 + k);
+      route.count[k + 1] = cnt + C_GL + k;
+    }
     for (size_t k = 0; k < cls.size(); ++k) {
-      route.half[k + 1] = cls[k].half;
-      route.list[k + 1] = lists + (int64_t)n * (6 + k);
-      route.count[k + 1] = cnt + C_CL + (int32_t)k;
+      route.half[ng + k + 1] = cls[k].half;
+      route.list[ng + k + 1] = lists + (int64_t)n * (6 + k);
+      route.count[ng + k + 1] = cnt + C_CL + (int32_t)k;
     }
     route.half[route.nclass] = INT32_MAX;
     route.list[route.nclass] = lists;  // the HBM-ring pass
@@ -664,7 +808,6 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   }
   if (group) {
     aim::WfaGroup G{};
-    if ((st = wfa_group_plan(c, L, P, n, 64, gwords, false, 2048, c->limit() / 8, G))) return st;
     for (int k = 0; k < 4; ++k) {
       G.need_cap[k] = WL.need_cap[k];
       G.need_list[k] = WL.need_list[k];
@@ -676,12 +819,8 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     G.long_list = WL.long_list;
     G.long_count = WL.long_count;
     G.route = route;
-    aim::Work W{order, order_count, n, cnt + C_W1, nullptr, nullptr, 0};
-    {
-      Phase ph(c, s, "wfa_score");
-      HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, 64, gwords, false, s));
-    }
-    c->last_window = 128 * gwords;
+    G.by_length = L > 1024;
+    if ((st = launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, 512, c->limit() / 8, G, s))) return st;
   } else if (w16) {
     const int32_t nslots16 = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * 28);
     aim::WfaLaunch A = WL;
@@ -717,7 +856,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       D.R = pl.R;
       D.seq_words = pl.seq_words;
       D.s_cap = 16000;
-      D.my_class = (int32_t)k + 1;
+      D.my_class = ng + (int32_t)k + 1;
       D.route = route;
       // scores and widest row a pair of this class is expected to need (a
       // pair that needs more leaves its codes to the full-store pass)
@@ -759,7 +898,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       for (size_t k = 0; k < cls.size(); ++k) {
         LL[k].codes = as<uint8_t>(c->sc->wlds);
         LL[k].gring = cls[k].global ? as<uint32_t>(c->sc->wgring) : nullptr;
-        aim::Work WC{route.list[k + 1], route.count[k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
+        aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
         static const char *cls_names[4] = {"wfa_lds1", "wfa_lds2", "wfa_lds3", "wfa_lds4"};
         Phase ph(c, s, cls_names[k]);
         HIP_TRY(aim::launch_wfa_lds(S, O, P, WC, LL[k], cls[k].threads, cls[k].nslots, s));
@@ -1045,7 +1184,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
   // ---- common scratch ----
   const size_t tmp = aim::scan_tmp_elems(n) + (size_t)n + 2;
   if ((st = ensure(c, c->sc->scan_tmp, tmp * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, c->sc->counters, C_N * sizeof(int32_t) + 64))) return st;
+  if ((st = ensure(c, c->sc->counters, C_ALL * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->sc->total, 64))) return st;
   if ((st = ensure(c, c->sc->nruns, (size_t)n * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->sc->spill, (size_t)n * sizeof(int32_t)))) return st;
@@ -1069,7 +1208,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     c->last_class_window[k] = 0;
     c->last_class_bucket[k] = -1;
   }
-  HIP_TRY(aim::launch_fill_i32(cnt, 0, C_N + 2, s));  // + the 64-bit adaptive drop count
+  HIP_TRY(aim::launch_fill_i32(cnt, 0, C_ALL, s));
 
   // ---- input encoding ----
   aim::Seqs S;
@@ -1143,6 +1282,10 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     if ((st = run_wfa_adaptive(c, S, O, P, n, L, cnt, WA, tu, s))) return st;
   } else if (alg == AIM_WFA_AFFINE) {
     if ((st = run_wfa(c, S, O, P, n, L, plain, cnt, order, order_count, tu, s))) return st;
+  } else if (!plain && band_by_wfa(P, tu, n, L)) {
+    // small batches: the wavefront algorithm reaches the same optimum and, with
+    // the same tie order, the same CIGAR
+    if ((st = run_wfa(c, S, O, P, n, L, false, cnt, order, order_count, tune_for(c, AIM_WFA_AFFINE, L), s))) return st;
   } else if (plain) {
     aim::Work W1{nullptr, nullptr, n, cnt + C_T1, nullptr, nullptr, 0};
     if ((st = run_full(W1, n, s))) return st;
@@ -1190,7 +1333,11 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     }
     int32_t *full_list = as<int32_t>(c->sc->list2);
     int32_t *full_count = cnt + C_L2;
-    if (w0 == 32) {
+    // pairs that left the 32 diagonals go to the wavefront passes where those
+    // have their narrow kernels (1,000,000 x 150 bp affine at 8 %, most of them
+    // escalated: 8 ms against 50 through the 64-diagonal band)
+    const bool by_wfa = wfa_group_fits(L, wfa_scoring(P)) && L <= 10240;
+    if (w0 == 32 && !by_wfa) {
       // tier 2: 64-diagonal band for the pairs tier 1 could not decide, one
       // pair per 32 lanes along the anti-diagonal, then a walk per lane
       const int64_t cw = aim::diag_chunk_words(affine, L);
@@ -1229,10 +1376,10 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     // with m x n; the full matrix for short reads (one launch instead of the
     // wavefront passes' six, which small batches notice) and for penalties
     // beyond the wavefront ring's reach
-    if (L > 256 && P.x <= WFA_MAX_STEP && P.o + P.e <= WFA_MAX_STEP) {
-      if ((st = run_wfa(c, S, O, P, n, L, false, cnt, full_list, full_count,
-                        tune_for(c, AIM_WFA_AFFINE, L), s)))
-        return st;
+    if (by_wfa || (L > 256 && P.x <= WFA_MAX_STEP && P.o + P.e <= WFA_MAX_STEP)) {
+      Tune tw = tune_for(c, AIM_WFA_AFFINE, L);
+      if (by_wfa && tw.wfa_c16 == 0) tw.wfa_c16 = 1;  // they are no narrow pairs
+      if ((st = run_wfa(c, S, O, P, n, L, false, cnt, full_list, full_count, tw, s))) return st;
     } else {
       aim::Work W3{full_list, full_count, n, cnt + C_T3, nullptr, nullptr, 0};
       if ((st = run_full(W3, n, s))) return st;
@@ -1253,6 +1400,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
                               as<int64_t>(c->sc->total), as<int32_t>(c->sc->spill), cnt + C_SPILL,
                               R->status, s));
   }
+  if (run_bound <= slot_cap) return AIM_OK;  // every pair's runs fit its slot
   // pairs whose runs exceeded the slot: recompute and write in place
   aim::Work WS{as<int32_t>(c->sc->spill), cnt + C_SPILL, n, cnt + C_SPILL_W, nullptr, nullptr, 1};
   if (alg == AIM_GENASM) {

@@ -35,16 +35,7 @@
 // Words start at diagonals of the end cell's parity, so that it lies in the
 // low half of its word.
 //
-// Arithmetic.  Two diagonals per instruction in packed 16 bits.  Offsets are
-// kept BIAS (32) above their value: each staged sequence has a word of 32
-// bases in front, A's before the pattern and C's before the text, and an
-// absent offset compares there, at base 0, without a mask.  An absent
-// offset is negative.  Its mark starts at -32768 (or, where the table bound
-// cut a candidate, at -32768 plus that offset, at most 16,033 more) and grows
-// by at most one a score, so pairs stay below 16,000 scores here, and texts
-// and patterns at 16,000 bases, and no mark reaches zero.  A
-// candidate passes its table bound min(n, m + k) by at most one (its source
-// was inside its own), so the cut only has to set its sign.
+// Arithmetic.  Two diagonals per instruction in packed 16 bits (wfa_packed.h).
 //
 // Origin codes.  Four bits a cell: X < M, I < M (of the cell), and of the
 // cell as a source, whether I, D were extended rather than opened from it
@@ -59,45 +50,7 @@ namespace {
 
 #include "wfa_common.h"
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-// sign mask of each half
-__device__ __forceinline__ uint32_t sign2(uint32_t v) {
-  uint32_t r;
-  asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(r) : "v"(v));
-  return r;
-}
-__device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) { return as1(__builtin_elementwise_max(as2(a), as2(b))); }
-__device__ __forceinline__ uint32_t min2(uint32_t a, uint32_t b) { return as1(__builtin_elementwise_min(as2(a), as2(b))); }
-__device__ __forceinline__ uint32_t add2(uint32_t a, uint32_t b) { return as1(as2(a) + as2(b)); }
-__device__ __forceinline__ uint32_t sub2(uint32_t a, uint32_t b) { return as1(as2(a) - as2(b)); }
-__device__ __forceinline__ uint32_t subs2(uint32_t a, uint32_t b) {
-  return as1(__builtin_elementwise_sub_sat(as2(a), as2(b)));
-}
-__device__ __forceinline__ uint32_t both(int32_t v) { return (uint32_t)(v & 0xffff) * 0x10001u; }
-__device__ __forceinline__ uint32_t pack2(int32_t lo, int32_t hi) {
-  return __builtin_amdgcn_perm((uint32_t)hi, (uint32_t)lo, 0x05040100u);
-}
-// a where the mask is set, else b (written out: the compiler spends an
-// instruction more on the same bits)
-__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ uint32_t bfi_v(uint32_t mask, uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(mask), "v"(a), "v"(b));
-  return r;
-}
-
-// A condition that is the same in every lane, as a scalar (where the compiler
-// does not see that it is, it keeps the loop's counters in vector registers).
-__device__ __forceinline__ bool uniform(bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; }
-
-// Candidate c against its bound: c, or c with its sign set where c > lim
-// (then c == lim + 1).  An absent c may have its sign set again.
-__device__ __forceinline__ uint32_t cut2(uint32_t c, uint32_t lim) { return (sub2(lim, c) & 0x80008000u) | c; }
+#include "wfa_packed.h"
 
 // The value of the next / previous lane of the group, round the group: lane
 // rotates of the wavefront (64) or of the rows of 16; for groups of 32 the two
@@ -138,50 +91,6 @@ __device__ __forceinline__ uint32_t group_min2(uint32_t v) {
   return v;
 }
 
-// LDS by byte address: the sequences' words are reached from 16-bit fields of
-// packed offsets, whose index arithmetic the compiler otherwise lengthens.
-typedef __attribute__((address_space(3))) uint32_t LdsWord;
-typedef __attribute__((address_space(3))) unsigned char LdsByte;
-__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(LdsByte *)p; }
-
-// 16 bases of a staged sequence from base i (16 i' <= i < 16 i' + 16, at word
-// i' of the sequence at byte address w).
-__device__ __forceinline__ uint32_t bases16(uint32_t w, uint32_t word, uint32_t shift) {
-  const LdsWord *p = (const LdsWord *)(uintptr_t)(w + (word << 2));
-  return __builtin_amdgcn_alignbit(p[1], p[0], shift);
-}
-__device__ __forceinline__ uint32_t bases16(uint32_t w, int32_t i) {
-  return bases16(w, (uint32_t)i >> 4, (uint32_t)i << 1);
-}
-// ... from the base in the low / high half of a packed pair of indices
-__device__ __forceinline__ uint32_t bases16_lo(uint32_t w, uint32_t ii) {
-  uint32_t word;
-  asm("v_bfe_u32 %0, %1, 4, 12" : "=v"(word) : "v"(ii));
-  return bases16(w, word, ii << 1);
-}
-__device__ __forceinline__ uint32_t bases16_hi(uint32_t w, uint32_t ii) {
-  uint32_t word;
-  asm("v_lshrrev_b32 %0, 20, %1" : "=v"(word) : "v"(ii));
-  return bases16(w, word, ii >> 15);
-}
-
-// Equal bases from base i of the pattern and j of the text, at most lim, 32 a
-// step (a step's second half is read within the sequences' words or not at
-// all).
-__device__ __forceinline__ int32_t match_run(uint32_t pw, uint32_t tw, int32_t i, int32_t j, int32_t lim) {
-  int32_t run = 0;
-  while (run < lim) {
-    const int32_t a = i + run, b = j + run, h = lim - run > 16 ? 16 : 0;
-    const uint32_t d0 = bases16(pw, a) ^ bases16(tw, b);
-    const uint32_t d1 = bases16(pw, a + h) ^ bases16(tw, b + h);
-    run += (int32_t)(d0 ? ffbl_raw(d0) >> 1 : 16u + min(ffbl_raw(d1) >> 1, 16u));
-    if (d0 | d1) break;
-  }
-  return min(run, lim);
-}
-
-constexpr int32_t BIAS = 32;
-constexpr uint64_t ENDS_T = 0x5555555555555555ull;  // C's
 constexpr int32_t IDLE = -1;
 constexpr int32_t LOST = -2;  // (score limit) the adaptive window was outgrown
 
@@ -189,6 +98,12 @@ constexpr int32_t LOST = -2;  // (score limit) the adaptive window was outgrown
 struct QItem {
   int32_t p, mn;  // pair (IDLE: invalid input), lengths (pattern in the low half)
   int64_t po, to;
+};
+constexpr int32_t QUEUES = 64, QUEUE_STRIDE = 128;  // bytes between the queues' counters
+constexpr int32_t LEAVE_AT = 16;
+// A pair that goes on to another pass, and that pass's index in the route.
+struct Leave {
+  int32_t p, to;
 };
 // A finished pair that awaits its walk.
 struct Done {
@@ -321,8 +236,8 @@ __device__ void walk_pair(ArgsPtr A, Done d, uint32_t *codes, int32_t rowmask) {
   // cannot happen for codes that were kept and read back intact
   A->O.nruns[p] = 0;
   if (A->L.walk_fail) atomicAdd(A->L.walk_fail, 1);
-  if (ADAPT) {
-    A->O.status[p] = ST_OVERFLOW;  // no exact fallback for a heuristic alignment
+  if (ADAPT || !A->L.need) {
+    A->O.status[p] = ST_OVERFLOW;  // no exact fallback for a heuristic alignment, or none planned
     return;
   }
   const int64_t sc = d.tf - d.t0;
@@ -340,7 +255,7 @@ __device__ void walk_pair(ArgsPtr A, Done d, uint32_t *codes, int32_t rowmask) {
 }
 
 template <int G, int C, bool ADAPT>
-__global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
+__global__ __launch_bounds__(64, C == 4 ? 3 : 4) void k_wfa_group(WfaGroupArgs arg) {
   static_assert(!ADAPT || C == 1, "the adaptive window holds one word a lane");
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NG = 64 / G;
@@ -353,7 +268,8 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
   const int32_t SW = arg.L.seq_words + 2;  // staged words per sequence, one of padding at each end
   Done *done = (Done *)smem;               // 64
   QItem *queue = (QItem *)(done + 64);     // 64
-  uint64_t *seqs = (uint64_t *)(queue + 64);
+  Leave *leave = (Leave *)(queue + 64);    // LEAVE_AT
+  uint64_t *seqs = (uint64_t *)(leave + LEAVE_AT);
   uint64_t *sP = seqs + (int64_t)gi * 2 * SW, *sT = sP + SW;
   // (opaque: one register each, not sums of what they are made of)
   uint32_t pw = lds_addr(sP), tw = lds_addr(sT);
@@ -371,9 +287,16 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
     count = a->Wk.count ? __builtin_amdgcn_readfirstlane(*(volatile const int32_t *)a->Wk.count) : (int32_t)a->Wk.n;
   }
   // a workgroup the work can never reach leaves before touching the counter
-  if ((int64_t)blockIdx.x * NG >= count) return;
-  // queue items fetched at a time: an eighth of a wavefront's share
-  const int32_t chunk = max(NG, min(64, count / (8 * (int32_t)gridDim.x)));
+  if ((int32_t)blockIdx.x >= count) return;
+  // The work lies in up to 64 queues (item li in queue li mod nq), each with a
+  // counter in a cache line of its own and a 64th of the wavefronts: up to
+  // half of a wavefront's share is its own from the start, the rest comes
+  // from its queue's counter, an eighth of a share at a time.  (Wavefronts
+  // adding to one address take about 10 ns each, on the chip as a whole: one
+  // counter made 65,536 pairs of 100 bp cost 0.64 ms, at any error rate.)
+  const int32_t grid = (int32_t)gridDim.x, nq = min(grid, QUEUES), qi = (int32_t)blockIdx.x % nq;
+  const int32_t qwaves = (grid - qi + nq - 1) / nq, qrank = (int32_t)blockIdx.x / nq;
+  const int32_t own = max(NG, min(64, count / (2 * grid))), chunk = max(NG, min(64, count / (8 * grid)));
   const bool keep = arg.P.want_cigar != 0;
   uint32_t *codes = arg.L.codes + (int64_t)blockIdx.x * arg.L.slot_words;  // [as_steps / 4][64 C]
   const int32_t as_steps = arg.L.as_steps, rowmask = as_steps / 4 - 1;
@@ -402,11 +325,11 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
   }
   const int32_t ad_min = arg.L.ad_min, ad_max = min(arg.L.ad_max, 0x7fff);
   uint64_t q_mask = 0;  // queue items not yet taken
-  bool q_end = false;
+  bool q_end = false, q_own = true;
   // the group's next pair and this lane's word of each of its sequences
   int32_t x_p = IDLE, x_mn = 0;
   uint64_t x_P = 0, x_T = 0;
-  int32_t nf = 0;  // finished pairs in `done`
+  int32_t nf = 0, nl = 0;  // finished pairs in `done`, leaving ones in `leave`
   uint32_t dropped = 0, dropped_hi = 0;
 
   int32_t t = 0;  // step
@@ -476,7 +399,9 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
           // past the pair's last score: rejected, or on to the next pass
           const int32_t smax = A->P.max_score;
           const bool lost = ADAPT && gslim == LOST;
-          const bool rej = !lost && smax >= 0 && s + 1 > smax;
+          // (a length difference alone may pass the threshold: before any score)
+          const int32_t ad = gm > gn ? gm - gn : gn - gm;
+          const bool rej = !lost && smax >= 0 && (s + 1 > smax || (ad > 0 && A->P.o + ad > smax));
           const bool bad = !lost && s + 1 > upper(A->P.o);  // cannot happen for exact WFA
           const bool ends = rej || bad || (ADAPT && !lost && s >= A->L.s_cap);
           const bool on = over && !ends;
@@ -486,12 +411,8 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
             A->O.nruns[gp] = 0;
           }
           if (__ballot(on)) {
-            if (ADAPT || A->L.over_list) {
-              if (on && gl == 0) {
-                const int32_t at = atomicAdd(A->L.over_count, 1);
-                A->L.over_list[at] = gp;
-              }
-            } else {
+            int32_t to = 1;
+            if (!ADAPT) {
               // the furthest anti-diagonal any kept M offset reaches, for
               // the prediction of the window the pair needs
               int32_t prog = 0;
@@ -508,13 +429,14 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
               const bool out = kend < -REACH || kend > REACH;  // left before any score
               if (on && gl == 0) {
                 const int32_t pred = predict_extent(out ? max(-kend, kend + 1) : REACH + 1, out ? 0 : prog, gm, gn);
-                int c = 1;
-                while (c < A->L.route.nclass && A->L.route.half[c] < pred) ++c;
+                to = A->L.my_class + 1;
+                while (to < A->L.route.nclass && A->L.route.half[to] < pred) ++to;
                 A->L.route.pred[gp] = pred;
-                const int32_t at = atomicAdd(A->L.route.count[c], 1);
-                A->L.route.list[c][at] = gp;
               }
             }
+            const uint64_t going = __ballot(on && gl == 0);
+            if (on && gl == 0) leave[nl + (int32_t)__popcll(going & ((1ull << lane) - 1ull))] = Leave{gp, to};
+            nl += (int32_t)__popcll(going);
           }
         }
         if (fin && ghit && gl == 0) {
@@ -555,12 +477,6 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
             gt0 = t;
             gdrop = 0;
             const int32_t pnw = (gm + 31) >> 5, tnw = (gn + 31) >> 5;
-            // past its end a pattern goes on with A's and a text with C's:
-            // a run that reaches both ends stops there
-            auto upto = [](uint64_t v, int32_t bases, uint64_t fill) {
-              const uint64_t in = bases >= 32 ? ~0ull : bases <= 0 ? 0ull : (1ull << (2 * bases)) - 1ull;
-              return (v & in) | (fill & ~in);
-            };
             if (gl <= pnw) sP[gl + 1] = upto(x_P, gm - 32 * gl, 0ull);
             if (gl <= tnw) sT[gl + 1] = upto(x_T, gn - 32 * gl, ENDS_T);
             if (max(pnw, tnw) >= G) {
@@ -574,9 +490,10 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
             const int32_t o = A->P.o, smax = A->P.max_score, kend = gn - gm;
             int32_t lim = min(upper(o), A->L.s_cap);
             if (smax >= 0) lim = min(lim, smax);
+            if (smax >= 0 && kend != 0 && o + (kend < 0 ? -kend : kend) > smax) lim = -1;
             if (!ADAPT && max(gm, gn) > REACH)
               // a wavefront of score s reaches diagonals -(s - o) .. s - o
-              lim = (kend < -REACH || kend > REACH) ? -1 : min(lim, REACH + o);
+              lim = (kend < -REACH || kend > REACH) ? -1 : min(lim, REACH + o);  // (-1 stays)
             gslim = lim;
             const int32_t f0 = match_run(pw, tw, BIAS, BIAS, min(gm, gn));
             for (int32_t r = 0; r < R; ++r) {
@@ -617,15 +534,19 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
           todo &= todo - 1;
           while (!q_mask && !q_end) {
             int32_t base = 0;
-            if (lane == 0) base = atomicAdd(A->Wk.counter, chunk);
-            base = __builtin_amdgcn_readfirstlane(base);
-            const int32_t cnt = min(chunk, count - base);
-            if (cnt <= 0) {
-              q_end = true;
-            } else {
+            if (!q_own) {
+              if (lane == 0) base = atomicAdd(A->Wk.counter + qi * (QUEUE_STRIDE / 4), chunk);
+              base = __builtin_amdgcn_readfirstlane(base) + own * qwaves;
+            }
+            const int32_t qn = (count - qi + nq - 1) / nq;  // items of this queue
+            const int32_t li = qi + nq * (q_own ? lane * qwaves + qrank : base + lane);
+            const int32_t cnt = q_own ? own : min(chunk, qn - base);
+            // (the last fetch, when nothing is left to the counter)
+            q_end = q_own ? own * qwaves >= qn : cnt <= 0;
+            q_own = false;
+            if (cnt > 0) {
               bool valid = false;
-              if (lane < cnt) {
-                const int32_t li = base + lane;
+              if (lane < cnt && li < count) {
                 const int32_t p = A->Wk.idx ? A->Wk.idx[li] : li;
                 if (A->O.flags && A->O.flags[p]) {
                   A->O.score[p] = -1;
@@ -667,12 +588,9 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
         // loads; the acquire drops lines that an earlier walk left in the
         // CU's vector L1
         if ((t & 3) != 3) {
-          const uint32_t sh = 4 * (3 - (t & 3));
 #pragma unroll
-          for (int c = 0; c < C; ++c) {
-            const uint32_t v = ((cacc[c] >> sh) & 0xffff0000u) | ((cacc[c] & 0xffffu) >> sh);
-            codes[((t >> 2) & rowmask) * (64 * C) + lane * C + c] = v;
-          }
+          for (int c = 0; c < C; ++c)
+            codes[((t >> 2) & rowmask) * (64 * C) + lane * C + c] = settle_codes(cacc[c], t);
         }
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -682,6 +600,24 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
       }
       nact = (int32_t)__popcll(__ballot(gp >= 0 && gl == 0));
       npend = 0;
+      if (nl > (A->L.by_length ? 0 : LEAVE_AT - NG) || (nl > 0 && !busy)) {
+        // the leaving pairs to their lists, one atomic per list; at once where
+        // lengths spread widely, so that the lists keep the queue's order,
+        // longest first (buffered, 200,000 pairs of 100-10,000 bp lost 7 % to the
+        // class kernels' last pairs)
+        __syncthreads();
+        const Leave v = lane < nl ? leave[lane] : Leave{IDLE, 0};
+        for (int32_t c = A->L.my_class + 1; c <= A->L.route.nclass; ++c) {
+          const uint64_t m = __ballot(v.to == c);
+          if (!m) continue;
+          int32_t at = 0;
+          if (lane == 0) at = atomicAdd(A->L.route.count[c], (int32_t)__popcll(m));
+          at = __builtin_amdgcn_readfirstlane(at) + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+          if (v.to == c) A->L.route.list[c][at] = v.p;
+        }
+        __syncthreads();
+        nl = 0;
+      }
       if (!busy) {
         if (ADAPT && A->L.ad_dropped && (dropped | dropped_hi))
           atomicAdd(A->L.ad_dropped, ((unsigned long long)dropped_hi << 32) | dropped);
@@ -760,36 +696,17 @@ __global__ __launch_bounds__(64, 4) void k_wfa_group(WfaGroupArgs arg) {
       const uint32_t ID = max2(I, D);
       Mv[c] = max2(X, ID);
       // extension: the first 16 bases of both diagonals by every lane
-      const uint32_t J = max2(Mv[c], 0u), Ii = max2(subs2(Mv[c], K2[c]), 0u);
-      const uint32_t da = bases16_lo(pw, Ii) ^ bases16_lo(tw, J), db = bases16_hi(pw, Ii) ^ bases16_hi(tw, J);
-      if (keep) {
-        const uint32_t sio = subs2(Mo[c], Iv[c]), sdo = subs2(Mo[c], Dv[c]);  // sign: extended, from this cell
-        const uint32_t cx = subs2(X, ID), ci = subs2(I, D);                   // sign: X < M; I < D
-        const uint32_t a = bfi(0x80008000u, cx, ci >> 1), b = bfi(0x80008000u, sio, sdo >> 1);
-        cacc[c] = bfi(0xf000f000u, bfi(0xc000c000u, a, b >> 2), cacc[c] >> 4);
-      }
+      rr[c] = first_run2(pw, tw, Mv[c], K2[c]);
+      if (keep) cacc[c] = push_codes(cacc[c], subs2(X, ID), subs2(I, D), subs2(Mo[c], Iv[c]), subs2(Mo[c], Dv[c]));
       Iv[c] = I;
       Dv[c] = D;
-      // matching bits, all ones for 16 bases (those are done again below)
-      rr[c] = pack2((int32_t)ffbl_raw(da), (int32_t)ffbl_raw(db));
-      asm("v_pk_lshrrev_b16 %0, 1, %1 op_sel_hi:[0,1]" : "=v"(rr[c]) : "v"(rr[c]));
+      // (a run of 16 is done again below)
       F[c] = min2(add2(Mv[c], rr[c]), LIM[c]);
       full |= rr[c];
     }
     if (full & 0x40004000u) {
-      // the runs of 16 and more, one half at a time
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        uint32_t todo = rr[c] & 0x40004000u;
-        while (todo) {
-          const uint32_t sh = (todo & 0x4000u) ? 0u : 16u;
-          todo &= todo - 1u;
-          const int32_t f = (int32_t)(Mv[c] >> sh) & 0xffff, l = (int32_t)(LIM[c] >> sh) & 0xffff;
-          const int32_t i = f - (int32_t)(int16_t)(K2[c] >> sh);
-          const int32_t g = min(f + 16 + match_run(pw, tw, i + 16, f + 16, max(l - f - 16, 0)), l);
-          F[c] = sh ? pack2((int32_t)F[c], g) : bfi_v(0xffffu, (uint32_t)g, F[c]);
-        }
-      }
+      for (int c = 0; c < C; ++c) F[c] = long_runs2(pw, tw, Mv[c], K2[c], LIM[c], rr[c], F[c]);
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) hit = (c > 0 && hit) || (int16_t)F[c] >= (int16_t)TGT[c];
@@ -845,7 +762,7 @@ hipError_t launch_group(const Seqs &S, const Outs &O, const Scoring &P, const Wo
 }  // namespace
 
 size_t wfa_group_lds(int32_t lanes, int32_t words, bool adaptive, int32_t R, int32_t seq_words) {
-  return 64 * (sizeof(Done) + sizeof(QItem)) +
+  return 64 * (sizeof(Done) + sizeof(QItem)) + LEAVE_AT * sizeof(Leave) +
          (size_t)(64 / lanes) * 2 * (seq_words + 2) * 8 + (size_t)R * 64 * 4 * (words + (adaptive ? 1 : 0));
 }
 

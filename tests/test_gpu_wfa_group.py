@@ -184,3 +184,34 @@ def test_many_equal_pairs(ctx):
         assert not s.any() and not st.any()
         assert np.array_equal(np.diff(off), (b.pat_len > 0).astype(np.int64))
         assert np.array_equal(cg[:off[-1]] >> 4, b.pat_len[b.pat_len > 0].astype(np.uint32))
+
+
+@pytest.mark.parametrize("alg,pen", [("nw", (0, 1, 0, 1)), ("nw", (0, 2, 0, 1)), ("swg", AFF), ("swg", (0, 1, 1, 1))])
+def test_small_band_batches(ctx, alg, pen):
+    # NW and SWG batches that take the wavefront passes at once, alone in them
+    # (short reads) or with every later pass behind them (longer ones)
+    b = edge_pairs(4)
+    for smax in (-1, 0, 3, 13, 30, 61):
+        check(ctx, b, alg, pen, smax)
+    check(ctx, b, alg, pen, want_cigar=False)
+    check(ctx, drift_pairs(11, 500, 900), alg, pen)
+
+
+@pytest.mark.parametrize("alg,pen", [("nw", (0, 1, 0, 1)), ("swg", AFF)])
+def test_band_escalates_to_wavefronts(ctx, alg, pen):
+    # 66,000 short pairs: the packed band and its second-stream walk, with the
+    # pairs it cannot decide (a third of these) in the wavefront passes beside it
+    rng = np.random.default_rng(12)
+    T = [rng.integers(0, 4, 60).astype(np.uint8) for _ in range(600)]
+    uniq = synth.from_lists([_noisy(rng, t, float(rng.choice([0.02, 0.3]))) if k % 3 else
+                             rng.integers(0, 4, 60).astype(np.uint8) for k, t in enumerate(T)], T)
+    b = uniq.subset(np.arange(66_000) % uniq.n)
+    got = run(ctx, b, alg, pen)
+    want = oracle.align_batch(uniq, alg, pen)
+    assert ctx.last_call_stats()["band_escalated"] > 1000
+    k = np.arange(b.n) % uniq.n
+    assert np.array_equal(got[0], want[0][k]) and np.array_equal(got[1], want[1][k])
+    for i in range(0, b.n, 37):
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
+    runs = np.diff(want[3])[k]
+    assert np.array_equal(np.diff(got[3]), runs)
