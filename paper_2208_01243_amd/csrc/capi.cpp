@@ -481,9 +481,12 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   // 32 lanes (16 for short reads, which end before theirs grows) hold nearly
   // every pair at max_dist 50, and 64 lanes nearly all of the rest; what
   // leaves those goes on to the kernel below, with every diagonal.
+  // Long reads start in 64 lanes: theirs drift furthest (10,000 pairs of 10 kbp
+  // at 5 % take 8.3 ms from 32 lanes on, 6.7 ms from 64).
   aim::Work WG = Wk;
-  if (!Wk.direct && wfa_group_fits(L, P) && c->ad_min <= 50 && c->ad_max <= 100) {
-    const int32_t first = c->ad_max > 50 ? 64 : L <= 192 ? 16 : 32;
+  const bool groups = wfa_group_fits(L, P) && c->ad_min <= 50 && c->ad_max <= 100;
+  if (!Wk.direct && groups) {
+    const int32_t first = c->ad_max > 50 || L > 4096 ? 64 : L <= 192 ? 16 : 32;
     int32_t *lists[2] = {as<int32_t>(c->sc->list2), as<int32_t>(c->sc->list3)};
     int k = 0;
     for (int32_t lanes = first; lanes <= 64; lanes = lanes < 64 ? 64 : 128, ++k) {
@@ -512,7 +515,9 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   const bool lds_ring = aim::wfa_lds_bytes(D.W, D.MG, D.R, P.e, D.seq_words, false) <= 24 * 1024;
   const size_t lds = aim::wfa_lds_bytes(D.W, D.MG, D.R, P.e, D.seq_words, !lds_ring);
   if (lds > 160 * 1024) return fail(AIM_ERR_UNSUPPORTED, "WFA-adaptive: sequences too long to stage");
-  const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds, 2048 / threads));
+  // behind the groups a pair or none comes here: a workgroup for each SIMD, for
+  // with all that fit the slots take 20-30 GB, whose return costs 0.7 s
+  const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds, groups ? 4 : 2048 / threads));
   int32_t nslots = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * per_cu);
   // per workgroup slot: the ring (with its guard word) and, with CIGARs, the
   // score table and the origin codes of every kept score, within 5/16 of
