@@ -342,6 +342,32 @@ size_t wfa_group_lds(int32_t lanes, int32_t words, bool adaptive, int32_t R, int
 hipError_t launch_wfa_group(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, const WfaGroup &L,
                             int32_t lanes, int32_t words, bool adaptive, hipStream_t s);
 
+// One wide pair per workgroup of `threads` lanes with up to `words` words of two
+// diagonals a lane (k_wfa_wide): a window of 2 threads words diagonals.
+struct WfaWide {
+  int32_t R, seq_words, s_cap;  // as in WfaGroup
+  int32_t pair_words;           // 32-bit words of codes one pair may store
+  int32_t code_words;           // ... and all pairs of a workgroup that await their walks
+  int32_t tok_cap;              // walk tokens (32-bit words) per wavefront, behind the codes
+  int64_t slot_words;           // words per workgroup: code_words + tok_cap threads / 64
+  uint32_t *codes;
+  int32_t my_class;             // this class's index in the route
+  WfaRoute route;
+  int64_t need_cap[4];          // the full-store fallback, as in WfaLaunch
+  int32_t *need_list[4];
+  int32_t *need_count[4];
+  int32_t *need_max[4];
+  int64_t *need;
+  int32_t *walk_fail, *walk_skip;
+  int32_t *long_list, *long_count;
+};
+size_t wfa_wide_lds(int32_t threads, int32_t words, int32_t R, int32_t seq_words);
+// Words of codes of a pair of that many scores, at most.
+int64_t wfa_wide_pair_words(int32_t threads, int32_t words, int32_t o, int32_t scores);
+// threads and words: 256 and 4, or 512 and 6
+hipError_t launch_wfa_wide(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, const WfaWide &L, int32_t threads,
+                           int32_t words, int32_t nslots, hipStream_t s);
+
 struct WfaPlan {
   int32_t R, wcap, wcap_lds, seq_words, lds_score_bytes, ring_slots, ring_threads, lds_arena_words;
   int64_t ring_slot_words;

@@ -667,36 +667,111 @@ aim_status launch_group_passes(aim_context *c, const aim::Seqs &S, const aim::Ou
   return AIM_OK;
 }
 
-// Batches whose pairs all stay in the group passes (short reads, or a low
-// threshold): those passes alone, with no list, ring or store of the others.
-// (A walk cannot fail on codes that were kept; if one did its pair would get
-// CIGAR_OVERFLOW.)  `done` false: not such a batch, nothing launched.
+// The passes for wide pairs (k_wfa_wide): up to 2,048 diagonals by workgroups of
+// 256 lanes (four to a CU), up to 6,144 by 512 lanes (two to a CU).
+struct WidePass {
+  int32_t threads, words;
+  int32_t reach() const { return threads * words - 3; }
+};
+constexpr WidePass WIDE_PASS[2] = {{256, 4}, {512, 6}};
+constexpr size_t CU_LDS = 160 * 1024;
+bool wide_fits(const aim::Scoring &P, int32_t L, const WidePass &wp) {
+  return aim::wfa_wide_lds(wp.threads, wp.words, std::max(P.x, P.o + 1) + 1, (L + 31) / 32) <= CU_LDS;
+}
+// Words of codes that any pair of the pass can need, and of its walk's tokens:
+// a pair ends in some stage, as wide as its lengths or its scores make it.
+int64_t wide_pair_words(const aim::Scoring &P, int32_t L, const WidePass &wp) {
+  const int32_t most = wfa_most_scores(P, L);
+  int64_t w = 0;
+  for (int32_t k = 1; k <= wp.words; ++k) {
+    const int32_t reach = wp.threads * k - 3;  // pairs no longer stay in the stage at any score
+    const int32_t scores = std::max(std::min(most, reach + P.o), wfa_most_scores(P, std::min(L, reach)));
+    w = std::max(w, aim::wfa_wide_pair_words(wp.threads, k, P.o, wp.reach() >= wfa_reach(P, L) && k == wp.words ? most : scores));
+  }
+  return w;
+}
+int32_t wide_tokens(int32_t L) { return 2 * (2 * L + 1) + 8; }
+// Launch over the listed pairs; D: route, class index and fallback lists.
+aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
+                            int32_t L, const WidePass &wp, const aim::Work &W, aim::WfaWide D, int64_t share, hipStream_t s) {
+  D.R = std::max(P.x, P.o + 1) + 1;
+  D.seq_words = (L + 31) / 32;
+  D.s_cap = 16000;
+  const size_t lds = aim::wfa_wide_lds(wp.threads, wp.words, D.R, D.seq_words);
+  int64_t slots = std::min<int64_t>(n, (int64_t)c->cus * std::max<size_t>(1, std::min<size_t>(CU_LDS / lds, 1024 / wp.threads)));
+  if (P.want_cigar) {
+    // codes of a pair for every wavefront's walk, within 16 MiB where that
+    // holds two
+    const int64_t waves = wp.threads / 64, tok = waves * wide_tokens(L);
+    const int64_t pair = std::max<int64_t>(1024, std::min<int64_t>(wide_pair_words(P, L, wp), share / 4 - tok));
+    slots = std::max<int64_t>(1, std::min(slots, share / 4 / (pair + tok)));
+    const int64_t want = std::max<int64_t>(pair, std::min<int64_t>(waves * pair, std::max<int64_t>(2 * pair, 4 << 20)));
+    const int64_t words = std::max<int64_t>(pair, std::min(want, share / 4 / slots - tok));
+    D.pair_words = (int32_t)pair;
+    D.code_words = (int32_t)((words + 3) / 4 * 4);
+    D.tok_cap = wide_tokens(L);
+    D.slot_words = (D.code_words + tok + 3) / 4 * 4;
+    aim_status st = ensure(c, c->sc->wlds, (size_t)(slots * D.slot_words * 4));
+    if (st) return st;
+    D.codes = static_cast<uint32_t *>(c->sc->wlds.p);
+  }
+  Phase ph(c, s, wp.threads == 256 ? "wfa_wide1" : "wfa_wide2");
+  HIP_TRY(aim::launch_wfa_wide(S, O, P, W, D, wp.threads, wp.words, (int32_t)slots, s));
+  return AIM_OK;
+}
+
+// Batches whose pairs all stay in the group and wide passes (reads of up to
+// 3,069 bp, or a low threshold): those passes alone, with no list, ring or store
+// of the others.  (A walk cannot fail on codes that were kept; if one did its
+// pair would get CIGAR_OVERFLOW.)  `done` false: not such a batch, nothing
+// launched.
 aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n, int32_t L,
                          int32_t *cnt, const int32_t *order, const int32_t *order_count,
                          const std::vector<GroupPass> &passes, hipStream_t s, bool &done) {
   done = false;
-  const int32_t most = wfa_most_scores(P, L);
-  if (passes.back().reach() < wfa_reach(P, L) || most > 16000) return AIM_OK;
-  const int64_t share = c->limit() / 8;
+  const int32_t most = wfa_most_scores(P, L), reach = wfa_reach(P, L);
+  if (most > 16000) return AIM_OK;
+  int nw = 0;
+  for (int32_t r = passes.back().reach(); r < reach; r = WIDE_PASS[nw++].reach())
+    if (nw == 2 || !wide_fits(P, L, WIDE_PASS[nw])) return AIM_OK;
+  const int64_t share = c->limit() / 8, wide_share = c->limit() / 3;
+  int64_t least = 64;  // steps of codes: any pair's of the pass
   if (P.want_cigar) {
-    // every pass must hold the codes of any pair, in 64 workgroups at least
+    // in 64 workgroups at least
+    least = (nw > 0 ? std::min(most, passes.back().reach() + P.o) : most) + 8;
     for (const GroupPass &gp : passes)
-      if (share < 2 * ((int64_t)most + 8) * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
+      if (share < 2 * least * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
+    for (int k = 0; k < nw; ++k)
+      if (wide_share < 4 * (wide_pair_words(P, L, WIDE_PASS[k]) + WIDE_PASS[k].threads / 64 * wide_tokens(L)) * std::min<int64_t>(n, 64))
+        return AIM_OK;
   }
   aim_status st;
-  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * (passes.size() > 1 ? passes.size() : 1)))) return st;
+  const int32_t ng = (int32_t)passes.size() - 1, later = ng + nw;
+  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * (later + 1)))) return st;
   int32_t *lists = as<int32_t>(c->sc->wlists);
   aim::WfaGroup G{};
   G.walk_fail = cnt + C_WF;
-  G.route.nclass = (int32_t)passes.size() - 1;
-  for (size_t k = 1; k < passes.size(); ++k) {
-    G.route.half[k] = passes[k].reach();
+  G.by_length = L > 1024;
+  G.route.nclass = later;
+  for (int32_t k = 1; k <= later; ++k) {
+    G.route.half[k] = k <= ng ? passes[k].reach() : WIDE_PASS[k - ng - 1].reach();
     G.route.list[k] = lists + (int64_t)n * k;
-    G.route.count[k] = cnt + C_GL + (int32_t)k - 1;
+    G.route.count[k] = k <= ng ? cnt + C_GL + k - 1 : cnt + C_CL + (k - ng - 1);
   }
+  G.route.half[later] = INT32_MAX;
   G.route.pred = lists;
   done = true;
-  return launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, (int64_t)most + 8, share, G, s);
+  if ((st = launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, least, share, G, s))) return st;
+  for (int k = 0; k < nw; ++k) {
+    aim::WfaWide D{};
+    D.route = G.route;
+    D.my_class = ng + 1 + k;
+    D.walk_fail = cnt + C_WF;
+    c->last_class_window[k] = 2 * WIDE_PASS[k].threads * WIDE_PASS[k].words;
+    const aim::Work W{D.route.list[D.my_class], D.route.count[D.my_class], n, cnt + C_CL + 4 + k, nullptr, nullptr, 0};
+    if ((st = launch_wide_pass(c, S, O, P, n, L, WIDE_PASS[k], W, D, wide_share, s))) return st;
+  }
+  return AIM_OK;
 }
 
 aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
@@ -761,6 +836,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     int32_t W, threads, nslots;
     bool global;
     int32_t half;  // routing bound: pairs predicted to span at most this many diagonals each side
+    int wide = -1;  // k_wfa_wide's pass instead, if any
   };
   std::vector<LdsClass> cls;
   const int32_t MG = 2 * pl.R + 4;
@@ -782,16 +858,23 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       const int32_t cb = len_bucket_host(k < 2 ? bound[k] : L);
       const auto ct = c->class_tunes.find({AIM_WFA_AFFINE, cb});
       const ClassTune *ctp = ct == c->class_tunes.end() ? nullptr : &ct->second;
-      const bool fits = aim::wfa_lds_bytes(full, MG, pl.R, P.e, pl.seq_words, false) <= 64 * 1024;
-      const bool glob = (ctp && ctp->global >= 0) ? ctp->global != 0
-                        : small && fits            ? false
-                                                   : ((tu.wfa_cls_global >> k) & 1) != 0;
-      const int32_t w = glob || (small && fits) ? full : std::min<int64_t>((int64_t)2 * std::min(bound[k], wmax / 2), wmax);
+      // the first two are k_wfa_wide's where it fits, unless the class's tune
+      // names a configuration of k_wfa_lds
+      if (group && k < 2 && !(ctp && (ctp->threads > 0 || ctp->global >= 0)) && wide_fits(P, L, WIDE_PASS[k])) {
+        const WidePass &wp = WIDE_PASS[k];
+        c->last_class_bucket[cls.size()] = cb;
+        cls.push_back({2 * wp.threads * wp.words, wp.threads, 0, false, wp.reach(), k});
+        prev_half = wp.reach();
+        if (prev_half >= L) break;
+        continue;
+      }
+      const bool glob = (ctp && ctp->global >= 0) ? ctp->global != 0 : ((tu.wfa_cls_global >> k) & 1) != 0;
+      const int32_t w = glob ? full : std::min<int64_t>((int64_t)2 * std::min(bound[k], wmax / 2), wmax);
       const int32_t half = glob ? bound[k] : w / 2;
       if (std::min(half, w / 2) <= prev_half) continue;
       const size_t lds = aim::wfa_lds_bytes(w, MG, pl.R, P.e, pl.seq_words, glob);
       if (lds > lds_cap) continue;
-      const int32_t th = (ctp && ctp->threads > 0) ? ctp->threads : small ? 256 : tu.wfa_cls_threads[k];
+      const int32_t th = (ctp && ctp->threads > 0) ? ctp->threads : tu.wfa_cls_threads[k];
       c->last_class_bucket[cls.size()] = cb;
       const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(lds_cap / lds, 2048 / th));
       cls.push_back({w, th, (int32_t)std::min<int64_t>(n, (int64_t)c->cus * per_cu), glob, half});
@@ -866,6 +949,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     size_t code_bytes = 0, ring_bytes = 0;
     for (size_t k = 0; k < cls.size(); ++k) {
       aim::WfaLds &D = LL[k];
+      if (cls[k].wide >= 0) continue;
       D.W = cls[k].W;
       D.MG = MG;
       D.R = pl.R;
@@ -911,6 +995,25 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       if ((st = ensure(c, c->sc->wlds, std::max<size_t>(code_bytes, 256)))) return st;
       if (ring_bytes && (st = ensure(c, c->sc->wgring, ring_bytes))) return st;
       for (size_t k = 0; k < cls.size(); ++k) {
+        if (cls[k].wide >= 0) {
+          aim::WfaWide D{};
+          D.route = route;
+          D.my_class = ng + (int32_t)k + 1;
+          for (int q = 0; q < 4; ++q) {
+            D.need_cap[q] = WL.need_cap[q];
+            D.need_list[q] = WL.need_list[q];
+            D.need_count[q] = WL.need_count[q];
+            D.need_max[q] = WL.need_max[q];
+          }
+          D.need = WL.need;
+          D.long_list = WL.long_list;
+          D.long_count = WL.long_count;
+          D.walk_fail = WL.walk_fail;
+          D.walk_skip = WL.walk_skip;
+          const aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
+          if ((st = launch_wide_pass(c, S, O, P, n, L, WIDE_PASS[cls[k].wide], WC, D, c->limit() / 3, s))) return st;
+          continue;
+        }
         LL[k].codes = as<uint8_t>(c->sc->wlds);
         LL[k].gring = cls[k].global ? as<uint32_t>(c->sc->wgring) : nullptr;
         aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
@@ -1725,9 +1828,12 @@ aim_status aim_autotune(aim_context *c, const aim_batch *B, int32_t alg, aim_pen
       const ClassTune prev = had_entry ? had->second : ClassTune{};
       ClassTune bestc{};
       double bestk = 1e300;
-      for (int th : {64, 128, 256})
+      // ({0, -1}: the built-in choice)
+      for (int th : {0, 64, 128, 256})
         for (int gl : {1, 0}) {
-          c->class_tunes[key] = ClassTune{th, gl};
+          if (th == 0 && gl == 0) continue;
+          const ClassTune ct = th == 0 ? ClassTune{} : ClassTune{th, gl};
+          c->class_tunes[key] = ct;
           st = aim_align_batch(c, B, alg, pen, max_score, R, stream);
           std::vector<double> ms;
           for (int r = 0; r < reps && st == AIM_OK; ++r) {
@@ -1745,7 +1851,7 @@ aim_status aim_autotune(aim_context *c, const aim_batch *B, int32_t alg, aim_pen
           std::sort(ms.begin(), ms.end());
           if (ms[ms.size() / 2] < bestk) {
             bestk = ms[ms.size() / 2];
-            bestc = ClassTune{th, gl};
+            bestc = ct;
           }
         }
       if (st == AIM_OK) {

@@ -1,0 +1,120 @@
+"""The workgroup kernel for wide wavefronts (k_wfa_wide) against the wavefront
+oracle, bit for bit, where it can go wrong: wavefronts and end diagonals around
+the edges of its stages (253, 509, 765, 1021 diagonals each side in the first
+window, on to 3069 in steps of 512 in the second) and past the last one, both
+parities, exact runs that cross wavefronts, scores only, thresholds beside the
+optimum, scratch that holds few pairs' codes, and more pairs than the walks'
+queue.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+import paper_2208_01243_amd as aim  # noqa: E402
+from gpu_util import compare, describe, run  # noqa: E402
+
+AFF = (0, 4, 6, 2)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = aim.Context(0)
+    yield c
+    c.close()
+
+
+def _noisy(rng, T, rate):
+    b = synth.from_lists([T], [T])
+    return synth.mutate(rng, b.txt, b.txt_off, [rate])[0]
+
+
+def stage_pairs(seed, edges, lo=-4, hi=4):
+    """One gap of a length around each edge, to either side, in the middle or at
+    an end, between exact or noisy halves; and unrelated pairs whose wavefronts
+    pass the edge."""
+    rng = np.random.default_rng(seed)
+    base = lambda n: rng.integers(0, 4, n).astype(np.uint8)  # noqa: E731
+    pats, txts = [], []
+    for e in edges:
+        for d in range(lo, hi + 1):
+            T = base(int(rng.integers(60, 300)))
+            at = (0, len(T) // 2, len(T))[int(rng.integers(3))]
+            P = np.concatenate([T[:at], base(e + d), T[at:]])
+            if d % 3 == 0:
+                P = _noisy(rng, P, 0.03)
+            pats += [P, T]
+            txts += [T, P]
+        n = 2 * e
+        T = base(n)
+        pats += [_noisy(rng, T, 0.12), base(n // 2 + 1)]
+        txts += [T, base(n // 2)]
+    return synth.from_lists(pats, txts)
+
+
+def check(ctx, b, pen, max_score=-1, want=None, want_cigar=True):
+    want = want or oracle.wfa_batch(b, pen, max_score)
+    got = run(ctx, b, "wfa", pen, max_score, want_cigar=want_cigar)
+    if not want_cigar:
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        return want
+    bad = compare(got, want)
+    assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
+    return want
+
+
+@pytest.mark.parametrize("pen", [AFF, (0, 1, 0, 1), (0, 3, 4, 1), (0, 30, 2, 1), (0, 1, 40, 1)])
+def test_first_window(ctx, pen):
+    b = stage_pairs(1, (253, 509, 765, 1021))
+    want = check(ctx, b, pen)
+    check(ctx, b, pen, want=want, want_cigar=False)
+
+
+@pytest.mark.parametrize("pen", [AFF, (0, 1, 0, 1), (0, 2, 5, 1)])
+def test_second_window(ctx, pen):
+    b = stage_pairs(2, (1533, 2045, 2557, 3069), -2, 2)
+    want = check(ctx, b, pen)
+    check(ctx, b, pen, want=want, want_cigar=False)
+
+
+def test_thresholds(ctx):
+    b = stage_pairs(3, (253, 509), -1, 1)
+    full = oracle.wfa_batch(b, AFF)[0]
+    for smax in sorted({0, 1, 506, 512, int(full[0]) - 2, int(full[0]) - 1, int(full[0]), int(full[0]) + 1}):
+        check(ctx, b, AFF, smax)
+
+
+def test_long_exact_runs(ctx):
+    # exact stretches of thousands of bases on far diagonals: one gap of several
+    # hundred bases first
+    rng = np.random.default_rng(4)
+    pats, txts = [], []
+    for k in range(24):
+        T = rng.integers(0, 4, 2000 + 37 * k).astype(np.uint8)
+        P = np.concatenate([rng.integers(0, 4, 300 + 20 * k).astype(np.uint8), T])
+        P[700 + 900 * (k % 2)] ^= 1
+        pats.append(P if k % 3 else T)
+        txts.append(T if k % 3 else P)
+    check(ctx, synth.from_lists(pats, txts), AFF)
+
+
+@pytest.mark.parametrize("limit", [12 << 20, 40 << 20, 1 << 30])
+def test_little_scratch(limit):
+    # room for the codes of few pairs, or of none that reaches the last stage
+    b = stage_pairs(5, (253, 1021, 2045), -1, 1)
+    with aim.Context(0, scratch_limit=limit) as c:
+        check(c, b, AFF)
+
+
+def test_more_pairs_than_await_their_walks(ctx):
+    uniq = stage_pairs(6, (100, 253, 300, 509, 1021), -3, 3)
+    want = oracle.wfa_batch(uniq, AFF)
+    k = np.random.default_rng(7).integers(0, uniq.n, 9000)
+    got = run(ctx, uniq.subset(k), "wfa", AFF)
+    assert np.array_equal(got[0], want[0][k]) and np.array_equal(got[1], want[1][k])
+    assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
+    for i in range(len(k)):
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
