@@ -119,7 +119,7 @@ struct Scratch {
   Buf order, hist;
   Buf flags, pflag, tflag, pat2, txt2, pat2off, txt2off, nruns, slot, tb32, tb64, full, list2,
       list3, counters, scan_tmp, spill, total, wring, warena1, warena2, warena3, wneed, wlists, pool, pooloff,
-      wbits, wwalk, wlds, wgring, flist, genasm, wlong;
+      wbits, wwalk, wlds, wgring, flist, wlong;
 };
 
 struct aim_graph {
@@ -549,21 +549,14 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   return AIM_OK;
 }
 
-// GenASM: one launch over the listed pairs, each wavefront with a slot of
-// every edit level a window can need (k + 1, at most 65, in whole sweeps).  The tune's
-// wavefronts per CU (in 256-thread blocks), fewer when the slots would pass a
-// quarter of the budget.
+// GenASM: one launch over the listed pairs, with as many wavefronts per CU as
+// fit (or the tune's, if those are fewer).
 aim_status run_genasm(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
                       const aim::Work &Wk, const Tune &tu, hipStream_t s) {
-  const int32_t levels = aim::genasm_levels(P.max_score);
-  const int64_t block_bytes = aim::genasm_block_words(levels) * 8;
-  const int64_t per_cu = std::max<int64_t>(1, tu.band_wpc / 4);
-  int64_t blocks = std::min<int64_t>((n + 255) / 256, (int64_t)c->cus * per_cu);
-  blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, c->limit() / 4 / block_bytes));
-  aim_status st = ensure(c, c->sc->genasm, (size_t)(blocks * block_bytes));
-  if (st) return st;
+  const int64_t per_cu = std::max(1, std::min(tu.band_wpc, aim::genasm_waves_per_cu()));
+  const int64_t blocks = std::min<int64_t>((n + 63) / 64, (int64_t)c->cus * per_cu);
   Phase ph(c, s, Wk.direct ? "genasm_rerun" : "genasm");
-  HIP_TRY(aim::launch_genasm(S, O, P, Wk, as<uint64_t>(c->sc->genasm), levels, (int32_t)blocks, s));
+  HIP_TRY(aim::launch_genasm(S, O, P, Wk, (int32_t)blocks, s));
   return AIM_OK;
 }
 
@@ -1187,7 +1180,7 @@ void aim_destroy(aim_context *c) {
                 &c->own.nruns, &c->own.slot, &c->own.tb32, &c->own.tb64, &c->own.full, &c->own.list2, &c->own.list3,
                 &c->own.counters, &c->own.scan_tmp, &c->own.spill, &c->own.total, &c->own.wring, &c->own.warena1,
                 &c->own.warena2, &c->own.warena3, &c->own.wneed, &c->own.wlists, &c->own.pool, &c->own.pooloff, &c->own.wbits, &c->own.wwalk, &c->own.wlds, &c->own.wgring, &c->own.flist,
-                &c->own.genasm, &c->own.wlong};
+                &c->own.wlong};
   for (Buf *b : all)
     if (b->p) clear_scratch(*b, c->aux);
   (void)hipStreamSynchronize(c->aux);
@@ -1761,8 +1754,8 @@ aim_status aim_autotune(aim_context *c, const aim_batch *B, int32_t alg, aim_pen
             cand.push_back(t);
         }
   } else if (alg == AIM_GENASM) {
-    // wavefronts per CU (the slots scale with them) and the order
-    for (int wpc : {4, 8, 12, 16})
+    // wavefronts per CU and the order
+    for (int wpc : {4, 8})
       for (int so : {0, 1}) {
         Tune t;
         t.band_wpc = wpc;
