@@ -47,11 +47,13 @@
 // traceback takes a run of matching bases at once and reads one entry per edit,
 // all lanes together.  Work comes 64 pairs at a time.
 //
-// What bounds it: vector instructions (38 a text position, of which 12 keep the
-// differences).  The same with 12-byte slices in global memory was bound by
-// their stores: 805 us against the 365 here, 1,000,000 pairs of 150 bp at 4 %
-// (four wavefronts a SIMD; more were slower).  Sweeps that built six levels of
-// status vectors each, stored for the traceback, took 2,072 us.
+// What bounds it: vector instructions (two thirds of their issue rate: 34 a text
+// position, of which 10 keep the differences, and about 100 an edit).  1,000,000
+// pairs of 150 bp at 4 %: 490 us; 684 with every pass's positions conditional and
+// an op's run emitted in each branch of the walk; 806 with 12-byte slices in
+// global memory, whose stores bound it (four wavefronts a SIMD, more were
+// slower); 2,072 with sweeps that built six levels of status vectors each and
+// stored them for the traceback.
 #include "aim_internal.h"
 #include "dev_util.h"
 
@@ -60,19 +62,11 @@ namespace {
 
 constexpr int32_t GW = 64;       // window bases
 constexpr int32_t GC = GW - 24;  // bases a window other than the final one commits
+constexpr int32_t GC_FROM = GW - GC;  // first text position whose differences the walk of a full window needs, less one
 constexpr uint32_t OP_NONE = 4;
 
 __device__ __forceinline__ uint64_t low_bits(int32_t q) {
   return q >= 64 ? ~0ull : (q <= 0 ? 0ull : ((1ull << q) - 1ull));
-}
-
-// The 32 bases of a window ending at position q (1-based; bases lo = 1..32,
-// hi = 33..64), position q in the top two bits; positions before 1 read 0.
-__device__ __forceinline__ uint64_t tail32(uint64_t lo, uint64_t hi, int32_t q) {
-  const int32_t sh = 2 * (q - 32);
-  if (sh <= 0) return sh == 0 ? lo : (lo << (-sh));
-  if (sh >= 64) return hi;
-  return (lo >> sh) | (hi << (64 - sh));
 }
 
 // The differences of a text position, 64 lanes' entries: three slices of 21 bits
@@ -103,8 +97,10 @@ __device__ __forceinline__ int32_t at_32(int32_t e) { return min(max(e - 16, 0),
 // +1 in pv, -1 in mv); the horizontal delta entering at the start row is +1 when
 // anchored, 0 when free; bits at and above a only carry upwards and are masked
 // off at the end.  Stops after position `upto`; those past `from` are kept (both the
-// same in every lane).
-template <int KEEP>
+// same in every lane).  FULL: the windows of all lanes are free and of 64 bases
+// each side, and keep what their walks need; no position is conditional then, and
+// slices begin at known bits.
+template <int KEEP, bool FULL = false>
 __device__ __forceinline__ int32_t window_pass(uint64_t p0, uint64_t p1, const uint32_t (&t)[4], int32_t a, int32_t b,
                                                bool anchored, int32_t from, int32_t upto, uint32_t *kept) {
   // (halves: v_bitop3_b32 takes any function of three words, bit by bit)
@@ -113,12 +109,13 @@ __device__ __forceinline__ int32_t window_pass(uint64_t p0, uint64_t p1, const u
   const uint32_t pa0 = (uint32_t)p0, pa1 = (uint32_t)(p0 >> 32), pb0 = (uint32_t)p1, pb1 = (uint32_t)(p1 >> 32);
   const uint32_t hin = anchored ? 1u : 0u;
   const int32_t e0 = a - b, last = min(b, upto);
-  for (int32_t w = 0; 16 * w < upto; ++w) {
+#pragma unroll FULL ? 4 : 1
+  for (int32_t w = 0; FULL ? w < 4 : 16 * w < upto; ++w) {
     const int32_t tw = (int32_t)(w == 0 ? t[0] : w == 1 ? t[1] : w == 2 ? t[2] : t[3]);
 #pragma unroll
     for (int32_t u = 0; u < 16; ++u) {
       const int32_t j = 16 * w + u + 1;
-      if (j <= last) {
+      if (FULL || j <= last) {
         const uint32_t t0 = (uint32_t)((tw << (31 - 2 * u)) >> 31), t1 = (uint32_t)((tw << (30 - 2 * u)) >> 31);
         const uint32_t eq0 = neither_diff(pa0 ^ t0, pb0, t1), eq1 = neither_diff(pa1 ^ t0, pb1, t1);
         const uint64_t sum = pair64(eq0 & pl, eq1 & ph_) + pair64(pl, ph_);
@@ -131,10 +128,10 @@ __device__ __forceinline__ int32_t window_pass(uint64_t p0, uint64_t p1, const u
         ph_ = or_nor((uint32_t)(hms >> 32), eq1 | mh_, hs1);
         ml = and_or(hs0, eq0, ml);
         mh_ = and_or(hs1, eq1, mh_);
-        if (KEEP != KEEP_NONE && j > from) {
-          uint32_t *q = kept + (j - 1 - from) * KEEP;
+        if (KEEP != KEEP_NONE && j > (FULL ? GC_FROM : from)) {
+          uint32_t *q = kept + (j - 1 - (FULL ? GC_FROM : from)) * KEEP;
           if (KEEP == KEEP_21) {
-            const int32_t at = at_21(e0 + j);
+            const int32_t at = at_21(FULL ? j : e0 + j);
             const uint32_t v = (uint32_t)(pair64(pl, ph_) >> at), h = (uint32_t)(pair64(hp0, hp1) >> at);
             const uint32_t z = (uint32_t)(pair64(z0, z1) >> at);
             reinterpret_cast<u32x2 *>(q)[lane] = u32x2{(v & 0x1fffffu) | h << 21, ((h >> 11) & 0x3ffu) | z << 10};
@@ -223,6 +220,8 @@ __global__ __launch_bounds__(64) void k_genasm(Seqs S, Outs O, int32_t k, int32_
       const uint64_t tlo = dev::window32(txt, tnw, ne - b), thi = dev::window32(txt, tnw, ne - b + 32);
       const uint64_t p0 = ((uint64_t)dev::even_bits(phi) << 32) | dev::even_bits(plo);
       const uint64_t p1 = ((uint64_t)dev::even_bits(phi >> 1) << 32) | dev::even_bits(plo >> 1);
+      const uint64_t q0 = ((uint64_t)dev::even_bits(thi) << 32) | dev::even_bits(tlo);
+      const uint64_t q1 = ((uint64_t)dev::even_bits(thi >> 1) << 32) | dev::even_bits(tlo >> 1);
       const uint32_t t[4] = {(uint32_t)tlo, (uint32_t)(tlo >> 32), (uint32_t)thi, (uint32_t)(thi >> 32)};
       int32_t lw = max(a, b);
       if (k >= 0) lw = min(lw, k - used);
@@ -237,7 +236,8 @@ __global__ __launch_bounds__(64) void k_genasm(Seqs S, Outs O, int32_t k, int32_
       const bool walk = cig || !anchored;
       int32_t upto = bmax, from = max(0, bmax - KEPT_WORDS / KEEP_21), form = KEEP_21;
       int32_t dist;
-      if (__any(walk)) dist = window_pass<KEEP_21>(p0, p1, t, a, b, anchored, from, upto, kept);
+      if (__all(!anchored && a == GW && b == GW)) dist = window_pass<KEEP_21, true>(p0, p1, t, GW, GW, false, GC_FROM, GW, kept);
+      else if (__any(walk)) dist = window_pass<KEEP_21>(p0, p1, t, a, b, anchored, from, upto, kept);
       else dist = window_pass<KEEP_NONE>(p0, p1, t, a, b, anchored, from, upto, kept);
       if (dist > lw) {
         rej = true;
@@ -267,21 +267,16 @@ __global__ __launch_bounds__(64) void k_genasm(Seqs S, Outs O, int32_t k, int32_
       bool done = false;
       while (true) {
         while (!done) {
-          int32_t r = 0;  // matching bases from (i, j) on, within the window's walk
+          // D(i-1, j-1) = D(i, j) where the bases match, so '=' is available:
+          // the bases that match from (i, j) back, within the window's walk
+          int32_t lim = min(i, j);
+          if (!anchored) lim = min(lim, min(GC - (a - i), GC - (b - j)));
+          const int32_t up = max(i - j, 0), down = max(j - i, 0);
+          const uint64_t x = ((p0 ^ (q0 << up >> down)) | (p1 ^ (q1 << up >> down))) << ((64 - i) & 63);
+          const int32_t r = min(x ? __clzll(x) : 64, lim);
           const bool gap = prev == OP_I || prev == OP_D;
-          for (;;) {
-            // D(i-1, j-1) = D(i, j) where the bases match, so '=' is available
-            int32_t lim = min(i, j);
-            if (!anchored) lim = min(lim, min(GC - (a - i), GC - (b - j)));
-            if (lim <= 0) {
-              done = true;
-              break;
-            }
-            const uint64_t x = tail32(plo, phi, i) ^ tail32(tlo, thi, j);
-            r = min(x ? (__clzll(x) >> 1) : 32, lim);
-            if (r == 0 || gap) break;
-            take(OP_EQ, r);
-          }
+          if (!gap && r > 0) take(OP_EQ, r);
+          done = lim <= 0 || (!gap && r == lim);
           if (done || j <= from) break;
           const uint32_t *q = kept + (j - 1 - from) * form;
           uint32_t v, h, z;  // the differences, the cell's in bit 0
@@ -304,12 +299,10 @@ __global__ __launch_bounds__(64) void k_genasm(Seqs S, Outs O, int32_t k, int32_
             z = (uint32_t)(pair64(w2.x, w2.y) >> (i - 1));
           }
           const bool ins = v & 1u, del = h & 1u;
-          if (prev == OP_I && ins) take(OP_I, 1);
-          else if (prev == OP_D && del) take(OP_D, 1);
-          else if (r > 0) take(OP_EQ, r);
-          else if (!(z & 1u)) take(OP_X, 1);
-          else if (ins) take(OP_I, 1);
-          else take(OP_D, 1);
+          const bool match = gap && r > 0;
+          const uint32_t other = !(z & 1u) ? OP_X : ins ? OP_I : OP_D;
+          const bool on = (prev == OP_I && ins) || (prev == OP_D && del);
+          take(on ? prev : match ? OP_EQ : other, !on && match ? r : 1);
         }
         if (!__any(!done)) break;
         // positions before `from`
