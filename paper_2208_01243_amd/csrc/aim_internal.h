@@ -117,20 +117,28 @@ struct Work {
 
 // ---- host-side launchers (each enqueues on `stream`) ----------------------
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
+// Words to zero in passing (launches bound small batches).
+struct ZeroSpans {
+  int32_t *p[3] = {nullptr, nullptr, nullptr};
+  int64_t n[3] = {0, 0, 0};
+};
 hipError_t launch_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
                              const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off,
-                             hipStream_t s);
+                             const ZeroSpans &Z, hipStream_t s);
 hipError_t launch_pack(int64_t n, int32_t enc, const uint8_t *seq, const int64_t *off,
                        const int32_t *len, int32_t max_len, uint64_t *words, int64_t words_cap,
                        int64_t *out_off, int8_t *flags, int64_t *scan_tmp, hipStream_t s);
-// The same packing with sequence s at word s * ceil(max_len / 32) (one
-// launch, no scan); words_cap must cover n such strides.
-hipError_t launch_pack_strided(int64_t n, int32_t enc, const uint8_t *seq, const int64_t *off,
-                               const int32_t *len, int32_t max_len, uint64_t *words,
-                               int64_t words_cap, int64_t *out_off, int8_t *flags, hipStream_t s);
+// The same packing of both sides ([0] and [1]) with sequence s at word
+// s * ceil(max_len / 32) (one launch, no scan); words_cap must cover n such
+// strides.
+hipError_t launch_pack_strided(int64_t n, int32_t enc, const uint8_t *const seq[2], const int64_t *const off[2],
+                               const int32_t *const len[2], int32_t max_len, uint64_t *const words[2],
+                               int64_t words_cap, int64_t *const out_off[2], int8_t *const flags[2], hipStream_t s);
 size_t scan_tmp_elems(int64_t n);
-// exclusive scan of int32 counts into int64 out[n+1]
-hipError_t launch_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *tmp, hipStream_t s);
+// exclusive scan of int32 counts into int64 out[n+1]; tw: the largest inclusive
+// prefix of at most cap, untouched if none is
+hipError_t launch_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *tmp, hipStream_t s, int64_t cap = 0,
+                           int64_t *tw = nullptr);
 
 // Banded DP (one pair per lane).  W in {32, 64}.
 hipError_t launch_band(int W, bool affine, const Seqs &S, const Outs &O, const Scoring &P,
@@ -406,8 +414,8 @@ hipError_t launch_wfa_trace(const Seqs &S, const Outs &O, const Scoring &P, cons
                             const WfaLaunch &L, int32_t *hbm, int32_t nslots, int32_t threads,
                             bool i16, hipStream_t s);
 
-// CIGAR compaction: cigar_off from nruns (with the cap cut), copy slot and
-// pool runs, collect pairs whose runs could not be held into the spill list.
+// CIGAR compaction: cigar_off from nruns (with the cap cut; total_written is 0
+// before), copy slot and pool runs, collect pairs whose runs could not be held into the spill list.
 hipError_t launch_compact(int64_t n, const Outs &O, int64_t *cigar_off, uint32_t *cigar,
                           int64_t cigar_cap, int64_t *scan_tmp, int64_t *total_written,
                           int32_t *spill_idx, int32_t *spill_count, int8_t *status,
@@ -415,8 +423,8 @@ hipError_t launch_compact(int64_t n, const Outs &O, int64_t *cigar_off, uint32_t
 hipError_t launch_zero_offsets(int64_t n, int64_t *cigar_off, hipStream_t s);
 
 // Length buckets: order[] = pair indices sorted by max(m, n), longest first
-// (128 buckets, 8 per octave; order within a bucket unspecified).  hist needs
-// 128 int32.
+// (128 buckets, 8 per octave; order within a bucket unspecified).  hist: 2 LEN_BUCKETS
+// int32, zero before.
 constexpr int LEN_BUCKETS = 128;
 hipError_t launch_length_sort(int64_t n, const int32_t *pl, const int32_t *tl, int32_t *hist,
                               int32_t *order, hipStream_t s);

@@ -1228,9 +1228,9 @@ static aim_status check_batch(const aim_batch *B) {
 
 // The batch as 2-bit words (packed into scratch unless it already is) and
 // the per-pair validity flags in c->sc->flags.
-// pool_off non-null: set to -1 for every pair on the way.
+// pool_off non-null: set to -1 for every pair on the way, and Z zeroed.
 static aim_status prep_inputs(aim_context *c, const aim_batch *B, hipStream_t s, aim::Seqs &S,
-                              int64_t *pool_off = nullptr) {
+                              int64_t *pool_off = nullptr, const aim::ZeroSpans &Z = {}) {
   aim_status st;
   const int64_t n = B->n_pairs;
   const int32_t L = B->max_len;
@@ -1250,19 +1250,20 @@ static aim_status prep_inputs(aim_context *c, const aim_batch *B, hipStream_t s,
     if ((st = ensure(c, c->sc->tflag, n))) return st;
     // lengths above max_len are flagged invalid below; one slot of
     // ceil(max_len / 32) words per sequence (the buffers hold n of them):
-    // one launch per side, no offset scan
-    HIP_TRY(aim::launch_pack_strided(n, B->enc, (const uint8_t *)B->pat_seq, B->pat_off, B->pat_len, L,
-                                     as<uint64_t>(c->sc->pat2), (int64_t)words, as<int64_t>(c->sc->pat2off),
-                                     as<int8_t>(c->sc->pflag), s));
-    HIP_TRY(aim::launch_pack_strided(n, B->enc, (const uint8_t *)B->txt_seq, B->txt_off, B->txt_len, L,
-                                     as<uint64_t>(c->sc->txt2), (int64_t)words, as<int64_t>(c->sc->txt2off),
-                                     as<int8_t>(c->sc->tflag), s));
+    // one launch for both sides, no offset scan
+    const uint8_t *seq[2] = {(const uint8_t *)B->pat_seq, (const uint8_t *)B->txt_seq};
+    const int64_t *off[2] = {B->pat_off, B->txt_off};
+    const int32_t *len[2] = {B->pat_len, B->txt_len};
+    uint64_t *out[2] = {as<uint64_t>(c->sc->pat2), as<uint64_t>(c->sc->txt2)};
+    int64_t *out_off[2] = {as<int64_t>(c->sc->pat2off), as<int64_t>(c->sc->txt2off)};
+    int8_t *bad[2] = {as<int8_t>(c->sc->pflag), as<int8_t>(c->sc->tflag)};
+    HIP_TRY(aim::launch_pack_strided(n, B->enc, seq, off, len, L, out, (int64_t)words, out_off, bad, s));
     S = {as<uint64_t>(c->sc->pat2), as<int64_t>(c->sc->pat2off), B->pat_len,
          as<uint64_t>(c->sc->txt2), as<int64_t>(c->sc->txt2off), B->txt_len};
     pf = as<int8_t>(c->sc->pflag);
     tf = as<int8_t>(c->sc->tflag);
   }
-  HIP_TRY(aim::launch_pair_flags(n, L, B->pat_len, B->txt_len, pf, tf, as<int8_t>(c->sc->flags), pool_off, s));
+  HIP_TRY(aim::launch_pair_flags(n, L, B->pat_len, B->txt_len, pf, tf, as<int8_t>(c->sc->flags), pool_off, Z, s));
   return AIM_OK;
 }
 
@@ -1322,12 +1323,21 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     c->last_class_window[k] = 0;
     c->last_class_bucket[k] = -1;
   }
-  HIP_TRY(aim::launch_fill_i32(cnt, 0, C_ALL, s));
 
   // ---- input encoding ----
   aim::Seqs S;
   if ((st = ensure(c, c->sc->pooloff, (size_t)n * 8))) return st;
-  if ((st = prep_inputs(c, B, s, S, as<int64_t>(c->sc->pooloff)))) return st;
+  const Tune tu = tune_for(c, alg, L);
+  const bool do_sort = (tu.sort >= 0 ? tu.sort != 0 : (alg != AIM_NW_LINEAR && alg != AIM_SWG_AFFINE) || L >= 512) &&
+                       c->opt.kernel != AIM_KERNEL_PLAIN;
+  // counters, the CIGAR total and the pool's top, and the length buckets
+  aim::ZeroSpans Z{{cnt, as<int32_t>(c->sc->total), nullptr}, {C_ALL, 4, 0}};
+  if (do_sort) {
+    if ((st = ensure(c, c->sc->hist, 2 * aim::LEN_BUCKETS * 4))) return st;
+    Z.p[2] = as<int32_t>(c->sc->hist);
+    Z.n[2] = 2 * aim::LEN_BUCKETS;
+  }
+  if ((st = prep_inputs(c, B, s, S, as<int64_t>(c->sc->pooloff), Z))) return st;
 
   // pool for runs beyond the per-pair slot (reset every call)
   // sized from the batch (a quarter of the worst-case run count per pair),
@@ -1339,14 +1349,10 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
                                                           n * std::min<int64_t>(2 * (int64_t)L + 1, 8192) / 4))
                     : 1;
   if ((st = ensure(c, c->sc->pool, (size_t)pool_cap * 4))) return st;
-  HIP_TRY(aim::launch_fill_i32(as<int32_t>(c->sc->total) + 2, 0, 2, s));
   // a2: length buckets, longest first (LPT order for the persistent queues)
-  const Tune tu = tune_for(c, alg, L);
-  const bool do_sort = tu.sort >= 0 ? tu.sort != 0 : (alg != AIM_NW_LINEAR && alg != AIM_SWG_AFFINE) || L >= 512;
   const int32_t *order = nullptr;
-  if (do_sort && c->opt.kernel != AIM_KERNEL_PLAIN) {
+  if (do_sort) {
     if ((st = ensure(c, c->sc->order, (size_t)n * 4))) return st;
-    if ((st = ensure(c, c->sc->hist, aim::LEN_BUCKETS * 4))) return st;
     Phase ph(c, s, "sort");
     HIP_TRY(aim::launch_length_sort(n, B->pat_len, B->txt_len, as<int32_t>(c->sc->hist),
                                     as<int32_t>(c->sc->order), s));

@@ -1,4 +1,6 @@
 // Sequence packing, per-pair validation, prefix scan and CIGAR compaction.
+#include <algorithm>
+
 #include "aim_internal.h"
 
 namespace aim {
@@ -13,7 +15,11 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
 }
 
 __global__ void k_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
-                             const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off) {
+                             const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off,
+                             ZeroSpans Z) {
+  for (int k = 0; k < 3; ++k)
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < Z.n[k]; i += (int64_t)gridDim.x * blockDim.x)
+      Z.p[k][i] = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t a = pl[i], b = tl[i];
@@ -36,51 +42,77 @@ __global__ void k_word_counts(int64_t n, const int32_t *len, int32_t max_len, in
   }
 }
 
-// One wavefront per sequence; lane l packs bytes [32 l, 32 l + 32) of each
-// 64-word group, so a wave reads 2 KB of contiguous input per iteration.
+// G neighbouring lanes per sequence, each packs 8 bases (16 bits of a word) at a
+// time: the sequence's last 8 bytes stand in for those past its end.  With a
+// wavefront per sequence and a byte at a time two sides of 10,000 x 100 bases
+// took 50 us, now 5; launch latency bounds such batches, and memory large ones.
 // stride > 0: sequence s starts at word s * stride, written to woff_set
-// (entries 0..n); else at woff[s].
-__global__ __launch_bounds__(256) void k_pack(int64_t n, int32_t enc, const uint8_t *seq,
-                                              const int64_t *off, const int32_t *len,
-                                              int32_t max_len, uint64_t *words,
-                                              int64_t words_cap, const int64_t *woff,
-                                              int8_t *flags, int64_t stride, int64_t *woff_set) {
-  const int lane = threadIdx.x & 63;
-  const int64_t s = blockIdx.x * (int64_t)(blockDim.x / 64) + (threadIdx.x >> 6);
-  if (s >= n) return;
-  if (stride > 0 && lane == 0) {
-    woff_set[s] = s * stride;
-    if (s == n - 1) woff_set[n] = n * stride;
-  }
-  if (len[s] > max_len) {
-    if (flags && lane == 0) flags[s] = 1;
-    return;
-  }
-  const int32_t L = len[s] > 0 ? len[s] : 0;
-  const uint8_t *src = seq + off[s];
-  const int64_t w0 = stride > 0 ? s * stride : woff[s];
-  const int32_t nw = (L + 31) >> 5;
+// (entries 0..n); else at woff[s].  blockIdx.y: the side.
+struct PackSide {
+  const uint8_t *seq;
+  const int64_t *off;
+  const int32_t *len;
+  uint64_t *words;
+  const int64_t *woff;
+  int8_t *flags;
+  int64_t *woff_set;
+};
+__global__ __launch_bounds__(256) void k_pack(int64_t n, int32_t enc, PackSide A, PackSide B, int32_t max_len,
+                                              int64_t words_cap, int64_t stride, int32_t G) {
+  const PackSide P = blockIdx.y ? B : A;
+  const int64_t s = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G;
+  const int32_t part = threadIdx.x & (G - 1);
   bool bad = false;
-  for (int32_t w = lane; w < nw; w += 64) {
-    uint64_t v = 0;
-    const int32_t b0 = w * 32;
-    const int32_t cnt = min(32, L - b0);
-    for (int32_t t = 0; t < cnt; ++t) {
-      const uint8_t c = src[b0 + t];
-      uint32_t code;
-      if (enc == 0) {
-        code = c == 'A' ? 0u : c == 'C' ? 1u : c == 'G' ? 2u : c == 'T' ? 3u : 4u;
-      } else {
-        code = c;
-      }
-      if (code > 3u) { bad = true; code = 0; }
-      v |= (uint64_t)code << (2 * t);
+  int32_t L = 0;
+  if (s < n) {
+    if (stride > 0 && part == 0) {
+      P.woff_set[s] = s * stride;
+      if (s == n - 1) P.woff_set[n] = n * stride;
     }
-    if (w0 + w < words_cap) words[w0 + w] = v;
-    else bad = true;
+    L = P.len[s];
+    if (L > max_len) {
+      bad = true;
+      L = 0;
+    }
+    const uint8_t *src = P.seq + (L > 0 ? P.off[s] : 0);
+    const int64_t w0 = stride > 0 ? s * stride : P.woff[s];
+    const int32_t pieces = L > 0 ? 4 * ((L + 31) >> 5) : 0;
+    for (int32_t q = part; q < pieces; q += G) {
+      const int32_t have = min(L - 8 * q, 8);  // bases of this piece (<= 0: none)
+      uint64_t v = 0;
+      if (have == 8) {
+        __builtin_memcpy(&v, src + 8 * q, 8);
+      } else if (have > 0 && L >= 8) {
+        __builtin_memcpy(&v, src + L - 8, 8);
+        v >>= 8 * (8 - have);
+      } else {
+        for (int32_t t = 0; t < have; ++t) v |= (uint64_t)src[8 * q + t] << (8 * t);
+      }
+      constexpr uint64_t B1 = 0x0101010101010101ull;
+      uint64_t code, wrong;  // a byte each; wrong: not 0 where the byte is no base
+      if (enc == 0) {
+        // bits 1 and 2 tell A, C, T, G apart; what they stand for is then compared
+        const uint64_t x = (v >> 1) & (3 * B1), isT = (x >> 1) & ~x & B1;
+        code = x ^ ((x >> 1) & B1);
+        wrong = v ^ ((0x41 * B1 | x << 1) ^ isT * 0x11);
+      } else {
+        code = v & (3 * B1);
+        wrong = v & (0xfc * B1);
+      }
+      const uint64_t in = have >= 8 ? ~0ull : have > 0 ? (1ull << (8 * have)) - 1 : 0ull;
+      wrong = ((((wrong & (0x7f * B1)) + 0x7f * B1) | wrong) >> 7) & B1 & in;
+      bad |= wrong != 0;
+      code &= in & ~(wrong * 3);
+      code = (code | code >> 6) & 0x000f000f000f000full;
+      code = (code | code >> 12) & 0x000000ff000000ffull;
+      code |= code >> 24;
+      const int64_t w = w0 + (q >> 2);
+      if (w < words_cap) reinterpret_cast<uint16_t *>(P.words + w)[q & 3] = (uint16_t)code;
+      else bad = true;
+    }
   }
-  const bool any_bad = __ballot(bad) != 0;
-  if (flags && lane == 0) flags[s] = any_bad ? 1 : 0;
+  const uint64_t any = __ballot(bad) >> ((threadIdx.x & 63) & ~(G - 1));
+  if (s < n && P.flags && part == 0) P.flags[s] = (any & (G == 64 ? ~0ull : (1ull << G) - 1)) ? 1 : 0;
 }
 
 // ---- three-phase exclusive scan of int32 -> int64 ----
@@ -128,10 +160,30 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(int64_t *tmp, int64_t nb) 
   if (threadIdx.x == 0) tmp[nb] = carry;
 }
 
+// tops: tmp holds the tiles' own sums (few enough to add up in each block, which
+// saves a launch), else their exclusive prefixes and the total.
+// tw non-null: receives the largest inclusive prefix that fits in cap, if any.
+constexpr int64_t SCAN_OWN_TOPS = 2048;
 __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(const int32_t *in, int64_t n,
                                                           const int64_t *tmp, int64_t *out,
-                                                          int64_t nb) {
+                                                          int64_t nb, bool tops, int64_t cap, int64_t *tw) {
   __shared__ int64_t buf[SCAN_TILE];
+  __shared__ int64_t sums[SCAN_BLOCK];
+  int64_t before = 0;
+  if (tops) {
+    int64_t part = 0;
+    for (int64_t k = threadIdx.x; k < blockIdx.x; k += SCAN_BLOCK) part += tmp[k];
+    sums[threadIdx.x] = part;
+    __syncthreads();
+    for (int w = SCAN_BLOCK / 2; w > 0; w >>= 1) {
+      if (threadIdx.x < w) sums[threadIdx.x] += sums[threadIdx.x + w];
+      __syncthreads();
+    }
+    before = sums[0];
+    __syncthreads();
+  } else {
+    before = tmp[blockIdx.x];
+  }
   const int64_t base = blockIdx.x * (int64_t)SCAN_TILE;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t i = base + (int64_t)k * SCAN_BLOCK + threadIdx.x;
@@ -139,7 +191,6 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(const int32_t *in, in
   }
   __syncthreads();
   // each thread scans a contiguous run of SCAN_ITEMS, then a block scan of sums
-  __shared__ int64_t sums[SCAN_BLOCK];
   int64_t local[SCAN_ITEMS];
   int64_t s = 0;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
@@ -154,22 +205,14 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(const int32_t *in, in
     sums[threadIdx.x] += add;
     __syncthreads();
   }
-  const int64_t pre = tmp[blockIdx.x] + sums[threadIdx.x] - s;
+  const int64_t pre = before + sums[threadIdx.x] - s;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t i = base + threadIdx.x * SCAN_ITEMS + k;
-    if (i < n) out[i] = pre + local[k];
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = tmp[nb];
-}
-
-// ---- CIGAR compaction ----
-// total_written = the largest inclusive prefix that fits in cigar_cap
-__global__ void k_cut(int64_t n, const int64_t *excl, int64_t cap, unsigned long long *tw) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t incl = excl[i + 1];
-    if (incl <= cap && (i + 1 == n || excl[i + 2] > cap))
-      atomicMax(tw, (unsigned long long)incl);
+    if (i >= n) break;
+    out[i] = pre + local[k];
+    const int64_t incl = pre + local[k] + buf[threadIdx.x * SCAN_ITEMS + k];
+    if (i + 1 == n) out[n] = incl;
+    if (tw && incl <= cap && (i + 1 == n || incl + in[i + 1] > cap)) *tw = incl;  // of one i at most
   }
 }
 
@@ -253,8 +296,6 @@ __global__ void k_zero_offsets(int64_t n, int64_t *off) {
     off[i] = 0;
 }
 
-__global__ void k_zero_u64(unsigned long long *p) { *p = 0ull; }
-
 // ---- length buckets: counting sort of pairs, longest first ----
 constexpr int NBUCKET = 128;
 
@@ -267,55 +308,67 @@ __device__ __forceinline__ int len_bucket(int32_t m, int32_t n) {
   return NBUCKET - 1 - b;
 }
 
+// Adds this lane's bucket (b < 0: none) to LDS counts and returns its rank: one
+// atomic for the wavefront where all its lanes have the same bucket.
+__device__ __forceinline__ int bucket_count(int32_t *cnt, int b) {
+  const uint64_t have = __ballot(b >= 0);
+  if (have == 0) return 0;
+  const int b0 = __shfl(b, __ffsll((unsigned long long)have) - 1);
+  if (__ballot(b == b0) != have) return b >= 0 ? atomicAdd(&cnt[b], 1) : 0;
+  const int lane = threadIdx.x & 63;
+  int r = 0;
+  if (lane == 0) r = atomicAdd(&cnt[b0], __popcll(have));
+  return __shfl(r, 0) + __popcll(have & ((1ull << lane) - 1));
+}
+
 __global__ void k_bucket_hist(int64_t n, const int32_t *pl, const int32_t *tl, int32_t *hist) {
   __shared__ int32_t h[NBUCKET];
   for (int k = threadIdx.x; k < NBUCKET; k += blockDim.x) h[k] = 0;
   __syncthreads();
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    atomicAdd(&h[len_bucket(pl[i], tl[i])], 1);
+  for (int64_t t0 = blockIdx.x * (int64_t)blockDim.x; t0 < n; t0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = t0 + threadIdx.x;
+    bucket_count(h, i < n ? len_bucket(pl[i], tl[i]) : -1);
+  }
   __syncthreads();
   for (int k = threadIdx.x; k < NBUCKET; k += blockDim.x)
     if (h[k]) atomicAdd(&hist[k], h[k]);
 }
 
-// hist -> exclusive offsets in place (one block)
-__global__ void k_bucket_scan(int32_t *hist) {
-  if (threadIdx.x == 0) {
-    int32_t acc = 0;
-    for (int k = 0; k < NBUCKET; ++k) {
-      const int32_t v = hist[k];
-      hist[k] = acc;
-      acc += v;
-    }
-  }
-}
-
 // Per tile of blockDim pairs: ranks within the tile's buckets from LDS
 // atomics, then one global atomic per non-empty bucket reserves the tile's
 // range (fixed-length batches put nearly every pair in one bucket, where one
-// global atomic per pair would serialise).
+// global atomic per pair would serialise).  Every block adds up the buckets
+// itself.
 __global__ __launch_bounds__(256) void k_bucket_scatter(int64_t n, const int32_t *pl, const int32_t *tl,
-                                                       int32_t *cursor, int32_t *order) {
-  __shared__ int32_t cnt[NBUCKET], base[NBUCKET];
+                                                       const int32_t *hist, int32_t *cursor, int32_t *order) {
+  __shared__ int32_t cnt[NBUCKET], base[NBUCKET], first[NBUCKET];
+  if (threadIdx.x < NBUCKET) first[threadIdx.x] = hist[threadIdx.x];
+  __syncthreads();
+  for (int w = 1; w < NBUCKET; w <<= 1) {
+    const int32_t add = (int)threadIdx.x >= w && threadIdx.x < NBUCKET ? first[threadIdx.x - w] : 0;
+    __syncthreads();
+    if (threadIdx.x < NBUCKET) first[threadIdx.x] += add;
+    __syncthreads();
+  }
+  if (threadIdx.x < NBUCKET) first[threadIdx.x] -= hist[threadIdx.x];
   for (int64_t t0 = blockIdx.x * (int64_t)blockDim.x; t0 < n; t0 += (int64_t)gridDim.x * blockDim.x) {
     for (int k = threadIdx.x; k < NBUCKET; k += blockDim.x) cnt[k] = 0;
     __syncthreads();
     const int64_t i = t0 + threadIdx.x;
-    int b = 0, r = 0;
-    if (i < n) {
-      b = len_bucket(pl[i], tl[i]);
-      r = atomicAdd(&cnt[b], 1);
-    }
+    const int b = i < n ? len_bucket(pl[i], tl[i]) : -1;
+    const int r = bucket_count(cnt, b);
     __syncthreads();
     for (int k = threadIdx.x; k < NBUCKET; k += blockDim.x)
-      if (cnt[k]) base[k] = atomicAdd(&cursor[k], cnt[k]);
+      if (cnt[k]) base[k] = first[k] + atomicAdd(&cursor[k], cnt[k]);
     __syncthreads();
     if (i < n) order[base[b] + r] = (int32_t)i;
     __syncthreads();
   }
 }
 
+// blocks of several tiles, for a tile's reservation is an atomic on one address
+inline dim3 sort_grid(int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)); }
+inline dim3 pack_grid(int64_t n, int32_t lanes, int sides) { return dim3((unsigned)((n + 256 / lanes - 1) / (256 / lanes)), sides); }
 inline dim3 grid_for(int64_t n, int block) {
   int64_t g = (n + block - 1) / block;
   if (g < 1) g = 1;
@@ -334,23 +387,25 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
 
 hipError_t launch_pair_flags(int64_t n, int32_t max_len, const int32_t *pl, const int32_t *tl,
                              const int8_t *pf, const int8_t *tf, int8_t *flags, int64_t *pool_off,
-                             hipStream_t s) {
+                             const ZeroSpans &Z, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pair_flags, grid_for(n, 256), dim3(256), 0, s, n, max_len, pl, tl, pf, tf,
-                     flags, pool_off);
+  const int64_t work = std::max({n, Z.n[0], Z.n[1], Z.n[2]});
+  hipLaunchKernelGGL(k_pair_flags, grid_for(work, 256), dim3(256), 0, s, n, max_len, pl, tl, pf, tf,
+                     flags, pool_off, Z);
   return hipGetLastError();
 }
 
 hipError_t launch_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *tmp,
-                           hipStream_t s) {
+                           hipStream_t s, int64_t cap, int64_t *tw) {
   const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
   if (nb == 0) {
     hipLaunchKernelGGL(k_zero_offsets, dim3(1), dim3(64), 0, s, (int64_t)0, out);
     return hipGetLastError();
   }
+  const bool tops = nb <= SCAN_OWN_TOPS;
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, in, n, tmp);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, s, tmp, nb);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, in, n, tmp, out, nb);
+  if (!tops) hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, s, tmp, nb);
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, in, n, tmp, out, nb, tops, cap, tw);
   return hipGetLastError();
 }
 
@@ -366,23 +421,21 @@ hipError_t launch_pack(int64_t n, int32_t enc, const uint8_t *seq, const int64_t
   hipLaunchKernelGGL(k_word_counts, grid_for(n, 256), dim3(256), 0, s, n, len, max_len, cnt);
   hipError_t err = launch_scan_i32(cnt, n, out_off, scan_tmp, s);
   if (err != hipSuccess) return err;
-  const int64_t blocks = (n + 3) / 4;
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, s, n, enc, seq, off, len, max_len,
-                     words, words_cap, out_off, flags, (int64_t)0, (int64_t *)nullptr);
+  const PackSide A{seq, off, len, words, out_off, flags, nullptr};
+  hipLaunchKernelGGL(k_pack, pack_grid(n, 64, 1), dim3(256), 0, s, n, enc, A, A, max_len, words_cap, (int64_t)0, 64);
   return hipGetLastError();
 }
 
-hipError_t launch_pack_strided(int64_t n, int32_t enc, const uint8_t *seq, const int64_t *off,
-                               const int32_t *len, int32_t max_len, uint64_t *words,
-                               int64_t words_cap, int64_t *out_off, int8_t *flags, hipStream_t s) {
-  if (n == 0) {
-    hipLaunchKernelGGL(k_zero_offsets, dim3(1), dim3(64), 0, s, (int64_t)0, out_off);
-    return hipGetLastError();
-  }
+hipError_t launch_pack_strided(int64_t n, int32_t enc, const uint8_t *const seq[2], const int64_t *const off[2],
+                               const int32_t *const len[2], int32_t max_len, uint64_t *const words[2],
+                               int64_t words_cap, int64_t *const out_off[2], int8_t *const flags[2], hipStream_t s) {
+  if (n == 0) return hipSuccess;
   const int64_t stride = ((int64_t)max_len + 31) / 32 > 0 ? ((int64_t)max_len + 31) / 32 : 1;
-  const int64_t blocks = (n + 3) / 4;
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, s, n, enc, seq, off, len, max_len,
-                     words, words_cap, (const int64_t *)nullptr, flags, stride, out_off);
+  int32_t G = 4;
+  while (G < 64 && (int64_t)G * 8 < max_len) G *= 2;
+  const PackSide A{seq[0], off[0], len[0], words[0], nullptr, flags[0], out_off[0]};
+  const PackSide B{seq[1], off[1], len[1], words[1], nullptr, flags[1], out_off[1]};
+  hipLaunchKernelGGL(k_pack, pack_grid(n, G, 2), dim3(256), 0, s, n, enc, A, B, max_len, words_cap, stride, G);
   return hipGetLastError();
 }
 
@@ -392,12 +445,10 @@ hipError_t launch_compact(int64_t n, const Outs &O, int64_t *cigar_off, uint32_t
                           hipStream_t s) {
   // scan_tmp layout: [scan blocks | excl (n+1)]
   int64_t *excl = scan_tmp + scan_tmp_elems(n);
-  hipError_t err = launch_scan_i32(O.nruns, n, excl, scan_tmp, s);
+  hipError_t err = launch_scan_i32(O.nruns, n, excl, scan_tmp, s, cigar_cap, total_written);
   if (err != hipSuccess) return err;
   unsigned long long *tw = (unsigned long long *)total_written;
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, tw);
   if (n > 0) {
-    hipLaunchKernelGGL(k_cut, grid_for(n, 256), dim3(256), 0, s, n, excl, cigar_cap, tw);
     // 64 pairs per wavefront, fewer where that would leave the chip short of
     // wavefronts (under 4,096)
     int32_t per = 64;
@@ -414,10 +465,8 @@ hipError_t launch_compact(int64_t n, const Outs &O, int64_t *cigar_off, uint32_t
 hipError_t launch_length_sort(int64_t n, const int32_t *pl, const int32_t *tl, int32_t *hist,
                               int32_t *order, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(NBUCKET), 0, s, hist, 0, (int64_t)NBUCKET);
-  hipLaunchKernelGGL(k_bucket_hist, grid_for(n, 256), dim3(256), 0, s, n, pl, tl, hist);
-  hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(64), 0, s, hist);
-  hipLaunchKernelGGL(k_bucket_scatter, grid_for(n, 256), dim3(256), 0, s, n, pl, tl, hist, order);
+  hipLaunchKernelGGL(k_bucket_hist, sort_grid(n), dim3(256), 0, s, n, pl, tl, hist);
+  hipLaunchKernelGGL(k_bucket_scatter, sort_grid(n), dim3(256), 0, s, n, pl, tl, hist, hist + NBUCKET, order);
   return hipGetLastError();
 }
 
