@@ -684,6 +684,10 @@ int64_t wide_pair_words(const aim::Scoring &P, int32_t L, const WidePass &wp) {
   return w;
 }
 int32_t wide_tokens(int32_t L) { return 2 * (2 * L + 1) + 8; }
+// Whether `share` bytes hold any pair's codes for each of `slots` workgroups.
+bool wide_share_fits(const aim::Scoring &P, int32_t L, const WidePass &wp, int64_t share, int64_t slots) {
+  return !P.want_cigar || share >= 4 * (wide_pair_words(P, L, wp) + wp.threads / 64 * wide_tokens(L)) * slots;
+}
 // Launch over the listed pairs; D: route, class index and fallback lists.
 aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
                             int32_t L, const WidePass &wp, const aim::Work &W, aim::WfaWide D, int64_t share, hipStream_t s) {
@@ -735,8 +739,7 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
     for (const GroupPass &gp : passes)
       if (share < 2 * least * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
     for (int k = 0; k < nw; ++k)
-      if (wide_share < 4 * (wide_pair_words(P, L, WIDE_PASS[k]) + WIDE_PASS[k].threads / 64 * wide_tokens(L)) * std::min<int64_t>(n, 64))
-        return AIM_OK;
+      if (!wide_share_fits(P, L, WIDE_PASS[k], wide_share, std::min<int64_t>(n, 64))) return AIM_OK;
   }
   aim_status st;
   const int32_t ng = (int32_t)passes.size() - 1, later = ng + nw;
@@ -858,13 +861,14 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
         c->last_class_bucket[cls.size()] = cb;
         cls.push_back({2 * wp.threads * wp.words, wp.threads, 0, false, wp.reach(), k});
         prev_half = wp.reach();
-        if (prev_half >= L) break;
+        // (a pair whose codes the pass has no room for goes on to the next)
+        if (prev_half >= L && wide_share_fits(P, L, wp, c->limit() / 3, 1)) break;
         continue;
       }
       const bool glob = (ctp && ctp->global >= 0) ? ctp->global != 0 : ((tu.wfa_cls_global >> k) & 1) != 0;
       const int32_t w = glob ? full : std::min<int64_t>((int64_t)2 * std::min(bound[k], wmax / 2), wmax);
       const int32_t half = glob ? bound[k] : w / 2;
-      if (std::min(half, w / 2) <= prev_half) continue;
+      if (std::min(half, w / 2) <= prev_half && prev_half < L) continue;
       const size_t lds = aim::wfa_lds_bytes(w, MG, pl.R, P.e, pl.seq_words, glob);
       if (lds > lds_cap) continue;
       const int32_t th = (ctp && ctp->threads > 0) ? ctp->threads : tu.wfa_cls_threads[k];

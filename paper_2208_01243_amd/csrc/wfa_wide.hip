@@ -410,6 +410,8 @@ __global__ __launch_bounds__(T, 4) void k_wfa_wide(Seqs S, Outs O, Scoring P, Wo
         // past the last score to try
         W.result = P.max_score >= 0 && s + 1 > P.max_score ? 2 : s + 1 > upper ? 4 : 3;
       }
+      // codes not kept: a later class may have the room
+      if (W.result == 1 && P.want_cigar && !W.keep && L.my_class < L.route.nclass) W.result = 3;
       if (W.result == 3) {
         // on to a later class, with the extent the pair is predicted to need:
         // from the furthest anti-diagonal i + j any kept M offset reaches
