@@ -656,7 +656,7 @@ aim_status launch_group_passes(aim_context *c, const aim::Seqs &S, const aim::Ou
     Phase ph(c, s, names[k]);
     HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, gp.lanes, gp.words, false, s));
   }
-  c->last_window = 2 * passes[0].lanes * passes[0].words;
+  if (!passes.empty()) c->last_window = 2 * passes[0].lanes * passes[0].words;
   return AIM_OK;
 }
 
@@ -721,7 +721,7 @@ aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs 
 // 3,069 bp, or a low threshold): those passes alone, with no list, ring or store
 // of the others.  (A walk cannot fail on codes that were kept; if one did its
 // pair would get CIGAR_OVERFLOW.)  `done` false: not such a batch, nothing
-// launched.
+// launched.  (No group passes: the wide ones take every pair.)
 aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n, int32_t L,
                          int32_t *cnt, const int32_t *order, const int32_t *order_count,
                          const std::vector<GroupPass> &passes, hipStream_t s, bool &done) {
@@ -729,13 +729,13 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
   const int32_t most = wfa_most_scores(P, L), reach = wfa_reach(P, L);
   if (most > 16000) return AIM_OK;
   int nw = 0;
-  for (int32_t r = passes.back().reach(); r < reach; r = WIDE_PASS[nw++].reach())
+  for (int32_t r = passes.empty() ? 0 : passes.back().reach(); r < reach || nw + passes.size() == 0; r = WIDE_PASS[nw++].reach())
     if (nw == 2 || !wide_fits(P, L, WIDE_PASS[nw])) return AIM_OK;
   const int64_t share = c->limit() / 8, wide_share = c->limit() / 3;
   int64_t least = 64;  // steps of codes: any pair's of the pass
   if (P.want_cigar) {
     // in 64 workgroups at least
-    least = (nw > 0 ? std::min(most, passes.back().reach() + P.o) : most) + 8;
+    if (!passes.empty()) least = (nw > 0 ? std::min(most, passes.back().reach() + P.o) : most) + 8;
     for (const GroupPass &gp : passes)
       if (share < 2 * least * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
     for (int k = 0; k < nw; ++k)
@@ -764,7 +764,11 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
     D.my_class = ng + 1 + k;
     D.walk_fail = cnt + C_WF;
     c->last_class_window[k] = 2 * WIDE_PASS[k].threads * WIDE_PASS[k].words;
-    const aim::Work W{D.route.list[D.my_class], D.route.count[D.my_class], n, cnt + C_CL + 4 + k, nullptr, nullptr, 0};
+    aim::Work W{D.route.list[D.my_class], D.route.count[D.my_class], n, cnt + C_CL + 4 + k, nullptr, nullptr, 0};
+    if (D.my_class == 0) {  // no group pass before it
+      W.idx = order;
+      W.count = order_count;
+    }
     if ((st = launch_wide_pass(c, S, O, P, n, L, WIDE_PASS[k], W, D, wide_share, s))) return st;
   }
   return AIM_OK;
@@ -781,6 +785,18 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   if (group) {
     passes = wfa_group_passes(P, L, small, tu);
     bool done = false;
+    // Small gap-affine batches of reads whose expected reach (a third of their
+    // length, as above) passes the widest group start in the wide pass: their
+    // time is that of the slowest pair, which would run twice, and a workgroup
+    // has a score done in less time than a wavefront.  2,048 pairs of 333-1,000
+    // bp, groups first / wide at once: 760 / 495 us at 8 %, 135 / 153 at 1 %; of
+    // 833-2,500 bp 1,841 / 1,213 and 268 / 277; 64 pairs of 333-1,000 bp 343 / 302
+    // and 104 / 90.  Shorter reads stay narrow (2,048 of 100-300 bp at 8 %: 144 /
+    // 221), and so do linear penalties (of 333-1,000 bp 195 / 299).
+    if (small && P.o > 0 && tu.wfa_c16 == 0 && std::min(wfa_reach(P, L), L / 3) > GroupPass{64, 4}.reach()) {
+      if ((st = run_wfa_short(c, S, O, P, n, L, cnt, order, order_count, {}, s, done))) return st;
+      if (done) return AIM_OK;
+    }
     if ((st = run_wfa_short(c, S, O, P, n, L, cnt, order, order_count, passes, s, done))) return st;
     if (done) return AIM_OK;
   }

@@ -118,3 +118,23 @@ def test_more_pairs_than_await_their_walks(ctx):
     assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
     for i in range(len(k)):
         assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
+
+
+@pytest.mark.parametrize("alg", ["wfa", "swg"])
+@pytest.mark.parametrize("lmax", [761, 762, 1021, 1100, 3069])
+def test_small_batches_start_wide(ctx, alg, lmax):
+    # around the length from which a small batch has no group pass, and where a
+    # second window follows the first; invalid pairs and thresholds on that route
+    rng = np.random.default_rng(lmax)
+    T = [rng.integers(0, 4, int(n)).astype(np.uint8) for n in [lmax, lmax, 0, 1] + rng.integers(0, lmax, 40).tolist()]
+    P = [rng.integers(0, 4, max(0, len(t) - 3)).astype(np.uint8) if k % 7 == 0 else _noisy(rng, t, 0.05)[:lmax]
+         for k, t in enumerate(T)]
+    b = synth.from_lists(P, T)
+    for smax in (-1, 40):
+        want = oracle.wfa_batch(b, AFF, smax)
+        got = run(ctx, b, alg, AFF, smax)
+        bad = compare(got, want)
+        assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
+    short = run(ctx, b, alg, AFF, max_len=lmax - 1)
+    over = np.maximum(b.pat_len, b.txt_len) > lmax - 1
+    assert (short[1][over] == aim.PAIR_INVALID).all() and (short[1][~over] == aim.PAIR_ALIGNED).all()
