@@ -48,24 +48,19 @@ PEAK_PK16_TOPS = 2 * PEAK_INT32_TOPS       # packed 16-bit: two halves per lane 
 # xor, count trailing zeros, advance: 10)
 OPS_PER_CELL = {"swg": 14, "nw": 10}
 WFA_OPS_PER_CELL, WFA_OPS_PER_WORD = 8, 10
-# GenASM: a status-vector update (one 64-bit vector at one text position and
-# edit level: match shift, start bit and text mask; the level below's
-# substitution, insertion and deletion terms; the window mask: 14 int32 ops)
-# stores its 8-byte vector for the traceback; a traceback step (12 ops) reads
-# at least one stored vector
-GENASM_OPS_PER_UPDATE, GENASM_OPS_PER_STEP, GENASM_BYTES_PER_UPDATE, GENASM_BYTES_PER_STEP = 14, 12, 8, 8
+# GenASM: a text position of a window (one step of the distance recurrence on 64
+# pattern bases: 12 operations on 64-bit vectors) and a traceback step
+GENASM_OPS_PER_POSITION, GENASM_OPS_PER_STEP = 24, 12
 PEAK_HBM_GBS = 8000.0
 # HBM bytes per launch of a kernel from two rocprofv3 --pmc passes (FETCH_SIZE
 # and WRITE_SIZE scaled by a copy-kernel calibration), valid only for the
 # kernel source they were taken on (first 16 hex of the SHA-256 of its source
 # file and the headers it includes)
-MEASURED_TRAFFIC = {("swg150", "k_band16<32>"): ("493d99bad8e4c2d4", 3.0799e9),
-                    ("wfa_mixed", "k_wfa_lds"): ("40348926033b3dc9", 2.2745e12),
-                    ("wfa250", "k_wfa_score16"): ("04f13bb9e7d35d4f", 4.335e9),
-                    ("genasm150", "k_genasm"): ("4e069b03afdd5683", 5.15e9)}
+MEASURED_TRAFFIC = {("wfa_mixed", "k_wfa_wide"): ("97ee7d64d965ec62", 1.1823e11)}
 KERNEL_SOURCE = {"k_band16<32>": ("dp_band16.hip", "aim_internal.h", "dev_util.h"),
                  "k_band<32>": ("dp_band.hip", "aim_internal.h"),
-                 "k_wfa_score16": ("wfa.hip", "aim_internal.h", "wfa_common.h"),
+                 "k_wfa_group": ("wfa_group.hip", "aim_internal.h", "wfa_common.h", "wfa_packed.h"),
+                 "k_wfa_wide": ("wfa_wide.hip", "aim_internal.h", "wfa_common.h", "wfa_packed.h"),
                  "k_wfa_score": ("wfa.hip", "aim_internal.h", "wfa_common.h"),
                  "k_wfa_lds": ("wfa_lds.hip", "aim_internal.h", "wfa_common.h"),
                  "k_genasm": ("genasm.hip", "aim_internal.h", "dev_util.h")}
@@ -112,8 +107,8 @@ def genasm_units(name):
 
 
 def wfa_units(name, window, filtered=False):
-    """(cells, words) of the pairs the one-wavefront pass completes (extent <=
-    window / 2) and of the rest, from the oracle's counts; None if absent.
+    """(cells, words) of the pairs that stay in a window of that many diagonals
+    (extent <= window / 2) and of the rest, from the oracle's counts; None if absent.
     filtered: only the pairs the pre-alignment filter lets through (the
     wavefront kernels see no others)."""
     path = os.path.join(ROOT, "tests", "golden", "wfa_work.json")
@@ -197,13 +192,14 @@ def roofline(run, phases, stats, steps):
                 "avg_launch_ms": round(ms / launches, 4), "ops_per_unit": OPS_PER_CELL[w["alg"]],
                 "units_per_launch": cells, "unit_name": "band cells (m x 32 per pair)"}
     if w["alg"] == "wfa_adaptive":
-        # one kernel (k_wfa_lds with the reduction step) over every pair
+        # k_wfa_group with the reduction step: every pair, and those whose
+        # wavefronts outgrow their lanes again on more of them
         if "wfa_adaptive" not in phases:
             return None
-        ms, launches = phases["wfa_adaptive"]
-        ms /= max(1, launches)
+        ms = sum(phases[k][0] for k in ("wfa_adaptive", "wfa_adaptive_b") if k in phases)
+        ms /= max(1, phases["wfa_adaptive"][1])
         units = wfa_units(run.name, 0) if run.n == w["total"] else None
-        out = {"bound": "alu", "kernel": "k_wfa_lds (adaptive)", "avg_launch_ms": round(ms, 4),
+        out = {"bound": "alu", "kernel": "k_wfa_group (adaptive)", "avg_launch_ms": round(ms, 4),
                "peak": round(PEAK_INT32_TOPS, 1), "unit": "Tops/s (int32)",
                "ops_per_unit": {"wavefront cell": WFA_OPS_PER_CELL, "extension word": WFA_OPS_PER_WORD},
                "achieved": None, "frac": None, "traffic": None}
@@ -215,50 +211,42 @@ def roofline(run, phases, stats, steps):
                         "unit_name": "cells of the reduced wavefronts (adaptive oracle) of every pair"})
         return out
     if w["alg"] == "genasm":
-        # one kernel, k_genasm, over every pair: the distance calculation is
-        # integer ALU work, and every status vector it builds is stored for
-        # the traceback, so both rooflines are given; `bound` is the tighter
+        # one kernel, k_genasm, over every pair: integer ALU work on data that
+        # stays in registers and LDS
         if "genasm" not in phases:
             return None
         ms, launches = phases["genasm"]
         ms /= max(1, launches)
         u = genasm_units(run.name) if run.n == w["total"] else None
-        meas = MEASURED_TRAFFIC.get((run.name, "k_genasm"))
         out = {"kernel": "k_genasm", "avg_launch_ms": round(ms, 4), "bound": "alu", "achieved": None,
                "peak": round(PEAK_INT32_TOPS, 1), "unit": "Tops/s (int32)", "frac": None, "traffic": None,
-               "ops_per_unit": {"status-vector update": GENASM_OPS_PER_UPDATE,
-                                "traceback step": GENASM_OPS_PER_STEP},
-               "bytes_per_unit": {"status-vector update": GENASM_BYTES_PER_UPDATE,
-                                  "traceback step": GENASM_BYTES_PER_STEP, "base": 0.25}}
+               "ops_per_unit": {"text position": GENASM_OPS_PER_POSITION, "traceback step": GENASM_OPS_PER_STEP}}
         if u:
-            t = ms / 1000.0
-            ops = GENASM_OPS_PER_UPDATE * u["updates"] + GENASM_OPS_PER_STEP * u["tb_steps"]
-            byts = GENASM_BYTES_PER_UPDATE * u["updates"] + GENASM_BYTES_PER_STEP * u["tb_steps"] + u["bases"] / 4
-            alu = {"achieved": round(ops / t / 1e12, 3), "peak": round(PEAK_INT32_TOPS, 1), "unit": "Tops/s (int32)",
-                   "frac": round(ops / t / 1e12 / PEAK_INT32_TOPS, 4)}
-            hbm = {"achieved": round(byts / t / 1e9, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                   "frac": round(byts / t / 1e9 / PEAK_HBM_GBS, 4)}
-            top = hbm if hbm["frac"] > alu["frac"] else alu
-            out.update(top)
-            out["bound"] = "hbm" if top is hbm else "alu"
-            if meas and meas[0] == src_hash("k_genasm"):
-                out["traffic"] = meas[1]
-            out.update({"alu": alu, "hbm": hbm,
-                        "units_per_launch": {"updates": u["updates"], "tb_steps": u["tb_steps"],
+            # a window other than a pair's last goes over 64 text bases and
+            # leaves at least 24 of them to the next
+            positions = int(run.batch.txt_len.sum()) + 24 * (u["windows"] - u["pairs"])
+            ops = GENASM_OPS_PER_POSITION * positions + GENASM_OPS_PER_STEP * u["tb_steps"]
+            out.update({"achieved": round(ops / (ms / 1000) / 1e12, 3),
+                        "frac": round(ops / (ms / 1000) / 1e12 / PEAK_INT32_TOPS, 4),
+                        "units_per_launch": {"positions": positions, "tb_steps": u["tb_steps"],
                                              "windows": u["windows"], "bases": u["bases"]},
-                        "unit_name": "status-vector updates (distance + 1) x text bases per window and "
-                                     "traceback steps, from the oracle's counters over every pair"})
+                        "unit_name": "text positions of every window (text bases plus 24 for each window but a "
+                                     "pair's last) and traceback steps, from the oracle's counters over every pair"})
         return out
     if w["alg"] != "wfa":
         return None
-    # the WFA passes of one call: the one-wavefront pass (k_wfa_score16) over
-    # every pair, completing those whose wavefronts stay in its window; the
-    # window classes (k_wfa_lds, one launch per class, taken together: the
-    # split of pairs between classes is a runtime prediction) completing the
-    # rest; the HBM-ring pass (k_wfa_score) for pairs past 16,000 scores
+    # the WFA passes of one call: the group passes (k_wfa_group: wfa_score, and
+    # wfa_score_b .. _d on twice the window each), completing the pairs whose
+    # wavefronts stay in theirs; k_wfa_wide (two windows) and k_wfa_lds for the
+    # rest, the launches of one kernel taken together; the HBM-ring pass
+    # (k_wfa_score) for pairs past 16,000 scores
     steps = max(1, phases.get("wfa_score", (0.0, 1))[1])
-    groups = {"k_wfa_score16": ["wfa_score"], "k_wfa_lds": [k for k in phases if k.startswith("wfa_lds")],
-              "k_wfa_score": ["wfa_score_hbm"]}
+    groups = {"k_wfa_group": [k for k in ("wfa_score", "wfa_score_b", "wfa_score_c", "wfa_score_d") if k in phases],
+              "k_wfa_wide": [k for k in phases if k.startswith("wfa_wide")],
+              "k_wfa_lds": [k for k in phases if k.startswith("wfa_lds")], "k_wfa_score": ["wfa_score_hbm"]}
+    # windows: of the last group pass, and of the last wide pass
+    w_group = stats.get("wfa_window", 0) << max(0, len(groups["k_wfa_group"]) - 1)
+    w_wide = max([w_group] + [v for v in stats.get("wfa_class_window", [])[:len(groups["k_wfa_wide"])]])
     per_call = {g: sum(phases[k][0] for k in ks if k in phases) / steps for g, ks in groups.items()}
     kname = max(per_call, key=per_call.get)
     if per_call[kname] <= 0:
@@ -266,22 +254,22 @@ def roofline(run, phases, stats, steps):
     ms = per_call[kname]
     launches = sum(phases[k][1] for k in groups[kname] if k in phases) // steps
     filtered = w["max_score"] >= 0  # the pre-alignment filter runs in front
-    units = wfa_units(run.name, stats.get("wfa_window", 0), filtered) if run.n == w["total"] else None
+    units = wfa_units(run.name, 0, filtered) if run.n == w["total"] else None
     out = {"bound": "alu", "kernel": kname, "avg_launch_ms": round(ms, 4), "launches_per_call": launches,
            "peak": round(PEAK_INT32_TOPS, 1), "unit": "Tops/s (int32)",
            "ops_per_unit": {"wavefront cell": WFA_OPS_PER_CELL, "extension word": WFA_OPS_PER_WORD},
            "achieved": None, "frac": None, "traffic": None}
     if units and kname != "k_wfa_score":
-        side = "inside" if kname == "k_wfa_score16" else "outside"
-        cells, words = units[side]
+        lo, hi = {"k_wfa_group": (0, w_group), "k_wfa_wide": (w_group, w_wide), "k_wfa_lds": (w_wide, 1 << 30)}[kname]
+        cells, words = (a - b for a, b in zip(wfa_units(run.name, hi, filtered)["inside"],
+                                              wfa_units(run.name, lo, filtered)["inside"]))
         ops = WFA_OPS_PER_CELL * cells + WFA_OPS_PER_WORD * words
         t = ms / 1000.0
         out.update({"achieved": round(ops / t / 1e12, 3), "frac": round(ops / t / 1e12 / PEAK_INT32_TOPS, 4),
                     "units_per_launch": {"cells": cells, "words": words},
-                    "unit_name": "wavefront cells of the pairs %s completes (%s the %d-diagonal window%s), "
+                    "unit_name": "wavefront cells of the pairs %s completes (windows of %d to %d diagonals%s), "
                                  "its launches of one call together" % (
-                                     kname, side, stats.get("wfa_window", 0),
-                                     "; pairs past the pre-alignment filter" if filtered else "")})
+                                     kname, lo, hi, "; pairs past the pre-alignment filter" if filtered else "")})
         meas = MEASURED_TRAFFIC.get((run.name, kname))
         if meas and meas[0] == src_hash(kname):
             out["traffic"] = meas[1]

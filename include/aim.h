@@ -325,8 +325,9 @@ aim_status aim_timing_reset(aim_context *ctx);
  * an empty batch.  These say which paths the pairs took; they are not part of
  * the results, which are the same whatever the path.
  *   band_escalated / band_escalated2: NW/SWG pairs the 32-diagonal band passed
- *     on to the 64-diagonal band, and that band on to the last tier;
- *   wfa_wide: WFA pairs whose wavefronts left the one-wavefront window;
+ *     on (to the wavefront passes where those take the penalties, else to the
+ *     64-diagonal band), and that band on to the last tier;
+ *   wfa_wide: WFA pairs whose wavefronts left every narrower window;
  *   wfa_walk_failed: WFA pairs whose walk over the kept origin codes failed
  *     (0 unless a code was read back wrong; each is re-walked from a full
  *     store, so results stay exact and only time is lost);
@@ -336,11 +337,12 @@ aim_status aim_timing_reset(aim_context *ctx);
  *     (LDS, 1 MB, 16 MB, largest);
  *   cigar_reruns: pairs whose runs outgrew their slot and the run pool,
  *     re-aligned in place by the compaction;
- *   wfa_window: the diagonals the one-wavefront WFA pass keeps, centred on
- *     diagonal 0 (0: that pass did not run); pairs whose wavefronts stay
- *     inside it are aligned there, the others go to wider windows;
- *   wfa_class_pairs[c] / wfa_class_window[c]: pairs routed to the c-th LDS
- *     window class, and its window in diagonals (0: no such class);
+ *   wfa_window: the diagonals the first WFA pass keeps, centred on diagonal 0
+ *     (0: no such pass ran); pairs whose wavefronts stay inside it are
+ *     aligned there, the others go to wider windows (twice as wide each, then
+ *     the classes);
+ *   wfa_class_pairs[c] / wfa_class_window[c]: pairs routed to the c-th window
+ *     class, and its window in diagonals (0: no such class);
  *     wfa_wide counts the pairs that outgrew them all (HBM-ring pass);
  *   prefilter_rejected: pairs rejected by the pre-alignment filter before
  *     any aligner ran (see aim_prefilter);
@@ -371,11 +373,11 @@ aim_status aim_last_call_stats(aim_context *ctx, aim_call_stats *out);
  * fastest for (alg, length bucket of pairs->max_len); later calls with that
  * key use it.  Candidates: NW/SWG -- first band width {32, 64}, resident
  * wavefronts per CU {8, 16, 32}, length sort {off, on}, packed 16-bit cells
- * {off, on} (32 diagonals only); WFA -- length sort {off, on}, one-wavefront
- * window {64, 128, 256} diagonals, workgroup size for the widest pairs {128,
- * 256}, then, for each window class the batch uses, its workgroup size {64,
- * 128, 256} (pairs per workgroup: one; lanes per pair: the size) and where its
- * ring lives (LDS or a global slot), kept per class length bucket (the
+ * {off, on} (32 diagonals only); WFA -- length sort {off, on}, the first
+ * window, workgroup size for the widest pairs {128,
+ * 256}, then, for each window class the batch uses, the built-in kernel
+ * or one whose workgroup size {64, 128, 256} (pairs per workgroup: one; lanes
+ * per pair: the size) and place of the ring (LDS or a global slot) vary, kept per class length bucket (the
  * class's extent bound, or max_len for the last class), so one mixed batch
  * runs each bucket with its own configuration; WFA-adaptive -- length sort,
  * workgroup size {64, 128}.  Each candidate runs once to warm up and `reps`
@@ -389,19 +391,19 @@ aim_status aim_autotune(aim_context *ctx, const aim_batch *pairs, int32_t alg, a
                         int32_t *best_params, double *best_ms);
 
 /* Launch parameters for (alg, max_len), 13 int32: params[0] first band width,
- * [1] wavefronts per CU (first band tier; GenASM), [2] length sort (-1 auto, 0 off, 1 on), [3] WFA ring
+ * [1] wavefronts per CU (first band tier; GenASM, at most 8), [2] length sort (-1 auto, 0 off, 1 on), [3] WFA ring
  * LDS KB, [4] WFA full-store LDS KB, [5] WFA long-pair workgroup size,
  * [6] packed 16-bit band cells when the value bound allows (0 off; 1 on, each
  * wavefront walking its own pairs' tracebacks; 2 on, the tracebacks walked by
  * a second kernel beside the escalation tiers; 3, the default: 2 for batches
  * of at least 65536 pairs, else 1, or 0 for fewer than 16384 pairs of reads
  * of at most 128 bases), [7] WFA pairs wider than the
- * one-wavefront window go through LDS-window classes (1, the default) or
+ * first windows go through window classes (1, the default) or
  * straight to the HBM-ring pass (0), [8..10] workgroup size (64, 128, 256 or
  * 512) of the three window classes (narrowest first), [11] bit c set: class
  * c + 1 keeps its recent wavefronts in a global buffer rather than LDS, [12]
- * the one-wavefront window in units of 64 diagonals (0: from the batch; at
- * most 4).  A class tune kept for a class's length bucket (aim_autotune)
+ * the first window, of 128, 256, 512 or 512 diagonals for 1 to 4 (64 each
+ * where the penalties take the one-wavefront pass; 0: from the batch).  A class tune kept for a class's length bucket (aim_autotune)
  * overrides [8..11] for that class.  Without a kept tune, the built-in
  * defaults apply (aim_tune_get returns them): those above, except [10] 256
  * and [12] 1 for WFA batches with max_len >= 4096, and [2] 0 for GenASM
