@@ -33,6 +33,12 @@ __device__ __forceinline__ uint32_t even_bits(uint64_t w) {
   return (uint32_t)w;
 }
 
+// Functions of three words, bit by bit: the truth table's index is 4 a + 2 b + c.
+__device__ __forceinline__ uint32_t neither_diff(uint32_t d, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(d, b, c, 0x09); }  // ~(d | (b ^ c))
+__device__ __forceinline__ uint32_t xor_or(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xbe); }        // (a ^ b) | c
+__device__ __forceinline__ uint32_t or_nor(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xf1); }        // a | ~(b | c)
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xe0); }        // a & (b | c)
+
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) v = max(v, __shfl_xor(v, s));

@@ -80,11 +80,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
-// Functions of three words, bit by bit: the truth table's index is 4 a + 2 b + c.
-__device__ __forceinline__ uint32_t neither_diff(uint32_t d, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(d, b, c, 0x09); }  // ~(d | (b ^ c))
-__device__ __forceinline__ uint32_t xor_or(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xbe); }        // (a ^ b) | c
-__device__ __forceinline__ uint32_t or_nor(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xf1); }        // a | ~(b | c)
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xe0); }        // a & (b | c)
 // First bit of a slice around the end diagonal's row e: bits e - 11 .. e + 9 (rows
 // e - 10 .. e + 10), or e - 16 .. e + 15; at the vector's ends its first or last.
 __device__ __forceinline__ int32_t at_21(int32_t e) { return min(max(e - 11, 0), 43); }
@@ -117,17 +112,17 @@ __device__ __forceinline__ int32_t window_pass(uint64_t p0, uint64_t p1, const u
       const int32_t j = 16 * w + u + 1;
       if (FULL || j <= last) {
         const uint32_t t0 = (uint32_t)((tw << (31 - 2 * u)) >> 31), t1 = (uint32_t)((tw << (30 - 2 * u)) >> 31);
-        const uint32_t eq0 = neither_diff(pa0 ^ t0, pb0, t1), eq1 = neither_diff(pa1 ^ t0, pb1, t1);
+        const uint32_t eq0 = dev::neither_diff(pa0 ^ t0, pb0, t1), eq1 = dev::neither_diff(pa1 ^ t0, pb1, t1);
         const uint64_t sum = pair64(eq0 & pl, eq1 & ph_) + pair64(pl, ph_);
-        const uint32_t xh0 = xor_or((uint32_t)sum, pl, eq0), xh1 = xor_or((uint32_t)(sum >> 32), ph_, eq1);
-        const uint32_t hp0 = or_nor(ml, xh0, pl), hp1 = or_nor(mh_, xh1, ph_);  // horizontal +1
+        const uint32_t xh0 = dev::xor_or((uint32_t)sum, pl, eq0), xh1 = dev::xor_or((uint32_t)(sum >> 32), ph_, eq1);
+        const uint32_t hp0 = dev::or_nor(ml, xh0, pl), hp1 = dev::or_nor(mh_, xh1, ph_);  // horizontal +1
         const uint32_t z0 = xh0 | ml, z1 = xh1 | mh_;                           // diagonal 0
         const uint64_t hps = pair64(hp0, hp1) << 1, hms = pair64(pl & xh0, ph_ & xh1) << 1;
         const uint32_t hs0 = (uint32_t)hps | hin, hs1 = (uint32_t)(hps >> 32);
-        pl = or_nor((uint32_t)hms, eq0 | ml, hs0);
-        ph_ = or_nor((uint32_t)(hms >> 32), eq1 | mh_, hs1);
-        ml = and_or(hs0, eq0, ml);
-        mh_ = and_or(hs1, eq1, mh_);
+        pl = dev::or_nor((uint32_t)hms, eq0 | ml, hs0);
+        ph_ = dev::or_nor((uint32_t)(hms >> 32), eq1 | mh_, hs1);
+        ml = dev::and_or(hs0, eq0, ml);
+        mh_ = dev::and_or(hs1, eq1, mh_);
         if (KEEP != KEEP_NONE && j > (FULL ? GC_FROM : from)) {
           uint32_t *q = kept + (j - 1 - (FULL ? GC_FROM : from)) * KEEP;
           if (KEEP == KEEP_21) {
