@@ -281,9 +281,12 @@ __device__ __forceinline__ void walk_one(const Seqs &S, const Outs &O, const Sco
     int32_t c;
     const int32_t at = code_row<T, CMAX>(cs >> 2, o, last, c);
     const int32_t kp = k + par, q = (kp >> 1) + T * c / 2;
-    if (q < 1 || q >= T * c - 1) return -1;
+    if (q < 0 || q >= T * c) return -1;
     const uint32_t *row = codes + at;
-    const uint32_t v = row[q] >> (4 * (cs & 3)), u = row[(kp & 1) ? q + 1 : q - 1] >> (4 * (cs & 3));
+    // (the furthest diagonal that a stage reaches may lie in its first or last
+    // word; past those every source is absent)
+    const int32_t qn = (kp & 1) ? q + 1 : q - 1;
+    const uint32_t v = row[q] >> (4 * (cs & 3)), u = qn >= 0 && qn < T * c ? row[qn] >> (4 * (cs & 3)) : 0u;
     // the cell's own bits, and those of k + 1 and k - 1 as sources
     const uint32_t own = (kp & 1) ? v >> 16 : v;
     const uint32_t up = (kp & 1) ? u : v >> 16, dn = (kp & 1) ? v : u >> 16;

@@ -138,3 +138,27 @@ def test_small_batches_start_wide(ctx, alg, lmax):
     short = run(ctx, b, alg, AFF, max_len=lmax - 1)
     over = np.maximum(b.pat_len, b.txt_len) > lmax - 1
     assert (short[1][over] == aim.PAIR_INVALID).all() and (short[1][~over] == aim.PAIR_ALIGNED).all()
+
+
+@pytest.mark.parametrize("alg,pen", [("wfa", AFF), ("swg", AFF), ("wfa", (0, 3, 4, 1))])
+@pytest.mark.parametrize("lmax", [1021, 1533, 3069])
+def test_gap_alone_ends_at_a_stage_edge(ctx, alg, pen, lmax):
+    # one side empty (or a base or two) and the other as long as a stage's
+    # furthest diagonal: the whole alignment ends, and its walk starts, there
+    rng = np.random.default_rng(lmax)
+    base = lambda n: rng.integers(0, 4, n).astype(np.uint8)  # noqa: E731
+    pats, txts = [], []
+    for e in (253, 509, 765, 1021, 1533, 2045, 2557, 3069):
+        for n in range(e - 3, e + 4):
+            for m in (0, 1, 2):
+                if n <= lmax:
+                    pats += [base(m), base(n)]
+                    txts += [base(n), base(m)]
+    b = synth.from_lists(pats, txts)
+    for smax in (-1, 6 + 2 * (lmax - 1) if pen == AFF else 4 + lmax - 1):
+        want = oracle.wfa_batch(b, pen, smax)
+        got = run(ctx, b, alg, pen, smax)
+        failed = ctx.last_call_stats()["wfa_walk_failed"]
+        bad = compare(got, want)
+        assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
+        assert failed == 0
