@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64) void k_wfa_score16(Seqs S, Outs O, Scoring P, W
         }
         prog = wave_max_i32(prog);
         const int32_t ext = kend_out ? max(-kend, kend + 1) : W / 2 + 1;
-        if (lane == 0) route_pair(L.route, 0, p, predict_extent(ext, prog, m, n));
+        if (lane == 0) route_pair(O, L.route, 0, p, predict_extent(ext, prog, m, n));
       } else {
         wave_append1(true, (int32_t)p, L.ring_list, L.ring_count);
       }

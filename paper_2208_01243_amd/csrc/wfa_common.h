@@ -409,7 +409,13 @@ __device__ __forceinline__ int32_t predict_extent(int32_t ext, int32_t prog, int
 // Sends pair p, which left the window of class `from`, to the first later
 // class whose half-window holds `pred` (the last class takes any pair).
 // Called by one thread.
-__device__ __forceinline__ void route_pair(const WfaRoute &rt, int32_t from, int64_t p, int32_t pred) {
+__device__ __forceinline__ void route_pair(const Outs &O, const WfaRoute &rt, int32_t from, int64_t p, int32_t pred) {
+  if (from >= rt.nclass) {  // no plan lets a pair leave its last class: no list to write to
+    O.score[p] = -1;
+    O.status[p] = ST_INVALID;
+    O.nruns[p] = 0;
+    return;
+  }
   int c = from + 1;
   while (c < rt.nclass && rt.half[c] < pred) ++c;
   rt.pred[p] = pred;

@@ -409,7 +409,8 @@ __global__ __launch_bounds__(64, C == 4 ? 3 : 4) void k_wfa_group(WfaGroupArgs a
           const int32_t ad = gm > gn ? gm - gn : gn - gm;
           const bool rej = !lost && smax >= 0 && (s + 1 > smax || (ad > 0 && A->P.o + ad > smax));
           const bool bad = !lost && s + 1 > upper(A->P.o);  // cannot happen for exact WFA
-          const bool ends = rej || bad || (ADAPT && !lost && s >= A->L.s_cap);
+          // (and no plan lets a pair leave the last pass)
+          const bool ends = rej || bad || (ADAPT && !lost && s >= A->L.s_cap) || A->L.my_class >= A->L.route.nclass;
           const bool on = over && !ends;
           if (over && ends && gl == 0) {
             A->O.score[gp] = -1;

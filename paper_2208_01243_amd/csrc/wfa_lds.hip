@@ -538,7 +538,7 @@ __global__ __launch_bounds__(T) void k_wfa_lds(Seqs S, Outs O, Scoring P, Work W
         __syncthreads();
         pred = predict_extent(ext_out, __builtin_amdgcn_readfirstlane(shv[2]), m, n);
       }
-      if (tid == 0) route_pair(L.route, L.my_class, p, pred);
+      if (tid == 0) route_pair(O, L.route, L.my_class, p, pred);
       continue;
     }
     bool walked = false;

@@ -386,11 +386,15 @@ __global__ __launch_bounds__(T, 4) void k_wfa_wide(Seqs S, Outs O, Scoring P, Wo
       const int32_t ad = m > n ? m - n : n - m;
       const int32_t upper = min(x * min(m, n) + (ad ? P.o + ad : 0), (m ? P.o + m : 0) + (n ? P.o + n : 0));
       W.s_lim = min(P.max_score >= 0 ? min(P.max_score, upper) : upper, L.s_cap);
+      // the length difference alone passes the threshold: rejected before any
+      // score (such an end diagonal may lie outside the last window of a batch
+      // whose windows the threshold bounds)
+      const bool past = P.max_score >= 0 && ad > 0 && P.o + ad > P.max_score;
       W.s = 0;
       W.rowW = 0;
       W.rowX = (R - x) * NW;
       W.rowO = (R - oe) * NW;
-      W.result = 0;
+      W.result = past ? 2 : 0;
       W.keep = P.want_cigar != 0;
       W.coff = 0;
       W.stage = 1;
@@ -403,7 +407,7 @@ __global__ __launch_bounds__(T, 4) void k_wfa_wide(Seqs S, Outs O, Scoring P, Wo
         if (kend == 0 && f0 >= n) flag[0] = 1;
       }
       __syncthreads();
-      if (!out) {
+      if (!out && !past) {
         wide_stage<T, 1, NW>(W, x, oe, R, ring, edge, flag, pw, tw, codes + code_at0, L.pair_words);
         if constexpr (CMAX >= 2)
           if (!W.result) wide_stage<T, 2, NW>(W, x, oe, R, ring, edge, flag, pw, tw, codes + code_at0, L.pair_words);
@@ -420,7 +424,7 @@ __global__ __launch_bounds__(T, 4) void k_wfa_wide(Seqs S, Outs O, Scoring P, Wo
       const int32_t s = W.s;
       if (W.result == 2) {
         // past the last score to try
-        W.result = P.max_score >= 0 && s + 1 > P.max_score ? 2 : s + 1 > upper ? 4 : 3;
+        W.result = past || (P.max_score >= 0 && s + 1 > P.max_score) ? 2 : s + 1 > upper ? 4 : 3;
       }
       // codes not kept: a later class may have the room
       if (W.result == 1 && P.want_cigar && !W.keep && L.my_class < L.route.nclass) W.result = 3;
@@ -442,7 +446,7 @@ __global__ __launch_bounds__(T, 4) void k_wfa_wide(Seqs S, Outs O, Scoring P, Wo
         }
         __syncthreads();
         if (tid == 0)
-          route_pair(L.route, L.my_class, p, predict_extent(out ? max(-kend, kend + 1) : s - P.o + 1, flag[3], m, n));
+          route_pair(O, L.route, L.my_class, p, predict_extent(out ? max(-kend, kend + 1) : s - P.o + 1, flag[3], m, n));
       } else {
         const bool walk = W.result == 1 && W.keep;
         if (walk) {

@@ -215,3 +215,22 @@ def test_band_escalates_to_wavefronts(ctx, alg, pen):
         assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
     runs = np.diff(want[3])[k]
     assert np.array_equal(np.diff(got[3]), runs)
+
+
+@pytest.mark.parametrize("alg,pen,unit", [("wfa", AFF, 2), ("wfa_adaptive", AFF, 2), ("swg", AFF, 2), ("nw", (0, 1, 0, 1), 1)])
+def test_thresholds_without_filter(alg, pen, unit):
+    # no pre-alignment filter: pairs whose length difference passes the threshold
+    # reach the passes, at thresholds that end the plan at each of the windows
+    # (13, 29, 61, 125 and 253 diagonals each side)
+    with aim.Context(0, prefilter=False) as c:
+        for reach in (13, 29, 61, 125, 253):
+            rng = np.random.default_rng(reach)
+            T = [rng.integers(0, 4, int(n)).astype(np.uint8) for n in rng.integers(0, 300, 40)]
+            P = []
+            for k, t in enumerate(T):
+                gap = rng.integers(0, 4, max(0, reach - 3 + k % 7)).astype(np.uint8)
+                at = (0, len(t) // 2, len(t))[k % 3]
+                P.append(np.concatenate([t[:at], gap, t[at:]]) if k % 8 else rng.integers(0, 4, 3 * reach).astype(np.uint8))
+            b = synth.from_lists(P + T, T + P)
+            for smax in {unit * (reach + d + pen[2] // unit) for d in (-1, 0, 1)}:
+                check(c, b, alg, pen, smax)

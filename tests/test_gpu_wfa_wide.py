@@ -162,3 +162,40 @@ def test_gap_alone_ends_at_a_stage_edge(ctx, alg, pen, lmax):
         bad = compare(got, want)
         assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
         assert failed == 0
+
+
+def length_difference_pairs(seed, diffs, max_len):
+    """Pairs that differ by one gap of each length, with a few errors beside it
+    or none, and unrelated ones of the same lengths; one pair of max_len bases."""
+    rng = np.random.default_rng(seed)
+    base = lambda n: rng.integers(0, 4, n).astype(np.uint8)  # noqa: E731
+    pats, txts = [base(max_len)], [base(max_len)]
+    for d in diffs:
+        n = int(rng.integers(0, min(90, max_len - d) + 1))
+        T = base(n)
+        at = (0, n // 2, n)[int(rng.integers(3))]
+        P = np.concatenate([T[:at], base(d), T[at:]])
+        for a, b in ((P, T), (T, P), (_noisy(rng, P, 0.02)[:max_len], T), (base(n + d), T)):
+            pats.append(a)
+            txts.append(b)
+    return synth.from_lists(pats, txts)
+
+
+@pytest.mark.parametrize("alg", ["wfa", "swg"])
+@pytest.mark.parametrize("max_len,smax", [(762, 514), (800, 520), (2000, 1000), (2000, 2048), (2000, 2050),
+                                          (4095, 3000), (4095, 6144), (4095, 6146)])
+def test_thresholds_without_filter(alg, max_len, smax):
+    # no pre-alignment filter: the kernel itself rejects pairs whose length
+    # difference passes the threshold, also where the end lies outside the last
+    # window (1021 or 3069 diagonals) that the threshold leaves in the plan
+    reach = smax // 2 - 3
+    diffs = sorted({d for e in (253, 509, reach, 1021, 3069, max_len - 2) for d in range(e - 2, e + 3) if 0 < d <= max_len})
+    b = length_difference_pairs(max_len + smax, diffs, max_len)
+    want = oracle.wfa_batch(b, AFF, smax)
+    print("no filter: %s, %d pairs up to %d bp, threshold %d" % (alg, b.n, max_len, smax), flush=True)
+    with aim.Context(0, prefilter=False) as c:
+        got = run(c, b, alg, AFF, smax)
+        bad = compare(got, want)
+        assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
+        got = run(c, b, alg, AFF, smax, want_cigar=False)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
