@@ -650,26 +650,30 @@ __global__ __launch_bounds__(WGMAX) void k_wfa_trace(Seqs S, Outs O, Scoring P, 
       stage_seq(sT, gT, tnw);
     }
     // table of sfin + 1 entries at the start of the arena, data after it
+    // (what the score passes counted fits its class's slot; a re-run brings pairs
+    // of any store, and one that passes the slot gets no CIGAR)
     int32_t *tab = arena;
-    const int32_t data0 = (sfin + 1) * ENTRY;
-    if (lane == 0) sh_top = data0;
+    const int64_t data0 = ((int64_t)sfin + 1) * ENTRY;
+    bool lost = data0 + wf_words<E>(3) > slot_words;
+    if (lane == 0) sh_top = lost ? 0 : (int32_t)data0;
     __syncthreads();
     const int32_t *stab = ring ? tab_ring : tab;
     auto slot_of = [&](int32_t s2) { return ring ? s2 % R : s2; };
     // the forward steps, once per way of reading the sequences
     auto forward = [&](const auto &q) {
-    for (int32_t s = 0; s <= sfin; ++s) {
+    for (int32_t s = 0; s <= sfin && !lost; ++s) {
       const int32_t base = sh_top;
       int32_t lo = 0, hi = -1;
       int present;
-      bool overflow = false;
+      // the widest wavefront that the rest of the slot holds
+      const int32_t room = (int32_t)min<int64_t>((slot_words - base) * (4 / (int64_t)sizeof(E)) / 3, INT32_MAX);
       if (s == 0) {
         if (lane == 0) reinterpret_cast<E *>(arena + base)[0] = wf_put<E>(q.ext(m, n, 0, 0));
         present = 1;
         lo = hi = 0;
       } else {
-        present = wf_step<E>(s, x, oe, e, m, n, stab, arena, slot_of, arena, base, INT32_MAX, lo, hi,
-                             q, overflow);
+        present = wf_step<E>(s, x, oe, e, m, n, stab, arena, slot_of, arena, base, room, lo, hi,
+                             q, lost);
       }
       __syncthreads();
       if (lane == 0) {
@@ -694,7 +698,12 @@ __global__ __launch_bounds__(WGMAX) void k_wfa_trace(Seqs S, Outs O, Scoring P, 
     else
       forward(SeqInPlace{gP, gT, pnw, tnw});
     // ---- backtrace (one lane) ----
-    if (lane == 0) {
+    if (lost) {
+      if (lane == 0) {
+        O.status[p] = ST_OVERFLOW;
+        if (!Wk.direct) O.nruns[p] = 0;
+      }
+    } else if (lane == 0) {
       const int32_t total = Wk.direct ? O.nruns[p] : 0;
       uint32_t *dst = Wk.direct ? (O.cigar + O.cigar_off[p]) : nullptr;
       RunSink sink;

@@ -75,3 +75,24 @@ def test_runs_beyond_slot_and_pool_are_rerun():
         st = c.last_call_stats()
         assert st["cigar_reruns"] > 0, st
         assert st["wfa_long_failed"] == 0, st
+
+
+@pytest.mark.parametrize("limit", [16 << 20, 24 << 20])
+def test_rerun_without_room_for_the_long_pass(limit):
+    # too little scratch for a slot of the long pass: pairs whose runs outgrow
+    # their slot and the pool are re-run from a full store, and one whose store
+    # passes the largest slot is CIGAR_OVERFLOW with its score (it must not be
+    # written past the slot)
+    rng = np.random.default_rng(46)
+    b = _pairs(46, [(int(n), 0.1) for n in rng.permutation(np.linspace(900, 2500, 300))])
+    print("re-run under %d MiB" % (limit >> 20), flush=True)
+    with aim.Context(0, scratch_limit=limit, hard_limit=True) as c:
+        s, st, cg, off = run(c, b, "wfa", AFF)
+        stats = c.last_call_stats()
+    ws, wst, wc, wo = oracle.wfa_batch(b, AFF)
+    assert stats["cigar_reruns"] > 0 and stats["wfa_long_pairs"] == 0, stats
+    assert np.array_equal(s, ws)
+    lost = st == aim.PAIR_CIGAR_OVERFLOW
+    assert (st[~lost] == aim.PAIR_ALIGNED).all() and (~lost).sum() > 20 and lost.any()
+    for i in np.nonzero(~lost)[0]:
+        assert np.array_equal(cg[off[i]:off[i + 1]], wc[wo[i]:wo[i + 1]]), i
