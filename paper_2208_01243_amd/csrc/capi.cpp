@@ -426,13 +426,28 @@ bool band_by_wfa(const aim::Scoring &P, const Tune &tu, int64_t n, int32_t L) {
          wfa_group_fits(L, wfa_scoring(P)) && L <= 10240;
 }
 
+// The furthest diagonal that a pair of the batch can reach before it is
+// aligned or rejected, and the highest score it can take (unit gap extension: a
+// score reaches score - o; gap runs over both sequences bound the optimum, and so
+// do mismatches all along with a gap for the length difference, which cost the
+// most where the lengths are equal or differ by one).
+int32_t wfa_reach(const aim::Scoring &P, int32_t L) {
+  return P.max_score >= 0 ? std::min(L, std::max(0, P.max_score - P.o)) : L;
+}
+int32_t wfa_most_scores(const aim::Scoring &P, int32_t L) {
+  const int64_t diag = std::max((int64_t)P.x * L, (int64_t)P.x * (L - 1) + P.o + 1);
+  const int32_t most = (int32_t)std::min<int64_t>(2 * ((int64_t)P.o + L), diag);
+  return P.max_score >= 0 ? std::min(most, P.max_score) : most;
+}
+
 // Launch shape of one group pass over at most n pairs: workgroups by what a CU
 // holds (registers: 16 wavefronts, 12 at four words a lane), each with a ring of
-// origin codes of `steps` steps, fewer (but at least `least`) where that takes
-// more than `share` bytes, then fewer workgroups (a pair of more scores than
-// the ring holds goes to the next pass).
-aim_status wfa_group_plan(aim_context *c, int32_t L, const aim::Scoring &P, int64_t n, int32_t lanes, int32_t words,
-                          bool adaptive, int64_t steps, int64_t least, int64_t share, aim::WfaGroup &D) {
+// origin codes of `steps` steps, but no more than a group's share of the pairs can
+// take (at least `least`), fewer (at least `least`) where that takes more than
+// `share` bytes, then fewer workgroups (a pair of more scores than the ring holds
+// goes to the next pass).  Returns the bytes of codes; D.codes is the caller's.
+int64_t wfa_group_plan(const aim_context *c, int32_t L, const aim::Scoring &P, int64_t n, int32_t lanes, int32_t words,
+                       bool adaptive, int64_t steps, int64_t least, int64_t share, aim::WfaGroup &D) {
   D.R = std::max(P.x, P.o + 1) + 1;
   D.seq_words = (L + 31) / 32;
   D.s_cap = 16000;
@@ -444,18 +459,17 @@ aim_status wfa_group_plan(aim_context *c, int32_t L, const aim::Scoring &P, int6
   D.slot_words = 0;
   D.codes = nullptr;
   if (P.want_cigar) {
+    const int64_t pairs = (n + slots * groups - 1) / (slots * groups);
+    steps = std::min(steps, std::max(least, pairs * (wfa_most_scores(P, L) + 8)));
     int64_t as = 64;
     while (as < steps) as *= 2;
     while (as / 2 >= least && as * 64 * words * slots > share) as /= 2;
     slots = std::max<int64_t>(1, std::min<int64_t>(slots, share / (as * 64 * words)));
     D.as_steps = (int32_t)as;
     D.slot_words = as * 16 * words;
-    aim_status st = ensure(c, c->sc->wbits, (size_t)(slots * D.slot_words * 4));
-    if (st) return st;
-    D.codes = static_cast<uint32_t *>(c->sc->wbits.p);
   }
   D.nslots = (int32_t)slots;
-  return AIM_OK;
+  return slots * D.slot_words * 4;
 }
 
 aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
@@ -483,31 +497,19 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   // leaves those goes on to the kernel below, with every diagonal.
   // Long reads start in 64 lanes: theirs drift furthest (10,000 pairs of 10 kbp
   // at 5 % take 8.3 ms from 32 lanes on, 6.7 ms from 64).
-  aim::Work WG = Wk;
   const bool groups = wfa_group_fits(L, P) && c->ad_min <= 50 && c->ad_max <= 100;
+  aim::WfaGroup G[2];
+  int32_t lanes[2] = {64, 64};
+  int ng = 0;
+  int64_t group_bytes = 0;
   if (!Wk.direct && groups) {
-    const int32_t first = c->ad_max > 50 || L > 4096 ? 64 : L <= 192 ? 16 : 32;
-    int32_t *lists[2] = {as<int32_t>(c->sc->list2), as<int32_t>(c->sc->list3)};
-    int k = 0;
-    for (int32_t lanes = first; lanes <= 64; lanes = lanes < 64 ? 64 : 128, ++k) {
-      aim::WfaGroup G{};
-      aim_status st = wfa_group_plan(c, L, P, n, lanes, 1, true, std::max<int64_t>(2048, (int64_t)L * 3 / 4), 512,
-                                     c->limit() / 24, G);
-      if (st) return st;
-      G.route.nclass = 1;
-      G.route.list[1] = lists[k];
-      G.route.count[1] = cnt + C_GL + k;
-      G.walk_fail = cnt + C_WF;
-      G.ad_min = c->ad_min;
-      G.ad_max = c->ad_max;
-      G.ad_dropped = D.ad_dropped;
-      WG.counter = group_counter(cnt, k);
-      Phase ph(c, s, k == 0 ? "wfa_adaptive" : "wfa_adaptive_b");
-      HIP_TRY(aim::launch_wfa_group(S, O, P, WG, G, lanes, 1, true, s));
-      WG.idx = G.route.list[1];
-      WG.count = G.route.count[1];
+    lanes[0] = c->ad_max > 50 || L > 4096 ? 64 : L <= 192 ? 16 : 32;
+    ng = lanes[0] == 64 ? 1 : 2;
+    for (int k = 0; k < ng; ++k) {
+      G[k] = aim::WfaGroup{};
+      group_bytes = std::max(group_bytes, wfa_group_plan(c, L, P, n, lanes[k], 1, true, std::max<int64_t>(2048, (int64_t)L * 3 / 4),
+                                                         512, c->limit() / 24, G[k]));
     }
-    WG.counter = Wk.counter;
   }
   // the ring in LDS when a window of every diagonal is small (short reads:
   // no global round trips per score, and the walk's tokens in LDS too),
@@ -540,9 +542,28 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   }
   D.code_slot = ((int64_t)D.steps_cap * 12 + D.code_cap + 255) / 256 * 256;
   if (!lds_ring && (st = ensure(c, c->sc->wgring, (size_t)D.gring_slot * 4 * nslots))) return st;
-  if ((st = ensure(c, c->sc->wlds, std::max<size_t>((size_t)D.code_slot * nslots, 256)))) return st;
+  // (the passes run one after the other: one buffer of codes for all)
+  if ((st = ensure(c, c->sc->wlds, std::max<size_t>((size_t)std::max(group_bytes, D.code_slot * nslots), 256)))) return st;
   D.gring = lds_ring ? nullptr : as<uint32_t>(c->sc->wgring);
   D.codes = as<uint8_t>(c->sc->wlds);
+  aim::Work WG = Wk;
+  int32_t *lists[2] = {as<int32_t>(c->sc->list2), as<int32_t>(c->sc->list3)};
+  for (int k = 0; k < ng; ++k) {
+    G[k].codes = as<uint32_t>(c->sc->wlds);
+    G[k].route.nclass = 1;
+    G[k].route.list[1] = lists[k];
+    G[k].route.count[1] = cnt + C_GL + k;
+    G[k].walk_fail = cnt + C_WF;
+    G[k].ad_min = c->ad_min;
+    G[k].ad_max = c->ad_max;
+    G[k].ad_dropped = D.ad_dropped;
+    WG.counter = group_counter(cnt, k);
+    Phase ph(c, s, k == 0 ? "wfa_adaptive" : "wfa_adaptive_b");
+    HIP_TRY(aim::launch_wfa_group(S, O, P, WG, G[k], lanes[k], 1, true, s));
+    WG.idx = G[k].route.list[1];
+    WG.count = G[k].route.count[1];
+  }
+  WG.counter = Wk.counter;
   c->last_class_window[0] = D.W;
   Phase ph(c, s, Wk.direct ? "wfa_adaptive_rerun" : WG.idx != Wk.idx ? "wfa_adaptive_wide" : "wfa_adaptive");
   HIP_TRY(aim::launch_wfa_lds(S, O, P, WG, D, threads, nslots, s));
@@ -595,16 +616,6 @@ struct GroupPass {
   int32_t lanes, words;  // words of two diagonals a lane
   int32_t reach() const { return lanes * words - 3; }
 };
-// The furthest diagonal that a pair of the batch can reach before it is
-// aligned or rejected, and the highest score it can take (unit gap extension:
-// a score reaches score - o; gap runs over both sequences bound the optimum).
-int32_t wfa_reach(const aim::Scoring &P, int32_t L) {
-  return P.max_score >= 0 ? std::min(L, std::max(0, P.max_score - P.o)) : L;
-}
-int32_t wfa_most_scores(const aim::Scoring &P, int32_t L) {
-  const int32_t most = 2 * (P.o + L);
-  return P.max_score >= 0 ? std::min(most, P.max_score) : most;
-}
 // Where pairs start.  Too narrow a first pass is time spent twice, too wide a
 // one lanes without cells.  The reach expected of a batch is a sixth of its
 // reads' length under gap-affine penalties (5 % errors; a third in small
@@ -636,25 +647,35 @@ std::vector<GroupPass> wfa_group_passes(const aim::Scoring &P, int32_t L, bool s
 }
 constexpr int64_t WFA_RING_STEPS = 2048;  // steps of codes a wavefront keeps (more if a pair can need them)
 
-// The passes' launches over the listed pairs; pass k > 0 takes the pairs of
-// route class k.  G: what they share.
+// The passes' launch shapes, each with G (what they share) and its index in the
+// route; `bytes` grows to the codes of the largest.
+std::vector<aim::WfaGroup> plan_group_passes(const aim_context *c, const aim::Scoring &P, int64_t n, int32_t L,
+                                             const std::vector<GroupPass> &passes, int64_t least, int64_t share,
+                                             const aim::WfaGroup &G, int64_t &bytes) {
+  std::vector<aim::WfaGroup> plan(passes.size(), G);
+  for (size_t k = 0; k < passes.size(); ++k) {
+    bytes = std::max(bytes, wfa_group_plan(c, L, P, n, passes[k].lanes, passes[k].words, false,
+                                           std::max<int64_t>(WFA_RING_STEPS, least), least, share, plan[k]));
+    plan[k].my_class = (int32_t)k;
+  }
+  return plan;
+}
+// Their launches over the listed pairs, one after the other, with the call's
+// buffer of codes; pass k > 0 takes the pairs of route class k.
 aim_status launch_group_passes(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
-                               int32_t L, int32_t *cnt, const int32_t *order, const int32_t *order_count,
-                               const std::vector<GroupPass> &passes, int64_t least, int64_t share, aim::WfaGroup G,
-                               hipStream_t s) {
+                               int32_t *cnt, const int32_t *order, const int32_t *order_count,
+                               const std::vector<GroupPass> &passes, std::vector<aim::WfaGroup> &plan, hipStream_t s) {
   static const char *names[4] = {"wfa_score", "wfa_score_b", "wfa_score_c", "wfa_score_d"};
   for (size_t k = 0; k < passes.size(); ++k) {
-    const GroupPass &gp = passes[k];
-    aim_status st = wfa_group_plan(c, L, P, n, gp.lanes, gp.words, false, std::max<int64_t>(WFA_RING_STEPS, least), least, share, G);
-    if (st) return st;
-    G.my_class = (int32_t)k;
+    aim::WfaGroup &G = plan[k];
+    G.codes = as<uint32_t>(c->sc->wlds);
     aim::Work W{order, order_count, n, group_counter(cnt, (int)k), nullptr, nullptr, 0};
     if (k > 0) {
       W.idx = G.route.list[k];
       W.count = G.route.count[k];
     }
     Phase ph(c, s, names[k]);
-    HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, gp.lanes, gp.words, false, s));
+    HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, passes[k].lanes, passes[k].words, false, s));
   }
   if (!passes.empty()) c->last_window = 2 * passes[0].lanes * passes[0].words;
   return AIM_OK;
@@ -688,9 +709,14 @@ int32_t wide_tokens(int32_t L) { return 2 * (2 * L + 1) + 8; }
 bool wide_share_fits(const aim::Scoring &P, int32_t L, const WidePass &wp, int64_t share, int64_t slots) {
   return !P.want_cigar || share >= 4 * (wide_pair_words(P, L, wp) + wp.threads / 64 * wide_tokens(L)) * slots;
 }
-// Launch over the listed pairs; D: route, class index and fallback lists.
-aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n,
-                            int32_t L, const WidePass &wp, const aim::Work &W, aim::WfaWide D, int64_t share, hipStream_t s) {
+// Launch shape over at most n pairs; returns the bytes of codes and tokens.
+struct WidePlan {
+  aim::WfaWide D{};  // (route, class index, lists and codes: the caller's)
+  int32_t slots = 0;
+};
+int64_t wide_plan(const aim_context *c, const aim::Scoring &P, int64_t n, int32_t L, const WidePass &wp, int64_t share,
+                  WidePlan &plan) {
+  aim::WfaWide &D = plan.D;
   D.R = std::max(P.x, P.o + 1) + 1;
   D.seq_words = (L + 31) / 32;
   D.s_cap = 16000;
@@ -708,12 +734,15 @@ aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs 
     D.code_words = (int32_t)((words + 3) / 4 * 4);
     D.tok_cap = wide_tokens(L);
     D.slot_words = (D.code_words + tok + 3) / 4 * 4;
-    aim_status st = ensure(c, c->sc->wlds, (size_t)(slots * D.slot_words * 4));
-    if (st) return st;
-    D.codes = static_cast<uint32_t *>(c->sc->wlds.p);
   }
+  plan.slots = (int32_t)slots;
+  return slots * D.slot_words * 4;
+}
+aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P,
+                            const WidePass &wp, const aim::Work &W, WidePlan &plan, hipStream_t s) {
+  plan.D.codes = as<uint32_t>(c->sc->wlds);
   Phase ph(c, s, wp.threads == 256 ? "wfa_wide1" : "wfa_wide2");
-  HIP_TRY(aim::launch_wfa_wide(S, O, P, W, D, wp.threads, wp.words, (int32_t)slots, s));
+  HIP_TRY(aim::launch_wfa_wide(S, O, P, W, plan.D, wp.threads, wp.words, plan.slots, s));
   return AIM_OK;
 }
 
@@ -757,9 +786,16 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
   G.route.half[later] = INT32_MAX;
   G.route.pred = lists;
   done = true;
-  if ((st = launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, least, share, G, s))) return st;
+  // every pass planned before any is launched: they run one after the other, so
+  // that one buffer holds the codes of each
+  int64_t bytes = 256;
+  std::vector<aim::WfaGroup> group_plan = plan_group_passes(c, P, n, L, passes, least, share, G, bytes);
+  WidePlan wide[2];
+  for (int k = 0; k < nw; ++k) bytes = std::max(bytes, wide_plan(c, P, n, L, WIDE_PASS[k], wide_share, wide[k]));
+  if ((st = ensure(c, c->sc->wlds, (size_t)bytes))) return st;
+  if ((st = launch_group_passes(c, S, O, P, n, cnt, order, order_count, passes, group_plan, s))) return st;
   for (int k = 0; k < nw; ++k) {
-    aim::WfaWide D{};
+    aim::WfaWide &D = wide[k].D;
     D.route = G.route;
     D.my_class = ng + 1 + k;
     D.walk_fail = cnt + C_WF;
@@ -769,7 +805,7 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
       W.idx = order;
       W.count = order_count;
     }
-    if ((st = launch_wide_pass(c, S, O, P, n, L, WIDE_PASS[k], W, D, wide_share, s))) return st;
+    if ((st = launch_wide_pass(c, S, O, P, WIDE_PASS[k], W, wide[k], s))) return st;
   }
   return AIM_OK;
 }
@@ -917,52 +953,50 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     route.count[route.nclass] = cnt + C_RL;
     route.pred = lists + (int64_t)n * 10;
   }
-  if (group) {
-    aim::WfaGroup G{};
-    for (int k = 0; k < 4; ++k) {
-      G.need_cap[k] = WL.need_cap[k];
-      G.need_list[k] = WL.need_list[k];
-      G.need_count[k] = WL.need_count[k];
-      G.need_max[k] = WL.need_max[k];
-    }
-    G.need = WL.need;
-    G.walk_fail = WL.walk_fail;
-    G.long_list = WL.long_list;
-    G.long_count = WL.long_count;
-    G.route = route;
-    G.by_length = L > 1024;
-    if ((st = launch_group_passes(c, S, O, P, n, L, cnt, order, order_count, passes, 512, c->limit() / 8, G, s))) return st;
-  } else if (w16) {
-    const int32_t nslots16 = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * 28);
-    aim::WfaLaunch A = WL;
-    if (P.want_cigar) {
-      // origin codes for the fused walk: every score up to the threshold, at
-      // most WFA16_WALK_STEPS (pairs above go to the full-store pass)
-      // and within an eighth of the scratch budget
-      A.bits_steps = P.max_score >= 0 ? std::min(P.max_score + 1, aim::WFA16_WALK_STEPS)
-                                      : aim::WFA16_WALK_STEPS;
-      A.bits_steps = (int32_t)std::max<int64_t>(
-          1, std::min<int64_t>(A.bits_steps, c->limit() / 8 / ((int64_t)nslots16 * (C16 * 32 + 32))));
-      // rows of C16 x 32 bytes plus 32 bytes of padding
-      if ((st = ensure(c, c->sc->wbits, (size_t)nslots16 * A.bits_steps * (C16 * 32 + 32)))) return st;
-      A.bits = as<uint8_t>(c->sc->wbits);
-    }
-    A.route = route;
-    aim::Work W{order, order_count, n, cnt + C_W1, nullptr, nullptr, 0};
-    {
-      Phase ph(c, s, "wfa_score");
-      HIP_TRY(aim::launch_wfa_score16(S, O, P, W, A, C16, nslots16, s));
-    }
-    c->last_window = 64 * C16;
-  }
+  // Every pass's shape before any launch: the group passes, the wide ones and
+  // the LDS-window classes run one after the other on this stream, with their
+  // origin codes in one buffer and the classes' rings in another.
+  std::vector<aim::WfaGroup> group_plan;
+  std::vector<WidePlan> wide(cls.size());
+  std::vector<aim::WfaLds> LL(cls.size());
   if (w16) {
-    // the LDS-window classes, narrowest first; origin codes in one buffer
-    // the classes share (they run one after the other on this stream)
-    std::vector<aim::WfaLds> LL(cls.size());
-    size_t code_bytes = 0, ring_bytes = 0;
+    int64_t code_bytes = 0, ring_bytes = 0;
+    if (group) {
+      aim::WfaGroup G{};
+      for (int k = 0; k < 4; ++k) {
+        G.need_cap[k] = WL.need_cap[k];
+        G.need_list[k] = WL.need_list[k];
+        G.need_count[k] = WL.need_count[k];
+        G.need_max[k] = WL.need_max[k];
+      }
+      G.need = WL.need;
+      G.walk_fail = WL.walk_fail;
+      G.long_list = WL.long_list;
+      G.long_count = WL.long_count;
+      G.route = route;
+      G.by_length = L > 1024;
+      group_plan = plan_group_passes(c, P, n, L, passes, 512, c->limit() / 8, G, code_bytes);
+    }
     for (size_t k = 0; k < cls.size(); ++k) {
       aim::WfaLds &D = LL[k];
-      if (cls[k].wide >= 0) continue;
+      if (cls[k].wide >= 0) {
+        aim::WfaWide &W = wide[k].D;
+        code_bytes = std::max(code_bytes, wide_plan(c, P, n, L, WIDE_PASS[cls[k].wide], c->limit() / 3, wide[k]));
+        W.route = route;
+        W.my_class = ng + (int32_t)k + 1;
+        for (int q = 0; q < 4; ++q) {
+          W.need_cap[q] = WL.need_cap[q];
+          W.need_list[q] = WL.need_list[q];
+          W.need_count[q] = WL.need_count[q];
+          W.need_max[q] = WL.need_max[q];
+        }
+        W.need = WL.need;
+        W.long_list = WL.long_list;
+        W.long_count = WL.long_count;
+        W.walk_fail = WL.walk_fail;
+        W.walk_skip = WL.walk_skip;
+        continue;
+      }
       D.W = cls[k].W;
       D.MG = MG;
       D.R = pl.R;
@@ -989,7 +1023,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
                                                     64 << 10)
                                 : 0;
       D.code_slot = ((int64_t)D.steps_cap * 12 + D.code_cap + 255) / 256 * 256;
-      ring_bytes = std::max(ring_bytes, (size_t)D.gring_slot * 4 * cls[k].nslots);
+      ring_bytes = std::max(ring_bytes, D.gring_slot * 4 * cls[k].nslots);
       for (int q = 0; q < 4; ++q) {
         D.need_cap[q] = WL.need_cap[q];
         D.need_list[q] = WL.need_list[q];
@@ -1001,39 +1035,51 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       D.long_count = WL.long_count;
       D.walk_fail = WL.walk_fail;
       D.walk_skip = WL.walk_skip;
-      code_bytes = std::max(code_bytes, (size_t)D.code_slot * cls[k].nslots);
+      code_bytes = std::max(code_bytes, D.code_slot * cls[k].nslots);
     }
     for (size_t k = 0; k < cls.size() && k < 4; ++k) c->last_class_window[k] = cls[k].W;
-    if (!cls.empty()) {
-      if ((st = ensure(c, c->sc->wlds, std::max<size_t>(code_bytes, 256)))) return st;
-      if (ring_bytes && (st = ensure(c, c->sc->wgring, ring_bytes))) return st;
-      for (size_t k = 0; k < cls.size(); ++k) {
-        if (cls[k].wide >= 0) {
-          aim::WfaWide D{};
-          D.route = route;
-          D.my_class = ng + (int32_t)k + 1;
-          for (int q = 0; q < 4; ++q) {
-            D.need_cap[q] = WL.need_cap[q];
-            D.need_list[q] = WL.need_list[q];
-            D.need_count[q] = WL.need_count[q];
-            D.need_max[q] = WL.need_max[q];
-          }
-          D.need = WL.need;
-          D.long_list = WL.long_list;
-          D.long_count = WL.long_count;
-          D.walk_fail = WL.walk_fail;
-          D.walk_skip = WL.walk_skip;
-          const aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
-          if ((st = launch_wide_pass(c, S, O, P, n, L, WIDE_PASS[cls[k].wide], WC, D, c->limit() / 3, s))) return st;
-          continue;
-        }
-        LL[k].codes = as<uint8_t>(c->sc->wlds);
-        LL[k].gring = cls[k].global ? as<uint32_t>(c->sc->wgring) : nullptr;
-        aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
-        static const char *cls_names[4] = {"wfa_lds1", "wfa_lds2", "wfa_lds3", "wfa_lds4"};
-        Phase ph(c, s, cls_names[k]);
-        HIP_TRY(aim::launch_wfa_lds(S, O, P, WC, LL[k], cls[k].threads, cls[k].nslots, s));
+    if ((st = ensure(c, c->sc->wlds, (size_t)std::max<int64_t>(code_bytes, 256)))) return st;
+    if (ring_bytes && (st = ensure(c, c->sc->wgring, (size_t)ring_bytes))) return st;
+  }
+  if (group) {
+    if ((st = launch_group_passes(c, S, O, P, n, cnt, order, order_count, passes, group_plan, s))) return st;
+  } else if (w16) {
+    const int32_t nslots16 = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * 28);
+    aim::WfaLaunch A = WL;
+    if (P.want_cigar) {
+      // origin codes for the fused walk: every score up to the threshold, at
+      // most WFA16_WALK_STEPS (pairs above go to the full-store pass)
+      // and within an eighth of the scratch budget
+      A.bits_steps = P.max_score >= 0 ? std::min(P.max_score + 1, aim::WFA16_WALK_STEPS)
+                                      : aim::WFA16_WALK_STEPS;
+      A.bits_steps = (int32_t)std::max<int64_t>(
+          1, std::min<int64_t>(A.bits_steps, c->limit() / 8 / ((int64_t)nslots16 * (C16 * 32 + 32))));
+      // rows of C16 x 32 bytes plus 32 bytes of padding
+      if ((st = ensure(c, c->sc->wbits, (size_t)nslots16 * A.bits_steps * (C16 * 32 + 32)))) return st;
+      A.bits = as<uint8_t>(c->sc->wbits);
+    }
+    A.route = route;
+    aim::Work W{order, order_count, n, cnt + C_W1, nullptr, nullptr, 0};
+    {
+      Phase ph(c, s, "wfa_score");
+      HIP_TRY(aim::launch_wfa_score16(S, O, P, W, A, C16, nslots16, s));
+    }
+    c->last_window = 64 * C16;
+  }
+  if (w16) {
+    // the window classes, narrowest first
+    for (size_t k = 0; k < cls.size(); ++k) {
+      if (cls[k].wide >= 0) {
+        const aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
+        if ((st = launch_wide_pass(c, S, O, P, WIDE_PASS[cls[k].wide], WC, wide[k], s))) return st;
+        continue;
       }
+      LL[k].codes = as<uint8_t>(c->sc->wlds);
+      LL[k].gring = cls[k].global ? as<uint32_t>(c->sc->wgring) : nullptr;
+      aim::Work WC{route.list[ng + k + 1], route.count[ng + k + 1], n, cnt + C_CL + 4 + (int32_t)k, nullptr, nullptr, 0};
+      static const char *cls_names[4] = {"wfa_lds1", "wfa_lds2", "wfa_lds3", "wfa_lds4"};
+      Phase ph(c, s, cls_names[k]);
+      HIP_TRY(aim::launch_wfa_lds(S, O, P, WC, LL[k], cls[k].threads, cls[k].nslots, s));
     }
   } else if (!plain && pl.wcap_lds > 0) {
     aim::WfaLaunch A = WL;

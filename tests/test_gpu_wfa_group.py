@@ -234,3 +234,20 @@ def test_thresholds_without_filter(alg, pen, unit):
             b = synth.from_lists(P + T, T + P)
             for smax in {unit * (reach + d + pen[2] // unit) for d in (-1, 0, 1)}:
                 check(c, b, alg, pen, smax)
+
+
+@pytest.mark.parametrize("alg,pen,most", [("nw", (0, 1, 0, 1), 1), ("swg", AFF, 2), ("wfa", AFF, 2)])
+@pytest.mark.parametrize("n", [300, 1024])
+def test_small_batches_take_little_scratch(alg, pen, most, n):
+    # a new context's scratch after one small batch: a ring of codes for one pair
+    # in each wavefront of the widest pass (four words a lane, a step in 256
+    # bytes; a pair of edit distance takes at most its length in scores, a
+    # gap-affine one twice that), an eighth more for growth, and 32 MiB for the rest
+    rng = np.random.default_rng(n)
+    T = [rng.integers(0, 4, 150).astype(np.uint8) for _ in range(n)]
+    b = synth.from_lists([_noisy(rng, t, 0.03)[:150] for t in T], T)
+    steps = 1 << int(np.ceil(np.log2(most * (150 + 8) + 8)))
+    with aim.Context(0) as c:
+        run(c, b, alg, pen)
+        current, peak = c.scratch_usage()
+    assert current == peak <= n * steps * 256 * 9 // 8 + (32 << 20)
