@@ -746,6 +746,16 @@ aim_status launch_wide_pass(aim_context *c, const aim::Seqs &S, const aim::Outs 
   return AIM_OK;
 }
 
+// Arrays of n int32 that a call holds for its band tiers and its compaction and
+// that nothing else uses while wavefront passes of unit gap extension run over
+// the pairs of `order`.
+std::vector<int32_t *> free_lists(aim_context *c, int64_t n, const int32_t *order) {
+  std::vector<int32_t *> v = {as<int32_t>(c->sc->list3), as<int32_t>(c->sc->spill), as<int32_t>(c->sc->scan_tmp),
+                              as<int32_t>(c->sc->scan_tmp) + n};  // (scan_tmp: over n int64)
+  if (order != as<int32_t>(c->sc->list2)) v.push_back(as<int32_t>(c->sc->list2));
+  return v;
+}
+
 // Batches whose pairs all stay in the group and wide passes (reads of up to
 // 3,069 bp, or a low threshold): those passes alone, with no list, ring or store
 // of the others.  (A walk cannot fail on codes that were kept; if one did its
@@ -772,19 +782,23 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
   }
   aim_status st;
   const int32_t ng = (int32_t)passes.size() - 1, later = ng + nw;
-  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * (later + 1)))) return st;
-  int32_t *lists = as<int32_t>(c->sc->wlists);
+  // predicted extents, and a list for each later pass
+  std::vector<int32_t *> lists = free_lists(c, n, order);
+  if (const int32_t more = later + 1 - (int32_t)lists.size(); more > 0) {
+    if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * more))) return st;
+    for (int32_t k = 0; k < more; ++k) lists.push_back(as<int32_t>(c->sc->wlists) + (int64_t)n * k);
+  }
   aim::WfaGroup G{};
   G.walk_fail = cnt + C_WF;
   G.by_length = L > 1024;
   G.route.nclass = later;
   for (int32_t k = 1; k <= later; ++k) {
     G.route.half[k] = k <= ng ? passes[k].reach() : WIDE_PASS[k - ng - 1].reach();
-    G.route.list[k] = lists + (int64_t)n * k;
+    G.route.list[k] = lists[k];
     G.route.count[k] = k <= ng ? cnt + C_GL + k - 1 : cnt + C_CL + (k - ng - 1);
   }
   G.route.half[later] = INT32_MAX;
-  G.route.pred = lists;
+  G.route.pred = lists[0];
   done = true;
   // every pass planned before any is launched: they run one after the other, so
   // that one buffer holds the codes of each
@@ -839,10 +853,10 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   const aim::WfaPlan pl = aim::wfa_plan(L, P, c->limit(), c->cus, plain, tu.wfa_ring_kb,
                                         tu.wfa_trace_kb, tu.wfa_long_threads, c->strict());
   if ((st = ensure(c, c->sc->wneed, (size_t)n * 8))) return st;
-  // lists: [0] the HBM-ring pass, [1-4] full-store classes, [5] unused,
-  // [6-9] LDS-window classes, [10] predicted extents, [11] long pairs, [12-15]
-  // wider group passes
-  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * 16))) return st;
+  // lists: [0] the HBM-ring pass, [1-4] full-store classes, [5-7] window
+  // classes, [8] predicted extents, [9] long pairs (the wider group passes' lie in
+  // arrays that are free)
+  if ((st = ensure(c, c->sc->wlists, (size_t)n * 4 * 10))) return st;
   int32_t *lists = as<int32_t>(c->sc->wlists);
   aim::WfaLaunch WL{};
   WL.R = pl.R;
@@ -865,7 +879,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
   if (P.want_cigar && !plain) {
     if ((st = wfa_long_plan(c, L, P, pl, long_i16, LG, long_slots))) return st;
     if (long_slots > 0) {
-      WL.long_list = lists + (int64_t)n * 11;
+      WL.long_list = lists + (int64_t)n * 9;
       WL.long_count = cnt + C_LL;
       LG.failed = cnt + C_LF;
     }
@@ -935,23 +949,24 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     if (!cls.empty() && cls.back().W >= 2 * L + 2) cls.back().half = INT32_MAX;
   }
   aim::WfaRoute route{};
-  const int32_t ng = std::max<int32_t>(0, (int32_t)passes.size() - 1);
+  const int32_t ng = std::max<int32_t>(0, (int32_t)passes.size() - 1);  // (at most 3 here)
+  const std::vector<int32_t *> group_lists = free_lists(c, n, order);
   if (!plain && w16) {
     route.nclass = ng + (int32_t)cls.size() + 1;
     for (int32_t k = 0; k < ng; ++k) {
       route.half[k + 1] = passes[k + 1].reach();
-      route.list[k + 1] = lists + (int64_t)n * (12 + k);
+      route.list[k + 1] = group_lists[k];
       route.count[k + 1] = cnt + C_GL + k;
     }
     for (size_t k = 0; k < cls.size(); ++k) {
       route.half[ng + k + 1] = cls[k].half;
-      route.list[ng + k + 1] = lists + (int64_t)n * (6 + k);
+      route.list[ng + k + 1] = lists + (int64_t)n * (5 + k);
       route.count[ng + k + 1] = cnt + C_CL + (int32_t)k;
     }
     route.half[route.nclass] = INT32_MAX;
     route.list[route.nclass] = lists;  // the HBM-ring pass
     route.count[route.nclass] = cnt + C_RL;
-    route.pred = lists + (int64_t)n * 10;
+    route.pred = lists + (int64_t)n * 8;
   }
   // Every pass's shape before any launch: the group passes, the wide ones and
   // the LDS-window classes run one after the other on this stream, with their
@@ -1095,7 +1110,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
     aim::WfaLaunch B = WL;
     B.wcap = pl.wcap;
     B.slot_words = pl.ring_slot_words;
-    B.ring_list = lists + (int64_t)n * 5;  // never reached: wcap bounds every width
+    B.ring_list = as<int32_t>(c->sc->spill);  // never reached: wcap bounds every width
     B.ring_count = cnt + C_FAIL;
     const bool all = plain || (!w16 && pl.wcap_lds == 0);
     int32_t grid = all ? std::min<int32_t>(slots, pl.ring_slots) : pl.ring_slots;

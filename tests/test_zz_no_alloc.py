@@ -106,3 +106,26 @@ def test_static_entry_refuses_oversized_batch_then_still_works():
     want = oracle.align_batch(small, "swg", (0, 4, 6, 2), -1)
     bad = compare(got, want)
     assert not bad, describe(small, bad[0], got, want)
+
+
+@pytest.mark.parametrize("n,want_cigar", [(2_440_000, False), (165_000, True)])
+def test_static_entry_holds_many_pairs_of_a_long_bound(n, want_cigar):
+    # per pair the wavefront passes with every later class behind them hold ten
+    # lists, a count and the arrays that any call has: 85 bytes beside the plans'
+    # own share of the array, and 512 of run slots where CIGARs are wanted
+    rng = np.random.default_rng(1)
+    words = torch.from_numpy(rng.integers(0, 1 << 62, 2 * 4096)).cuda()
+    off = (torch.arange(n, device="cuda") % 4096) * 2
+    lens = torch.full((n,), 40, dtype=torch.int32, device="cuda")
+    score = torch.full((n,), 7, dtype=torch.int32, device="cuda")
+    status = torch.full((n,), 9, dtype=torch.int8, device="cuda")
+    cigar = torch.zeros(n, dtype=torch.int32, device="cuda")
+    coff = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    with aim.Context(0, static_scratch=True) as c:
+        c.align_batch_static(words, off, lens, words, off, lens, enc=aim.ENC_2BIT, max_len=9000, alg="wfa",
+                             pen=(0, 4, 6, 2), max_score=-1, score=score, status=status, cigar=cigar, cigar_off=coff,
+                             want_cigar=want_cigar)
+        torch.cuda.synchronize()
+    assert not score.any() and not status.any()
+    if want_cigar:
+        assert torch.equal(coff, torch.arange(n + 1, device="cuda")) and bool((cigar == 40 << 4).all())
