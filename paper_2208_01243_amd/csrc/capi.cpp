@@ -419,13 +419,6 @@ bool wfa_group_fits(int32_t L, const aim::Scoring &P) {
   return P.e == 1 && std::max(P.x, P.o + 1) <= 31 && L > 0 && L <= aim::WFA_GROUP_MAX_LEN;
 }
 
-// Whether a NW/SWG batch goes to the wavefront passes at once rather than
-// through the band tiers.
-bool band_by_wfa(const aim::Scoring &P, const Tune &tu, int64_t n, int32_t L) {
-  return tu.band_w0 == 32 && tu.band16 == 3 && (n < SPLIT_MIN_PAIRS || L > WFA_BAND_LEN) &&
-         wfa_group_fits(L, wfa_scoring(P)) && L <= 10240;
-}
-
 // The furthest diagonal that a pair of the batch can reach before it is
 // aligned or rejected, and the highest score it can take (unit gap extension: a
 // score reaches score - o; gap runs over both sequences bound the optimum, and so
@@ -645,6 +638,8 @@ std::vector<GroupPass> wfa_group_passes(const aim::Scoring &P, int32_t L, bool s
   }
   return passes;
 }
+// Batches whose wavefronts do not fill the chip.
+bool wfa_small(const aim_context *c, int64_t n) { return n <= (int64_t)c->cus * 16; }
 constexpr int64_t WFA_RING_STEPS = 2048;  // steps of codes a wavefront keeps (more if a pair can need them)
 
 // The passes' launch shapes, each with G (what they share) and its index in the
@@ -761,25 +756,39 @@ std::vector<int32_t *> free_lists(aim_context *c, int64_t n, const int32_t *orde
 // of the others.  (A walk cannot fail on codes that were kept; if one did its
 // pair would get CIGAR_OVERFLOW.)  `done` false: not such a batch, nothing
 // launched.  (No group passes: the wide ones take every pair.)
+struct ShortPlan {
+  bool fits = false;
+  int nw = 0;          // wide passes
+  int64_t least = 64;  // steps of codes: any pair's of a group pass
+  int64_t share, wide_share;  // bytes of codes
+};
+ShortPlan wfa_short_plan(const aim_context *c, const aim::Scoring &P, int64_t n, int32_t L, const std::vector<GroupPass> &passes) {
+  ShortPlan sp;
+  sp.share = c->limit() / 8;
+  sp.wide_share = c->limit() / 3;
+  const int32_t most = wfa_most_scores(P, L), reach = wfa_reach(P, L);
+  if (most > 16000) return sp;
+  for (int32_t r = passes.empty() ? 0 : passes.back().reach(); r < reach || sp.nw + passes.size() == 0; r = WIDE_PASS[sp.nw++].reach())
+    if (sp.nw == 2 || !wide_fits(P, L, WIDE_PASS[sp.nw])) return sp;
+  if (P.want_cigar) {
+    // in 16 workgroups at least (the other route would have no more)
+    const int64_t least_slots = std::min<int64_t>(n, 16);
+    if (!passes.empty()) sp.least = (sp.nw > 0 ? std::min(most, passes.back().reach() + P.o) : most) + 8;
+    for (const GroupPass &gp : passes)
+      if (sp.share < 2 * sp.least * 64 * gp.words * least_slots) return sp;
+    for (int k = 0; k < sp.nw; ++k)
+      if (!wide_share_fits(P, L, WIDE_PASS[k], sp.wide_share, least_slots)) return sp;
+  }
+  sp.fits = true;
+  return sp;
+}
 aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &P, int64_t n, int32_t L,
                          int32_t *cnt, const int32_t *order, const int32_t *order_count,
                          const std::vector<GroupPass> &passes, hipStream_t s, bool &done) {
-  done = false;
-  const int32_t most = wfa_most_scores(P, L), reach = wfa_reach(P, L);
-  if (most > 16000) return AIM_OK;
-  int nw = 0;
-  for (int32_t r = passes.empty() ? 0 : passes.back().reach(); r < reach || nw + passes.size() == 0; r = WIDE_PASS[nw++].reach())
-    if (nw == 2 || !wide_fits(P, L, WIDE_PASS[nw])) return AIM_OK;
-  const int64_t share = c->limit() / 8, wide_share = c->limit() / 3;
-  int64_t least = 64;  // steps of codes: any pair's of the pass
-  if (P.want_cigar) {
-    // in 64 workgroups at least
-    if (!passes.empty()) least = (nw > 0 ? std::min(most, passes.back().reach() + P.o) : most) + 8;
-    for (const GroupPass &gp : passes)
-      if (share < 2 * least * 64 * gp.words * std::min<int64_t>(n, 64)) return AIM_OK;
-    for (int k = 0; k < nw; ++k)
-      if (!wide_share_fits(P, L, WIDE_PASS[k], wide_share, std::min<int64_t>(n, 64))) return AIM_OK;
-  }
+  const ShortPlan sp = wfa_short_plan(c, P, n, L, passes);
+  const int nw = sp.nw;
+  done = sp.fits;
+  if (!done) return AIM_OK;
   aim_status st;
   const int32_t ng = (int32_t)passes.size() - 1, later = ng + nw;
   // predicted extents, and a list for each later pass
@@ -799,13 +808,12 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
   }
   G.route.half[later] = INT32_MAX;
   G.route.pred = lists[0];
-  done = true;
   // every pass planned before any is launched: they run one after the other, so
   // that one buffer holds the codes of each
   int64_t bytes = 256;
-  std::vector<aim::WfaGroup> group_plan = plan_group_passes(c, P, n, L, passes, least, share, G, bytes);
+  std::vector<aim::WfaGroup> group_plan = plan_group_passes(c, P, n, L, passes, sp.least, sp.share, G, bytes);
   WidePlan wide[2];
-  for (int k = 0; k < nw; ++k) bytes = std::max(bytes, wide_plan(c, P, n, L, WIDE_PASS[k], wide_share, wide[k]));
+  for (int k = 0; k < nw; ++k) bytes = std::max(bytes, wide_plan(c, P, n, L, WIDE_PASS[k], sp.wide_share, wide[k]));
   if ((st = ensure(c, c->sc->wlds, (size_t)bytes))) return st;
   if ((st = launch_group_passes(c, S, O, P, n, cnt, order, order_count, passes, group_plan, s))) return st;
   for (int k = 0; k < nw; ++k) {
@@ -824,12 +832,27 @@ aim_status run_wfa_short(aim_context *c, const aim::Seqs &S, const aim::Outs &O,
   return AIM_OK;
 }
 
+// Whether the pairs of a NW/SWG batch that the band does not take go to the
+// wavefront passes.  Reads of at most 256 bp have no other use for those in the
+// band tiers, whose scratch can be less than that of every later class: under a
+// hard limit and in the static entry they do where the short route takes them.
+bool band_to_wfa(const aim_context *c, const aim::Scoring &Pin, const Tune &wfa_tune, int64_t n, int32_t L) {
+  const aim::Scoring P = wfa_scoring(Pin);
+  if (!wfa_group_fits(L, P) || L > 10240) return false;
+  return L > 256 || !(c->strict() || c->arena) ||
+         wfa_short_plan(c, P, n, L, wfa_group_passes(P, L, wfa_small(c, n), wfa_tune)).fits;
+}
+// Whether all of them do, at once.
+bool band_by_wfa(const aim_context *c, const aim::Scoring &P, const Tune &tu, const Tune &wfa_tune, int64_t n, int32_t L) {
+  return tu.band_w0 == 32 && tu.band16 == 3 && (n < SPLIT_MIN_PAIRS || L > WFA_BAND_LEN) && band_to_wfa(c, P, wfa_tune, n, L);
+}
+
 aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                    int64_t n, int32_t L, bool plain, int32_t *cnt, const int32_t *order,
                    const int32_t *order_count, const Tune &tu, hipStream_t s) {
   aim_status st;
   const aim::Scoring P = wfa_scoring(Pin);
-  const bool small = n <= (int64_t)c->cus * 16;
+  const bool small = wfa_small(c, n);
   const bool group = !plain && wfa_group_fits(L, P) && L <= 10240;
   std::vector<GroupPass> passes;
   if (group) {
@@ -1377,10 +1400,22 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
   aim::Scoring P{pen.mismatch, alg == AIM_NW_LINEAR ? 0 : pen.gap_open, pen.gap_extend, max_score,
                  R->want_cigar ? 1 : 0};
 
+  const bool plain = c->opt.kernel == AIM_KERNEL_PLAIN;
+  const Tune tu = tune_for(c, alg, L);
+  // the wavefront passes' part in a NW/SWG batch: all its pairs, or those that
+  // leave the first band (no narrow ones, which start in 64 lanes)
+  const bool band = alg == AIM_NW_LINEAR || alg == AIM_SWG_AFFINE;
+  const Tune tune_all = tune_for(c, AIM_WFA_AFFINE, L);
+  Tune tune_left = tune_all;
+  if (tune_left.wfa_c16 == 0) tune_left.wfa_c16 = 1;
+  const bool all_wfa = band && !plain && band_by_wfa(c, P, tu, tune_all, n, L);
+  const bool left_wfa = band && !plain && band_to_wfa(c, P, tune_left, n, L);
+
   // ---- common scratch ----
   const size_t tmp = aim::scan_tmp_elems(n) + (size_t)n + 2;
   if ((st = ensure(c, c->sc->scan_tmp, tmp * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, c->sc->counters, C_ALL * sizeof(int32_t)))) return st;
+  const int32_t counters = all_wfa || left_wfa || alg == AIM_WFA_AFFINE || alg == AIM_WFA_ADAPTIVE ? C_ALL : C_GQ;
+  if ((st = ensure(c, c->sc->counters, counters * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->sc->total, 64))) return st;
   if ((st = ensure(c, c->sc->nruns, (size_t)n * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->sc->spill, (size_t)n * sizeof(int32_t)))) return st;
@@ -1408,11 +1443,10 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
   // ---- input encoding ----
   aim::Seqs S;
   if ((st = ensure(c, c->sc->pooloff, (size_t)n * 8))) return st;
-  const Tune tu = tune_for(c, alg, L);
   const bool do_sort = (tu.sort >= 0 ? tu.sort != 0 : (alg != AIM_NW_LINEAR && alg != AIM_SWG_AFFINE) || L >= 512) &&
                        c->opt.kernel != AIM_KERNEL_PLAIN;
   // counters, the CIGAR total and the pool's top, and the length buckets
-  aim::ZeroSpans Z{{cnt, as<int32_t>(c->sc->total), nullptr}, {C_ALL, 4, 0}};
+  aim::ZeroSpans Z{{cnt, as<int32_t>(c->sc->total), nullptr}, {counters, 4, 0}};
   if (do_sort) {
     if ((st = ensure(c, c->sc->hist, 2 * aim::LEN_BUCKETS * 4))) return st;
     Z.p[2] = as<int32_t>(c->sc->hist);
@@ -1443,7 +1477,6 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
               as<int8_t>(c->sc->flags), R->cigar, R->cigar_off, R->cigar_cap, as<uint32_t>(c->sc->pool),
               pool_cap, (unsigned long long *)(as<int64_t>(c->sc->total) + 1), as<int64_t>(c->sc->pooloff)};
   const int64_t budget = c->limit() / 4;
-  const bool plain = c->opt.kernel == AIM_KERNEL_PLAIN;
 
   // exact pre-alignment filter: with a threshold, pairs whose lower bound
   // already exceeds it are finished here and the aligners take the rest (in
@@ -1483,10 +1516,10 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     if ((st = run_wfa_adaptive(c, S, O, P, n, L, cnt, WA, tu, s))) return st;
   } else if (alg == AIM_WFA_AFFINE) {
     if ((st = run_wfa(c, S, O, P, n, L, plain, cnt, order, order_count, tu, s))) return st;
-  } else if (!plain && band_by_wfa(P, tu, n, L)) {
+  } else if (all_wfa) {
     // small batches: the wavefront algorithm reaches the same optimum and, with
     // the same tie order, the same CIGAR
-    if ((st = run_wfa(c, S, O, P, n, L, false, cnt, order, order_count, tune_for(c, AIM_WFA_AFFINE, L), s))) return st;
+    if ((st = run_wfa(c, S, O, P, n, L, false, cnt, order, order_count, tune_all, s))) return st;
   } else if (plain) {
     aim::Work W1{nullptr, nullptr, n, cnt + C_T1, nullptr, nullptr, 0};
     if ((st = run_full(W1, n, s))) return st;
@@ -1537,8 +1570,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     // pairs that left the 32 diagonals go to the wavefront passes where those
     // have their narrow kernels (1,000,000 x 150 bp affine at 8 %, most of them
     // escalated: 8 ms against 50 through the 64-diagonal band)
-    const bool by_wfa = wfa_group_fits(L, wfa_scoring(P)) && L <= 10240;
-    if (w0 == 32 && !by_wfa) {
+    if (w0 == 32 && !left_wfa) {
       // tier 2: 64-diagonal band for the pairs tier 1 could not decide, one
       // pair per 32 lanes along the anti-diagonal, then a walk per lane
       const int64_t cw = aim::diag_chunk_words(affine, L);
@@ -1577,10 +1609,8 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     // with m x n; the full matrix for short reads (one launch instead of the
     // wavefront passes' six, which small batches notice) and for penalties
     // beyond the wavefront ring's reach
-    if (by_wfa || (L > 256 && P.x <= WFA_MAX_STEP && P.o + P.e <= WFA_MAX_STEP)) {
-      Tune tw = tune_for(c, AIM_WFA_AFFINE, L);
-      if (by_wfa && tw.wfa_c16 == 0) tw.wfa_c16 = 1;  // they are no narrow pairs
-      if ((st = run_wfa(c, S, O, P, n, L, false, cnt, full_list, full_count, tw, s))) return st;
+    if (left_wfa || (L > 256 && P.x <= WFA_MAX_STEP && P.o + P.e <= WFA_MAX_STEP)) {
+      if ((st = run_wfa(c, S, O, P, n, L, false, cnt, full_list, full_count, left_wfa ? tune_left : tune_all, s))) return st;
     } else {
       aim::Work W3{full_list, full_count, n, cnt + C_T3, nullptr, nullptr, 0};
       if ((st = run_full(W3, n, s))) return st;

@@ -251,3 +251,21 @@ def test_small_batches_take_little_scratch(alg, pen, most, n):
         run(c, b, alg, pen)
         current, peak = c.scratch_usage()
     assert current == peak <= n * steps * 256 * 9 // 8 + (32 << 20)
+
+
+@pytest.mark.parametrize("alg,pen,L", [("nw", (0, 1, 0, 1), 150), ("swg", AFF, 100), ("swg", AFF, 150)])
+def test_large_band_batch_under_a_hard_limit(alg, pen, L):
+    # 70,000 pairs in 64 MiB of scratch: room for the band tiers, but not for the
+    # wavefront passes with every later class behind them
+    rng = np.random.default_rng(L)
+    T = [rng.integers(0, 4, L).astype(np.uint8) for _ in range(500)]
+    uniq = synth.from_lists([_noisy(rng, t, float(rng.choice([0.01, 0.15])))[:L] for t in T], T)
+    k = np.arange(70_000) % uniq.n
+    want = oracle.align_batch(uniq, alg, pen)
+    with aim.Context(0, scratch_limit=64 << 20, hard_limit=True) as c:
+        got = run(c, uniq.subset(k), alg, pen)
+        assert c.last_call_stats()["band_escalated"] > 0
+    assert np.array_equal(got[0], want[0][k]) and np.array_equal(got[1], want[1][k])
+    assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
+    for i in range(0, len(k), 41):
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
