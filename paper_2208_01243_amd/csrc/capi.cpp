@@ -348,6 +348,28 @@ struct Phase {
   }
 };
 
+// Work on the context's second stream from open() to join(), which every way out
+// of the call makes: a call that is refused on the way (scratch past a hard limit)
+// has launched work there that the context's next call must wait for.
+struct Fork {
+  aim_context *c;
+  hipStream_t s;
+  bool open_ = false;
+  hipError_t open() {
+    hipError_t e = hipEventRecord(c->ev_fork, s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(c->aux, c->ev_fork, 0);
+    open_ = e == hipSuccess;
+    return e;
+  }
+  hipError_t join() {
+    if (!open_) return hipSuccess;
+    open_ = false;
+    const hipError_t e = hipEventRecord(c->ev_join, c->aux);
+    return e == hipSuccess ? hipStreamWaitEvent(s, c->ev_join, 0) : e;
+  }
+  ~Fork() { (void)join(); }
+};
+
 constexpr int32_t MAX_LEN_LIMIT = 1 << 20;
 constexpr int32_t SLOT_CAP = 128;  // at most this many runs per pair held before compaction
 
@@ -1561,10 +1583,8 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
     // `s` right behind the fill: their few long-running wavefronts are then
     // dispatched first and hold their slots while the traceback takes the rest.
     hipStream_t s2 = c->aux;
-    if (split) {
-      HIP_TRY(hipEventRecord(c->ev_fork, s));
-      HIP_TRY(hipStreamWaitEvent(s2, c->ev_fork, 0));
-    }
+    Fork fork{c, s};
+    if (split) HIP_TRY(fork.open());
     int32_t *full_list = as<int32_t>(c->sc->list2);
     int32_t *full_count = cnt + C_L2;
     // pairs that left the 32 diagonals go to the wavefront passes where those
@@ -1615,10 +1635,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
       aim::Work W3{full_list, full_count, n, cnt + C_T3, nullptr, nullptr, 0};
       if ((st = run_full(W3, n, s))) return st;
     }
-    if (split) {
-      HIP_TRY(hipEventRecord(c->ev_join, s2));
-      HIP_TRY(hipStreamWaitEvent(s, c->ev_join, 0));
-    }
+    HIP_TRY(fork.join());
   }
 
   if (!R->want_cigar) {

@@ -276,6 +276,37 @@ def test_hard_scratch_limit():
         assert hc.scratch_usage()[1] <= 64 << 20
 
 
+def test_refused_on_the_way_then_retried():
+    # limits that end a two-stream batch at one tier after another (the first
+    # tier's walk may be running on the second stream then): the smaller batch
+    # behind it, with no wait between them, is right in scores and CIGARs where it
+    # is taken
+    big = synth.workload("swg150", n=70_000)
+    small = synth.workload("swg150", start=70_000, n=3000)
+    dev, enc = to_device(big, "2bit")
+    want = oracle.align_batch(small, "swg", (0, 4, 6, 2), -1)
+    refused = taken = 0
+    for mib in range(40, 68, 2):
+        print("hard limit %d MiB" % mib, flush=True)
+        outs = _outputs(big)
+        with aim.Context(0, scratch_limit=mib << 20, hard_limit=True) as hc:
+            try:
+                hc.align_batch(*dev, enc=enc, max_len=200, alg="swg", pen=(0, 4, 6, 2), max_score=-1, score=outs[0],
+                               status=outs[1], cigar=outs[2], cigar_off=outs[3])
+            except aim.AimError as e:
+                assert e.code == -3
+                refused += 1
+            try:
+                got = run(hc, small, "swg", (0, 4, 6, 2), -1)
+            except aim.AimError as e:
+                assert e.code == -3
+                continue
+            bad = compare(got, want)
+            assert not bad, (mib, bad[:5])
+            taken += 1
+    assert refused and taken
+
+
 def test_autotune_wfa_mixed_per_bucket(tmp_path):
     # one mixed batch (100 bp - 10 kbp): the tuner keeps a batch tune and a
     # tune per window-class length bucket; the tuned calls return exactly what
