@@ -160,9 +160,9 @@ typedef struct {
    * memory the context's scratch holds never exceeds it (launch plans are
    * then sized for half of it, 3/8 below 1 GiB, the rest holding the arrays
    * that grow with the batch): a call that would need more fails with
-   * AIM_ERR_OOM (its outputs
-   * are then unspecified), and a smaller batch can be retried on the same
-   * context. */
+   * AIM_ERR_OOM (its outputs are then unspecified), and the context gives back
+   * all its scratch, so that a smaller batch can be retried on it (graphs captured
+   * from it have to be captured again). */
   int64_t scratch_limit;
 } aim_options;
 

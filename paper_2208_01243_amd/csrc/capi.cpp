@@ -122,6 +122,13 @@ struct Scratch {
       wbits, wwalk, wlds, wgring, flist, wlong;
 };
 
+std::vector<Buf *> all_buffers(Scratch &s) {
+  return {&s.order, &s.hist, &s.flags, &s.pflag, &s.tflag, &s.pat2, &s.txt2, &s.pat2off, &s.txt2off, &s.nruns, &s.slot,
+          &s.tb32, &s.tb64, &s.full, &s.list2, &s.list3, &s.counters, &s.scan_tmp, &s.spill, &s.total, &s.wring, &s.warena1,
+          &s.warena2, &s.warena3, &s.wneed, &s.wlists, &s.pool, &s.pooloff, &s.wbits, &s.wwalk, &s.wlds, &s.wgring, &s.flist,
+          &s.wlong};
+}
+
 struct aim_graph {
   aim_context *c = nullptr;  // nullptr once the context is destroyed
   int32_t device = 0;
@@ -255,6 +262,26 @@ aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
   c->dev_bytes += (int64_t)want;
   c->dev_peak = std::max(c->dev_peak, c->dev_bytes);
   return AIM_OK;
+}
+
+// Gives back all scratch behind the work on `s` (a call was refused for want of
+// it): what the call and those before it held may leave no room for the smaller
+// batch that is tried next.  The error message stays.
+void release_scratch(aim_context *c, hipStream_t s) {
+  bool waited = false;
+  for (Buf *b : all_buffers(c->own)) {
+    if (!b->p) continue;
+    if (!b->pooled && !waited) {
+      (void)hipDeviceSynchronize();
+      waited = true;
+    }
+    (void)(b->pooled ? hipFreeAsync(b->p, s) : hipFree(b->p));
+    *b = Buf{};
+  }
+  c->dev_bytes = 0;
+  c->generation += 1;
+  c->last_cnt = nullptr;
+  c->last_n = 0;
 }
 
 template <class T>
@@ -1302,11 +1329,7 @@ void aim_destroy(aim_context *c) {
   for (aim_graph *gr : c->graphs) gr->c = nullptr;  // their launches now fail; destroy still frees them
   c->graphs.clear();
   (void)hipDeviceSynchronize();
-  Buf *all[] = {&c->own.order, &c->own.hist, &c->own.flags, &c->own.pflag, &c->own.tflag, &c->own.pat2, &c->own.txt2, &c->own.pat2off, &c->own.txt2off,
-                &c->own.nruns, &c->own.slot, &c->own.tb32, &c->own.tb64, &c->own.full, &c->own.list2, &c->own.list3,
-                &c->own.counters, &c->own.scan_tmp, &c->own.spill, &c->own.total, &c->own.wring, &c->own.warena1,
-                &c->own.warena2, &c->own.warena3, &c->own.wneed, &c->own.wlists, &c->own.pool, &c->own.pooloff, &c->own.wbits, &c->own.wwalk, &c->own.wlds, &c->own.wgring, &c->own.flist,
-                &c->own.wlong};
+  const auto all = all_buffers(c->own);
   for (Buf *b : all)
     if (b->p) clear_scratch(*b, c->aux);
   (void)hipStreamSynchronize(c->aux);
@@ -1696,6 +1719,7 @@ aim_status aim_align_batch(aim_context *c, const aim_batch *B, int32_t alg, aim_
   if (c->has_done && c->done_stream != s) HIP_TRY(hipStreamWaitEvent(s, c->ev_done, 0));
   c->astream = s;
   const aim_status st = align_batch(c, B, alg, pen, max_score, R, stream);
+  if (st == AIM_ERR_OOM) release_scratch(c, s);
   c->astream = nullptr;
   HIP_TRY(hipEventRecord(c->ev_done, s));
   c->has_done = true;

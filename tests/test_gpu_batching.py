@@ -307,6 +307,30 @@ def test_refused_on_the_way_then_retried():
     assert refused and taken
 
 
+@pytest.mark.parametrize("alg", ["swg", "wfa"])
+def test_smaller_batch_after_a_refused_one(alg):
+    # whatever the refused batch (or one before it) held of the limit, a batch that
+    # a new context takes is taken after it
+    big = synth.workload("swg150", n=70_000)
+    small = synth.workload("swg150", start=70_000, n=3000)
+    want = oracle.align_batch(small, alg, (0, 4, 6, 2), -1)
+    refused = 0
+    for mib in range(16, 68, 4):
+        with aim.Context(0, scratch_limit=mib << 20, hard_limit=True) as hc:
+            run(hc, small, "nw", (0, 1, 0, 1), -1)
+            try:
+                run(hc, big, alg, (0, 4, 6, 2), -1)
+            except aim.AimError as e:
+                assert e.code == -3
+                refused += 1
+                assert hc.scratch_usage()[0] == 0
+                assert hc.last_call_stats()["n_pairs"] == 0
+                bad = compare(run(hc, small, alg, (0, 4, 6, 2), -1), want)
+                assert not bad, (mib, bad[:5])
+            assert hc.scratch_usage()[1] <= mib << 20
+    assert refused
+
+
 def test_autotune_wfa_mixed_per_bucket(tmp_path):
     # one mixed batch (100 bp - 10 kbp): the tuner keeps a batch tune and a
     # tune per window-class length bucket; the tuned calls return exactly what
