@@ -305,7 +305,8 @@ enum Counter {
   C_W1, C_W1G, C_RL, C_FAIL, C_N0, C_N1, C_N2, C_N3, C_P0, C_P1, C_P2, C_P3, C_TB, C_DTB,
   C_M0, C_M1, C_M2, C_M3, C_WF, C_WS, C_FL, C_FR, C_LL, C_LW, C_LF,
   C_CL = 32,  // WFA window classes 1..4: list lengths, then their work counters (C_CL + 4)
-  C_GL = 40,  // WFA group passes: pairs passed on
+  C_GL = 40,  // WFA group passes: pairs passed on (at most 4)
+  C_AL = 44, C_ALW, C_AL2, C_AL2W,  // WFA-adaptive pairs past the first shape's slots, and of a re-run
   C_N = 48,   // (then the 64-bit adaptive drop count)
   C_GQ = 64,  // work counters of up to four WFA group passes
   C_ALL = C_GQ + 4 * aim::WFA_GROUP_COUNTERS
@@ -559,35 +560,51 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   const bool lds_ring = aim::wfa_lds_bytes(D.W, D.MG, D.R, P.e, D.seq_words, false) <= 24 * 1024;
   const size_t lds = aim::wfa_lds_bytes(D.W, D.MG, D.R, P.e, D.seq_words, !lds_ring);
   if (lds > 160 * 1024) return fail(AIM_ERR_UNSUPPORTED, "WFA-adaptive: sequences too long to stage");
-  // behind the groups a pair or none comes here: a workgroup for each SIMD, for
-  // with all that fit the slots take 20-30 GB, whose return costs 0.7 s
-  const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds, groups ? 4 : 2048 / threads));
-  int32_t nslots = (int32_t)std::min<int64_t>(n, (int64_t)c->cus * per_cu);
-  // per workgroup slot: the ring (with its guard word) and, with CIGARs, the
-  // score table and the origin codes of every kept score, within 5/16 of
-  // the budget each way (fewer workgroups when they do not fit)
+  // Two shapes.  The first, 24 wavefronts a CU behind the groups, has slots (the
+  // ring with its guard word, and with CIGARs the score table and the origin codes
+  // of every kept score) whose codes take an eighth of the budget together, at
+  // least 256 KiB each.  Where that is less than any pair can need, up to 4 MiB, a
+  // second shape of a wavefront for each SIMD takes the pairs that outgrow it, with
+  // 5/16 of the budget (a pair needing more gets no CIGAR).  With every slot at
+  // its largest the first took 20-30 GB, whose return costs 0.7 s.  A pair or none
+  // comes here at max_dist 50 and some per cent of errors, but with four
+  // wavefronts a CU alone 200,000 unrelated pairs of 150 bp took 100 ms instead of
+  // 34, and 50,000 of 1 kbp at 20 % with max_dist 100 72 instead of 24 (8, 12 and
+  // 16 a CU: 40, 30 and 26; 32: no faster).
+  const int64_t per_cu = (int64_t)std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds, (groups ? 1536 : 2048) / threads));
   D.gring_slot = lds_ring ? 0 : (aim::wfa_ring_words(D.W, D.MG, D.R, P.e) + 1 + 63) / 64 * 64;
-  const int64_t share = c->limit() * 5 / 16;
-  if (!lds_ring) nslots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nslots, share / (D.gring_slot * 4)));
   // scores kept: up to what any alignment of the batch can cost (2 L ops at
   // the dearest step), at most s_cap; codes: up to the widest row at every
-  // kept score, at most 4 MiB per slot (a pair needing more gets no CIGAR)
+  // kept score
   // (gap runs over both sequences bound every score)
   const int64_t steps =
       std::min<int64_t>(D.s_cap, std::min<int64_t>(2 * (int64_t)L * std::max(P.x, P.o + P.e), 2 * ((int64_t)P.o + (int64_t)L * P.e)) + 1) + 1;
+  const int64_t most = std::min<int64_t>(steps * (D.W / 2 + 1), (int64_t)4 << 20);
   D.steps_cap = P.want_cigar ? (int32_t)steps : 0;
-  if (P.want_cigar) {
-    const int64_t fixed = (int64_t)D.steps_cap * 12;
-    nslots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nslots, share / (fixed + (256 << 10))));
-    const int64_t most = std::min<int64_t>(steps * (D.W / 2 + 1), (int64_t)4 << 20);
-    D.code_cap = std::min<int64_t>(most, std::max<int64_t>(share / nslots - fixed, 256 << 10));
+  aim::WfaLds shape[2] = {D, D};
+  int32_t nslots[2];
+  int64_t code_bytes = std::max<int64_t>(group_bytes, 256), ring_bytes = 0;
+  int shapes = 0;
+  for (bool all = false; !all; ++shapes) {
+    aim::WfaLds &F = shape[shapes];
+    const int64_t share = c->limit() * 5 / 16, code_share = shapes == 0 && groups ? c->limit() / 8 : share;
+    int64_t slots = std::min<int64_t>(n, c->cus * (shapes == 0 ? per_cu : std::min<int64_t>(per_cu, 4)));
+    // (fewer workgroups when rings or codes do not fit)
+    if (!lds_ring) slots = std::max<int64_t>(1, std::min(slots, share / (F.gring_slot * 4)));
+    if (P.want_cigar) {
+      const int64_t fixed = (int64_t)F.steps_cap * 12;
+      slots = std::max<int64_t>(1, std::min(slots, code_share / (fixed + (256 << 10))));
+      F.code_cap = std::min<int64_t>(most, std::max<int64_t>(code_share / slots - fixed, 256 << 10));
+    }
+    F.code_slot = ((int64_t)F.steps_cap * 12 + F.code_cap + 255) / 256 * 256;
+    all = shapes == 1 || !P.want_cigar || F.code_cap == most;
+    nslots[shapes] = (int32_t)slots;
+    code_bytes = std::max(code_bytes, F.code_slot * slots);
+    ring_bytes = std::max(ring_bytes, F.gring_slot * 4 * slots);
   }
-  D.code_slot = ((int64_t)D.steps_cap * 12 + D.code_cap + 255) / 256 * 256;
-  if (!lds_ring && (st = ensure(c, c->sc->wgring, (size_t)D.gring_slot * 4 * nslots))) return st;
+  if (ring_bytes && (st = ensure(c, c->sc->wgring, (size_t)ring_bytes))) return st;
   // (the passes run one after the other: one buffer of codes for all)
-  if ((st = ensure(c, c->sc->wlds, std::max<size_t>((size_t)std::max(group_bytes, D.code_slot * nslots), 256)))) return st;
-  D.gring = lds_ring ? nullptr : as<uint32_t>(c->sc->wgring);
-  D.codes = as<uint8_t>(c->sc->wlds);
+  if ((st = ensure(c, c->sc->wlds, (size_t)code_bytes))) return st;
   aim::Work WG = Wk;
   int32_t *lists[2] = {as<int32_t>(c->sc->list2), as<int32_t>(c->sc->list3)};
   for (int k = 0; k < ng; ++k) {
@@ -607,8 +624,23 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   }
   WG.counter = Wk.counter;
   c->last_class_window[0] = D.W;
-  Phase ph(c, s, Wk.direct ? "wfa_adaptive_rerun" : WG.idx != Wk.idx ? "wfa_adaptive_wide" : "wfa_adaptive");
-  HIP_TRY(aim::launch_wfa_lds(S, O, P, WG, D, threads, nslots, s));
+  for (int k = 0; k < shapes; ++k) {
+    aim::WfaLds &F = shape[k];
+    F.gring = lds_ring ? nullptr : as<uint32_t>(c->sc->wgring);
+    F.codes = as<uint8_t>(c->sc->wlds);
+    if (k + 1 < shapes) {
+      F.long_list = as<int32_t>(Wk.direct ? c->sc->list2 : c->sc->spill);
+      F.long_count = cnt + (Wk.direct ? C_AL2 : C_AL);
+    }
+    {
+      Phase ph(c, s, Wk.direct ? "wfa_adaptive_rerun" : WG.idx != Wk.idx ? "wfa_adaptive_wide" : "wfa_adaptive");
+      HIP_TRY(aim::launch_wfa_lds(S, O, P, WG, F, threads, nslots[k], s));
+    }
+    shape[1].ad_dropped = nullptr;  // (counted by the first)
+    WG.idx = F.long_list;
+    WG.count = F.long_count;
+    WG.counter = cnt + (Wk.direct ? C_AL2W : C_ALW);
+  }
   return AIM_OK;
 }
 

@@ -144,3 +144,31 @@ def test_graph_replays(name, n):
             bad = compare(got, want)
             assert not bad, (rep, describe(b, bad[0], got, want))
         g.close()
+
+
+@pytest.mark.parametrize("n,hard", [(400, False), (200, True)])
+def test_codes_past_the_first_slots(n, hard):
+    # unrelated pairs of 3 kbp: ranges too wide for the lane groups and origin
+    # codes (some 700 KB) past the slots of the wide kernel's first launch, so that
+    # its second one aligns them, and re-runs those whose runs outgrow the pool;
+    # every other pair stays in the groups
+    rng = np.random.default_rng(n)
+    T = [rng.integers(0, 4, 3000).astype(np.uint8) for _ in range(n)]
+    P = [rng.integers(0, 4, 2990 + k % 20).astype(np.uint8) if k % 4 else T[k] for k in range(n)]
+    b = synth.from_lists(P, T)
+    with aim.Context(0, scratch_limit=1 << 30, hard_limit=hard) as c, aim.Context(0) as free:
+        c.wfa_adaptive_params(10, 100)
+        free.wfa_adaptive_params(10, 100)
+        got = run(c, b, "wfa_adaptive", AFF)
+        stats = c.last_call_stats()
+        ref = run(free, b, "wfa_adaptive", AFF)
+        # (a re-run drops its diagonals once more)
+        dropped = free.last_call_stats()["wfa_adaptive_dropped"]
+    assert stats["wfa_adaptive_dropped"] > dropped if hard else stats["wfa_adaptive_dropped"] == dropped
+    assert not hard or stats["cigar_reruns"] > 0
+    assert not compare(got, ref)
+    some = np.arange(0, n, 7)
+    want = oracle.wfa_batch(b.subset(some), AFF, -1, adaptive=(10, 100))
+    for t, i in enumerate(some):
+        assert (got[0][i], got[1][i]) == (want[0][t], want[1][t])
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][t]:want[3][t + 1]])
