@@ -562,10 +562,11 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   if (lds > 160 * 1024) return fail(AIM_ERR_UNSUPPORTED, "WFA-adaptive: sequences too long to stage");
   // Two shapes.  The first, 24 wavefronts a CU behind the groups, has slots (the
   // ring with its guard word, and with CIGARs the score table and the origin codes
-  // of every kept score) whose codes take an eighth of the budget together, at
-  // least 256 KiB each.  Where that is less than any pair can need, up to 4 MiB, a
-  // second shape of a wavefront for each SIMD takes the pairs that outgrow it, with
-  // 5/16 of the budget (a pair needing more gets no CIGAR).  With every slot at
+  // of every kept score) whose codes take a sixteenth of the budget together, at
+  // least 256 KiB each (5/16 in batches of few pairs).  Where that is less than any
+  // pair can need, up to 4 MiB, a second shape of a wavefront for each SIMD takes
+  // the pairs that outgrow it, with 5/16 of the budget (a pair needing more gets no
+  // CIGAR).  With every slot at
   // its largest the first took 20-30 GB, whose return costs 0.7 s.  A pair or none
   // comes here at max_dist 50 and some per cent of errors, but with four
   // wavefronts a CU alone 200,000 unrelated pairs of 150 bp took 100 ms instead of
@@ -587,7 +588,7 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   int shapes = 0;
   for (bool all = false; !all; ++shapes) {
     aim::WfaLds &F = shape[shapes];
-    const int64_t share = c->limit() * 5 / 16, code_share = shapes == 0 && groups ? c->limit() / 8 : share;
+    const int64_t share = c->limit() * 5 / 16, code_share = shapes == 0 && groups && n > c->cus * 8 ? c->limit() / 16 : share;
     int64_t slots = std::min<int64_t>(n, c->cus * (shapes == 0 ? per_cu : std::min<int64_t>(per_cu, 4)));
     // (fewer workgroups when rings or codes do not fit)
     if (!lds_ring) slots = std::max<int64_t>(1, std::min(slots, share / (F.gring_slot * 4)));
