@@ -324,6 +324,7 @@ struct WfaGroup {
   // pairs that leave the pass: by predicted extent to a later class (a wider
   // group, a window class); adaptive ones to class 1
   int32_t by_length; // leaving pairs keep the queue's order
+  int32_t pool_share; // runs of the pool a pair may reserve unseen (O.pool_cap over the batch's pairs)
   int32_t my_class;  // this pass's index in the route (0: the first pass)
   WfaRoute route;
   // the full-store fallback of a failed walk, as in WfaLaunch

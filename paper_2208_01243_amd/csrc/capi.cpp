@@ -515,6 +515,8 @@ int64_t wfa_group_plan(const aim_context *c, int32_t L, const aim::Scoring &P, i
   return slots * D.slot_words * 4;
 }
 
+int32_t wfa_pool_share(const aim::Outs &O, int64_t n) { return (int32_t)std::min<int64_t>(O.pool_cap / n, INT32_MAX); }
+
 aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                             int64_t n, int32_t L, int32_t *cnt, const aim::Work &Wk, const Tune &tu,
                             hipStream_t s) {
@@ -617,6 +619,7 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
     G[k].ad_min = c->ad_min;
     G[k].ad_max = c->ad_max;
     G[k].ad_dropped = D.ad_dropped;
+    G[k].pool_share = wfa_pool_share(O, n);
     WG.counter = group_counter(cnt, k);
     Phase ph(c, s, k == 0 ? "wfa_adaptive" : "wfa_adaptive_b");
     HIP_TRY(aim::launch_wfa_group(S, O, P, WG, G[k], lanes[k], 1, true, s));
@@ -752,6 +755,7 @@ aim_status launch_group_passes(aim_context *c, const aim::Seqs &S, const aim::Ou
       W.count = G.route.count[k];
     }
     Phase ph(c, s, names[k]);
+    G.pool_share = wfa_pool_share(O, n);
     HIP_TRY(aim::launch_wfa_group(S, O, P, W, G, passes[k].lanes, passes[k].words, false, s));
   }
   if (!passes.empty()) c->last_window = 2 * passes[0].lanes * passes[0].words;
@@ -1539,7 +1543,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
   const int64_t pool_cap =
       R->want_cigar ? std::max<int64_t>(c->strict() ? 1 << 14 : 1 << 20,
                                         std::min<int64_t>(c->limit() / 64 / 4,
-                                                          n * std::min<int64_t>(2 * (int64_t)L + 1, 8192) / 4))
+                                                          n * std::min<int64_t>(2 * (int64_t)L + 1, 20480) / 4))
                     : 1;
   if ((st = ensure(c, c->sc->pool, (size_t)pool_cap * 4))) return st;
   // a2: length buckets, longest first (LPT order for the persistent queues)

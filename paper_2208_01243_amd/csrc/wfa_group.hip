@@ -181,43 +181,37 @@ __device__ void walk_pair(ArgsPtr A, Done d, uint32_t *codes, int32_t rowmask) {
       cur = 0;
     }
   }
-  // runs go to the end of the pair's slot (or of a reservation in the pool)
-  // backwards, so that they lie there last op first, as every pass leaves them
-  const int64_t bound = 2 * (int64_t)nt + 1;
-  const int32_t slot_cap = A->O.slot_cap;
-  uint32_t *end = A->O.slot + (p + 1) * (int64_t)slot_cap;
-  int64_t room = slot_cap, tag = POOL_OFF_TAIL;
-  if (bound > slot_cap) {
-    const unsigned long long at = atomicAdd(A->O.pool_top, (unsigned long long)bound);
-    if (at + (unsigned long long)bound <= (unsigned long long)A->O.pool_cap) {
-      end = A->O.pool + at + bound;
-      room = bound;
-      tag = POOL_OFF_WHOLE | (int64_t)(at + bound);
-    }
+  if (nt & 7) {
+    const int32_t w = nt >> 3;
+    if (w == 0) w0 = cur;
+    else if (w == 1) w1 = cur;
+    else tok_at(w) = cur;
   }
-  int32_t nr = 0;
-  uint32_t rop = 0xffu, rlen = 0;
-  auto put = [&](uint32_t op, uint32_t len) {
-    if (len == 0) return;
-    if (op == rop) {
-      rlen += len;
-      return;
-    }
-    if (rlen && nr < room) end[-1 - nr] = (rlen << 4) | rop;
-    nr += rlen != 0;
-    rop = op;
-    rlen = len;
-  };
-  if (ok) {
+  // The forward replay, which meets the runs first op first: emit(r, run) for the
+  // r-th, returns their number, -1 where it does not end at (m, n).
+  auto replay = [&](auto emit) -> int32_t {
+    int32_t nr = 0, left = nt;
+    uint32_t rop = 0xffu, rlen = 0, word = 0;
+    auto put = [&](uint32_t op, uint32_t len) {
+      if (len == 0) return;
+      if (op == rop) {
+        rlen += len;
+        return;
+      }
+      if (rlen) emit(nr, (rlen << 4) | rop);
+      nr += rlen != 0;
+      rop = op;
+      rlen = len;
+    };
     int32_t j = extend(gP, pnw, m, gT, tnw, n, 0, 0), i = j;
     put(OP_EQ, (uint32_t)j);
-    while (nt > 0) {
-      if ((nt & 7) == 0) {
-        const int32_t w = (nt >> 3) - 1;
-        cur = w == 0 ? w0 : w == 1 ? w1 : tok_at(w);
+    while (left > 0) {
+      if ((left & 7) == 0 || left == nt) {
+        const int32_t w = (left - 1) >> 3;
+        word = w == 0 ? w0 : w == 1 ? w1 : tok_at(w);
       }
-      --nt;
-      const uint32_t tok = cur >> (4 * (nt & 7));
+      --left;
+      const uint32_t tok = word >> (4 * (left & 7));
       const uint32_t op = tok & 3u;
       i += op != OP_D;
       j += op != OP_I;
@@ -229,14 +223,49 @@ __device__ void walk_pair(ArgsPtr A, Done d, uint32_t *codes, int32_t rowmask) {
         j = f;
       }
     }
-    if (rlen && nr < room) end[-1 - nr] = (rlen << 4) | rop;
+    if (rlen) emit(nr, (rlen << 4) | rop);
     nr += rlen != 0;
-    ok = i == m && j == n;
+    return i == m && j == n ? nr : -1;
+  };
+  // The runs go to the end of the pair's slot, or of a reservation in the pool,
+  // backwards, so that they lie there last op first, as every pass leaves them.
+  // The reservation is for all that there can be, two a token and one, where that
+  // is within the pair's share of the pool or the pool less than half used.  Where
+  // it is not, and the runs pass the slot, a second replay lays them out the usual
+  // way: the last slot_cap in the slot, the others in a reservation of their
+  // number.  (With the first kind alone 10,000 unrelated pairs of 250 bp, about 170
+  // runs each in a pool of 125 a pair, used that up at 261 a pair, and half were
+  // re-run in place: 956 ms instead of 2; with the second for every pair past its
+  // share 4,000 adaptive pairs of 10 kbp at 10 % took 8.0 ms instead of 7.1.)
+  int32_t room = A->O.slot_cap;
+  uint32_t *end = A->O.slot + (p + 1) * (int64_t)room;
+  if (const int32_t bound = 2 * nt + 1; bound > room) {
+    const int64_t pool_cap = A->O.pool_cap;
+    if (bound <= A->L.pool_share || (int64_t)*(volatile unsigned long long *)A->O.pool_top + bound <= pool_cap / 2) {
+      const int64_t at = (int64_t)atomicAdd(A->O.pool_top, (unsigned long long)bound);
+      if (at + bound <= pool_cap) {
+        end = A->O.pool + at + bound;
+        room = bound;
+      }
+    }
   }
-  if (ok) {
+  const int32_t nr = ok ? replay([&](int32_t r, uint32_t run) { if (r < room) end[-1 - r] = run; }) : -1;
+  if (nr > room) {
+    const int32_t need = nr - room;  // (room: the slot's)
+    const int64_t at = (int64_t)atomicAdd(A->O.pool_top, (unsigned long long)need);
+    const bool fits = at + need <= A->O.pool_cap;
     A->O.nruns[p] = nr;
-    A->O.pool_off[p] = nr > room ? -2  // re-run in place by the compaction
-                                 : (tag & POOL_OFF_WHOLE) && tag > 0 ? tag - nr : tag;
+    A->O.pool_off[p] = fits ? at : -2;  // (-2: re-run in place by the compaction)
+    if (fits)
+      replay([&](int32_t r, uint32_t run) {
+        const int32_t k = nr - 1 - r, cap = A->O.slot_cap;
+        (k < cap ? A->O.slot + p * (int64_t)cap : A->O.pool + A->O.pool_off[p] - cap)[k] = run;
+      });
+    return;
+  }
+  if (nr >= 0) {
+    A->O.nruns[p] = nr;
+    A->O.pool_off[p] = room == A->O.slot_cap ? POOL_OFF_TAIL : (POOL_OFF_WHOLE | (end - A->O.pool)) - nr;
     return;
   }
   // cannot happen for codes that were kept and read back intact

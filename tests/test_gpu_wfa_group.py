@@ -269,3 +269,22 @@ def test_large_band_batch_under_a_hard_limit(alg, pen, L):
     assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
     for i in range(0, len(k), 41):
         assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
+
+
+@pytest.mark.parametrize("alg,pen", [("wfa", AFF), ("swg", AFF), ("nw", (0, 1, 0, 1))])
+def test_unrelated_pairs_fit_the_pool(alg, pen):
+    # 10,000 unrelated pairs of 250 bp: most have 130 to 190 runs where the pool
+    # holds 125 a pair beside the slots of 128; none may need the in-place re-run
+    rng = np.random.default_rng(21)
+    base = lambda n: rng.integers(0, 4, n).astype(np.uint8)  # noqa: E731
+    uniq = synth.from_lists([base(int(rng.integers(200, 251))) for _ in range(500)], [base(250) for _ in range(500)])
+    k = np.arange(10_000) % uniq.n
+    want = oracle.align_batch(uniq, alg, pen)
+    with aim.Context(0) as c:
+        got = run(c, uniq.subset(k), alg, pen)
+        stats = c.last_call_stats()
+    assert (np.diff(want[3]) > 128).any() and stats["cigar_reruns"] == 0
+    assert np.array_equal(got[0], want[0][k]) and np.array_equal(got[1], want[1][k])
+    assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
+    for i in range(len(k)):
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
