@@ -515,6 +515,9 @@ int64_t wfa_group_plan(const aim_context *c, int32_t L, const aim::Scoring &P, i
   return slots * D.slot_words * 4;
 }
 
+// Batches whose wavefronts do not fill the chip.
+bool wfa_small(const aim_context *c, int64_t n) { return n <= (int64_t)c->cus * 16; }
+
 int32_t wfa_pool_share(const aim::Outs &O, int64_t n) { return (int32_t)std::min<int64_t>(O.pool_cap / n, INT32_MAX); }
 
 aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
@@ -541,14 +544,18 @@ aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs 
   // every pair at max_dist 50, and 64 lanes nearly all of the rest; what
   // leaves those goes on to the kernel below, with every diagonal.
   // Long reads start in 64 lanes: theirs drift furthest (10,000 pairs of 10 kbp
-  // at 5 % take 8.3 ms from 32 lanes on, 6.7 ms from 64).
+  // at 5 % take 8.3 ms from 32 lanes on, 6.7 ms from 64).  So do batches that do not
+  // fill the chip, whose time is that of the pairs that start twice (2,000 of 150 bp
+  // at 2 % 0.148 from 16 on, 0.090 from 64; 600 of 1 kbp at 5 % 0.55 and 0.26; 64 of
+  // 3 kbp, a fifth unrelated, under a threshold of 5.5 % 2.6 and 2.1, against 1.7
+  // with the kernel below alone).
   const bool groups = wfa_group_fits(L, P) && c->ad_min <= 50 && c->ad_max <= 100;
   aim::WfaGroup G[2];
   int32_t lanes[2] = {64, 64};
   int ng = 0;
   int64_t group_bytes = 0;
   if (!Wk.direct && groups) {
-    lanes[0] = c->ad_max > 50 || L > 4096 ? 64 : L <= 192 ? 16 : 32;
+    lanes[0] = c->ad_max > 50 || L > 4096 || wfa_small(c, n) ? 64 : L <= 192 ? 16 : 32;
     ng = lanes[0] == 64 ? 1 : 2;
     for (int k = 0; k < ng; ++k) {
       G[k] = aim::WfaGroup{};
@@ -723,8 +730,6 @@ std::vector<GroupPass> wfa_group_passes(const aim::Scoring &P, int32_t L, bool s
   }
   return passes;
 }
-// Batches whose wavefronts do not fill the chip.
-bool wfa_small(const aim_context *c, int64_t n) { return n <= (int64_t)c->cus * 16; }
 constexpr int64_t WFA_RING_STEPS = 2048;  // steps of codes a wavefront keeps (more if a pair can need them)
 
 // The passes' launch shapes, each with G (what they share) and its index in the

@@ -288,3 +288,18 @@ def test_unrelated_pairs_fit_the_pool(alg, pen):
     assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
     for i in range(len(k)):
         assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 0), (100, 192), (193, 600), (2000, 3000)])
+@pytest.mark.parametrize("adaptive", [(10, 50), (2, 3), (30, 20)])
+def test_adaptive_batches_that_start_narrow(ctx, lo, hi, adaptive):
+    # more pairs than the chip has wavefronts for: those start in 16 or 32 lanes
+    uniq = drift_pairs(lo + adaptive[1], lo, hi) if lo else edge_pairs(6)
+    k = np.arange(4200) % uniq.n
+    ctx.wfa_adaptive_params(*adaptive)
+    want = oracle.wfa_batch(uniq, AFF, -1, adaptive=adaptive)
+    got = run(ctx, uniq.subset(k), "wfa_adaptive", AFF)
+    assert np.array_equal(got[0], want[0][k]) and np.array_equal(got[1], want[1][k])
+    assert np.array_equal(np.diff(got[3]), np.diff(want[3])[k])
+    for i in range(len(k)):
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][k[i]]:want[3][k[i] + 1]]), i
