@@ -192,6 +192,13 @@ struct aim_context {
 
 namespace {
 
+// Scratch is given back cleared: it holds the caller's sequences and
+// alignments, and freed memory comes back as it is from the process's next
+// allocation.  (3 TB/s, where a buffer grows and where a context ends.)
+void clear_scratch(const Buf &b, hipStream_t s) {
+  if (aim::launch_fill_i32(static_cast<int32_t *>(b.p), 0, (int64_t)(b.bytes / 4), s) != hipSuccess) (void)hipGetLastError();
+}
+
 aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
   if (bytes == 0) bytes = 256;
   if (b.bytes >= bytes) return AIM_OK;
@@ -214,9 +221,12 @@ aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
     // previously enqueued work may still use the old buffer: free it behind
     // that work on the call's stream, or after a device synchronisation
     if (b.pooled && as) {
+      clear_scratch(b, as);
       HIP_TRY(hipFreeAsync(b.p, as));
     } else {
       HIP_TRY(hipDeviceSynchronize());
+      clear_scratch(b, c->aux);
+      HIP_TRY(hipStreamSynchronize(c->aux));
       if (b.pooled)
         HIP_TRY(hipFreeAsync(b.p, nullptr));
       else
@@ -1362,6 +1372,9 @@ void aim_destroy(aim_context *c) {
   c->graphs.clear();
   (void)hipDeviceSynchronize();
   const auto all = all_buffers(c->own);
+  for (Buf *b : all)
+    if (b->p) clear_scratch(*b, c->aux);
+  (void)hipStreamSynchronize(c->aux);
   for (Buf *b : all)
     if (b->p) (void)(b->pooled ? hipFreeAsync(b->p, nullptr) : hipFree(b->p));
   (void)hipDeviceSynchronize();
