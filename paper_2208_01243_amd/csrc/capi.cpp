@@ -192,9 +192,12 @@ struct aim_context {
 
 namespace {
 
-// Scratch is given back cleared: it holds the caller's sequences and
-// alignments, and freed memory comes back as it is from the process's next
-// allocation.  (3 TB/s, where a buffer grows and where a context ends.)
+// Scratch is given back cleared: freed memory comes back as it is from the
+// process's next allocation, and a caller that reads what no call has written
+// (results behind cigar_off[n], say) would find alignments there.  It is filled
+// where a buffer grows from one call to the next (3 TB/s: a third of a
+// millisecond for 1 GB, beside some milliseconds for the allocation; no buffer
+// grows within a call) and where a context gives its scratch back.
 void clear_scratch(const Buf &b, hipStream_t s) {
   if (aim::launch_fill_i32(static_cast<int32_t *>(b.p), 0, (int64_t)(b.bytes / 4), s) != hipSuccess) (void)hipGetLastError();
 }
@@ -275,6 +278,8 @@ void release_scratch(aim_context *c, hipStream_t s) {
       (void)hipDeviceSynchronize();
       waited = true;
     }
+    clear_scratch(*b, s);
+    if (!b->pooled) (void)hipStreamSynchronize(s);
     (void)(b->pooled ? hipFreeAsync(b->p, s) : hipFree(b->p));
     *b = Buf{};
   }
