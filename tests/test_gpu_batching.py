@@ -331,6 +331,27 @@ def test_smaller_batch_after_a_refused_one(alg):
     assert refused
 
 
+@pytest.mark.parametrize("alg,pen,n,field", [("nw", (0, 1, 0, 1), 2048, 6), ("swg", (0, 4, 6, 2), 4096, 6),
+                                             ("wfa", (0, 4, 6, 2), 64, 12)])
+def test_autotune_tries_the_built_in_choice(alg, pen, n, field):
+    # small batches of 100-1,000 bp: the built-in route (field 6: band16 3, the
+    # wavefront passes at once; field 12: 0, a window from the batch) is several
+    # times (WFA: twice) faster than any other candidate
+    rng = np.random.default_rng(n)
+    lens = synth.log_uniform_int(rng, 333 if alg == "wfa" else 100, 1000, n)
+    b = synth._gen_chunk(rng, n, lens, rng.uniform(0.06, 0.08, n), None)
+    dev, enc = to_device(b, "2bit")
+    outs = _outputs(b)
+    max_len = int(max(b.pat_len.max(), b.txt_len.max()))
+    with aim.Context(0) as c:
+        want = run(c, b, alg, pen)
+        params, _ = c.autotune(*dev, enc=enc, max_len=max_len, alg=alg, pen=pen, max_score=-1, score=outs[0],
+                               status=outs[1], cigar=outs[2], cigar_off=outs[3], reps=3)
+        assert params[field] == (3 if field == 6 else 0), params
+        assert not compare(run(c, b, alg, pen), want)
+        assert not compare(_host(outs), want)
+
+
 def test_autotune_wfa_mixed_per_bucket(tmp_path):
     # one mixed batch (100 bp - 10 kbp): the tuner keeps a batch tune and a
     # tune per window-class length bucket; the tuned calls return exactly what
