@@ -79,7 +79,9 @@ typedef enum { AIM_ENC_ASCII = 0, AIM_ENC_CODE = 1, AIM_ENC_2BIT = 2 } aim_encod
                                      slots, a score past 2^20, or one score's
                                      origin codes past its code window; see
                                      aim_call_stats.wfa_long_failed), or (WFA-
-                                     adaptive) its origin codes outgrew the slot */
+                                     adaptive) its origin codes outgrew the slot, or
+                                     its walk failed (never seen; see
+                                     aim_call_stats.wfa_walk_failed) */
 #define AIM_PAIR_INVALID 3        /* non-ACGT base or length beyond max_len */
 
 /* CIGAR run encoding: (run_length << 4) | op. */
@@ -329,8 +331,13 @@ aim_status aim_timing_reset(aim_context *ctx);
  *     64-diagonal band), and that band on to the last tier;
  *   wfa_wide: WFA pairs whose wavefronts left every narrower window;
  *   wfa_walk_failed: WFA pairs whose walk over the kept origin codes failed
- *     (0 unless a code was read back wrong; each is re-walked from a full
- *     store, so results stay exact and only time is lost);
+ *     (0 unless a code was read back wrong).  Where the batch's plan has the
+ *     full-store passes, each is re-walked from one, so that results stay exact
+ *     and only time is lost.  Batches that the group and wide passes hold alone
+ *     (penalties with gap_extend their common divisor and max_len <= 3,069 or a
+ *     threshold that keeps wavefronts as narrow; NW and SWG among them) and
+ *     WFA-adaptive have none: there such a pair keeps its score and is
+ *     AIM_PAIR_CIGAR_OVERFLOW, whatever cigar_cap;
  *   wfa_walk_skipped: accepted WFA pairs whose codes were not kept (more
  *     scores than the code slot holds);
  *   full_store[c]: pairs walked by the full-store pass, per store class
