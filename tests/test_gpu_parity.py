@@ -282,3 +282,61 @@ def test_pack_2bit_entry_point(ctx, enc):
     got2 = out2.cpu().numpy().view(np.uint64)
     ok2 = np.repeat((f2 == 0)[:1000], np.diff(woff)[:1000])
     assert np.array_equal(got2[:int(woff[1000])][ok2], words[:int(woff[1000])][ok2])
+
+
+# penalties that the wavefront group passes do not take (the gap extension is not
+# the common divisor): every tier of the band, and the first one-wavefront window
+# and window classes of WFA, with the path counters that say so
+SWG3, NW4 = (0, 4, 6, 3), (0, 3, 0, 4)
+
+
+@pytest.mark.parametrize("alg,pen", [("swg", SWG3), ("nw", NW4)])
+def test_band_tiers_with_wider_extension(ctx, alg, pen):
+    # 64 diagonals and their walk, then the full matrix (reads of at most 256 bp)
+    b = _length_gap_batch(42, 700, 40, 170, 80, [0.0, 0.02, 0.08])
+    assert max(b.pat_len.max(), b.txt_len.max()) <= 256
+    full = check(ctx, b, alg, pen)
+    st = ctx.last_call_stats()
+    assert st["band_escalated"] > st["band_escalated2"] > 0 and st["wfa_window"] == 0
+    check(ctx, b, alg, pen, 120)
+    s_, st_, _, off = run(ctx, b, alg, pen, want_cigar=False)
+    assert np.array_equal(s_, full[0]) and np.array_equal(st_, full[1]) and not off.any()
+
+
+def test_second_tier_chunks_of_a_small_scratch(ctx):
+    # 4 MiB hold the traceback of few chunks of the 64-diagonal tier: the pairs of
+    # the others go on, to the full matrix and, of longer reads, to WFA
+    for seed, lo, hi in ((43, 130, 200), (44, 300, 400)):
+        b = _length_gap_batch(seed, 600, lo, hi, 50, [0.0, 0.03])
+        check(ctx, b, "swg", SWG3)
+        free = ctx.last_call_stats()
+        with aim.Context(0, scratch_limit=4 << 20) as c:
+            check(c, b, "swg", SWG3)
+            st = c.last_call_stats()
+        assert st["band_escalated"] == free["band_escalated"]
+        assert st["band_escalated2"] >= free["band_escalated2"] + 10, (st, free)
+
+
+def test_window_classes_with_wider_extension(ctx):
+    # the one-wavefront window, the classes to 512 and 1,536 diagonals and the rest
+    rng = np.random.default_rng(45)
+    base = lambda n: rng.integers(0, 4, n).astype(np.uint8)  # noqa: E731
+    pats, txts = [], []
+    for k, gap in enumerate([0, 20, 150, 300, 450, 700, 1000, 1300, 1700, 2200] * 4):
+        T = base(int(rng.integers(300, 600)))
+        P = np.concatenate([T[:200], base(gap), T[200:]])
+        pats.append(P if k % 2 else T)
+        txts.append(T if k % 2 else P)
+    for L in np.linspace(300, 3000, 60):
+        T = base(int(L))
+        one = synth.from_lists([T], [T])
+        pats.append(synth.mutate(rng, one.txt, one.txt_off, [0.1])[0])
+        txts.append(T)
+    b = synth.from_lists(pats, txts)
+    for smax in (-1, 2500):
+        want = oracle.wfa_batch(b, SWG3, smax)
+        got = run(ctx, b, "wfa", SWG3, smax)
+        st = ctx.last_call_stats()
+        bad = compare(got, want)
+        assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
+        assert 0 < st["wfa_window"] <= 256 and min(st["wfa_class_pairs"][:3 if smax < 0 else 2]) > 0, st
