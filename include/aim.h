@@ -163,8 +163,9 @@ typedef struct {
    * then sized for half of it, 3/8 below 1 GiB, the rest holding the arrays
    * that grow with the batch): a call that would need more fails with
    * AIM_ERR_OOM (its outputs are then unspecified), and the context gives back
-   * all its scratch, so that a smaller batch can be retried on it (graphs captured
-   * from it have to be captured again). */
+   * all its scratch, so that a smaller batch can be retried on it.  Graphs captured
+   * from it have to be captured again, unless the call was refused before any
+   * buffer changed: they can still be replayed then, and the scratch is kept. */
   int64_t scratch_limit;
 } aim_options;
 
@@ -378,9 +379,9 @@ aim_status aim_last_call_stats(aim_context *ctx, aim_call_stats *out);
 
 /* Time every candidate launch configuration on this batch and keep the
  * fastest for (alg, length bucket of pairs->max_len); later calls with that
- * key use it.  Candidates: NW/SWG -- first band width {32, 64}, resident
- * wavefronts per CU {8, 16, 32}, length sort {off, on}, packed 16-bit cells
- * {off, on} (32 diagonals only); WFA -- length sort {off, on}, the first
+ * key use it.  Candidates: the built-in choice; NW/SWG -- first band width
+ * {32, 64}, resident wavefronts per CU {8, 16, 32}, length sort {off, on}, packed
+ * 16-bit cells {off, on} (32 diagonals only); WFA -- length sort {off, on}, the first
  * window, workgroup size for the widest pairs {128,
  * 256}, then, for each window class the batch uses, the built-in kernel
  * or one whose workgroup size {64, 128, 256} (pairs per workgroup: one; lanes
@@ -402,9 +403,11 @@ aim_status aim_autotune(aim_context *ctx, const aim_batch *pairs, int32_t alg, a
  * LDS KB, [4] WFA full-store LDS KB, [5] WFA long-pair workgroup size,
  * [6] packed 16-bit band cells when the value bound allows (0 off; 1 on, each
  * wavefront walking its own pairs' tracebacks; 2 on, the tracebacks walked by
- * a second kernel beside the escalation tiers; 3, the default: 2 for batches
- * of at least 65536 pairs, else 1, or 0 for fewer than 16384 pairs of reads
- * of at most 128 bases), [7] WFA pairs wider than the
+ * a second kernel beside the escalation tiers; 3, the default: batches below
+ * 65536 pairs or of reads over 192 bases go through the wavefront passes at once
+ * where those take the penalties and [0] is 32, the others as with 2 from 65536
+ * pairs on, else as with 1, or 0 for fewer than 16384 pairs of reads of at most
+ * 128 bases), [7] WFA pairs wider than the
  * first windows go through window classes (1, the default) or
  * straight to the HBM-ring pass (0), [8..10] workgroup size (64, 128, 256 or
  * 512) of the three window classes (narrowest first), [11] bit c set: class

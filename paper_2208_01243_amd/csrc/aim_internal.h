@@ -444,9 +444,8 @@ hipError_t launch_prefilter(int64_t n, const Seqs &S, const int8_t *flags, int32
                             const Outs *O, int32_t *list, int32_t *count, int32_t *rejected, hipStream_t s);
 
 // GenASM (windowed bitap with traceback, unit edits, threshold max_score),
-// one pair per lane, 64 pairs per wavefront from Wk's counter.  Each
-// wavefront keeps `levels` edit levels of 64 x 64 status words in its slot of
-// nblocks blocks of a wavefront.
+// one pair per lane, 64 pairs at a time from Wk's counter: nblocks workgroups of
+// one wavefront, which keep a window's differences in LDS (no scratch).
 int32_t genasm_waves_per_cu();
 hipError_t launch_genasm(const Seqs &S, const Outs &O, const Scoring &P, const Work &Wk, int32_t nblocks, hipStream_t s);
 

@@ -220,7 +220,17 @@ aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
     return AIM_OK;
   }
   if (c->capturing) return fail(AIM_ERR_INVALID_ARG, "scratch would grow during graph capture");
+  size_t want = bytes + bytes / 8;
+  if (c->opt.flags & AIM_FLAG_HARD_LIMIT) {
+    // (refused before the old buffer goes: captured graphs may still use it)
+    const int64_t held = c->dev_bytes - (int64_t)b.bytes, room = c->opt.scratch_limit - held;
+    if ((int64_t)bytes > room)
+      return fail(AIM_ERR_OOM, "scratch limit of %lld bytes reached (%lld held, %zu more needed)",
+                  (long long)c->opt.scratch_limit, (long long)held, bytes);
+    want = std::min<size_t>(want, (size_t)room);
+  }
   hipStream_t as = c->astream;
+  c->generation += 1;
   if (b.p) {
     // previously enqueued work may still use the old buffer: free it behind
     // that work on the call's stream, or after a device synchronisation
@@ -240,15 +250,6 @@ aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
     b.p = nullptr;
     b.bytes = 0;
   }
-  size_t want = bytes + bytes / 8;
-  if (c->opt.flags & AIM_FLAG_HARD_LIMIT) {
-    const int64_t room = c->opt.scratch_limit - c->dev_bytes;
-    if ((int64_t)bytes > room)
-      return fail(AIM_ERR_OOM, "scratch limit of %lld bytes reached (%lld held, %zu more needed)",
-                  (long long)c->opt.scratch_limit, (long long)c->dev_bytes, bytes);
-    want = std::min<size_t>(want, (size_t)room);
-  }
-  c->generation += 1;
   auto alloc = [&](size_t sz) { return as ? hipMallocAsync(&b.p, sz, as) : hipMalloc(&b.p, sz); };
   b.pooled = as != nullptr;
   hipError_t e = alloc(want);
@@ -270,8 +271,11 @@ aim_status ensure(aim_context *c, Buf &b, size_t bytes) {
 
 // Gives back all scratch behind the work on `s` (a call was refused for want of
 // it): what the call and those before it held may leave no room for the smaller
-// batch that is tried next.  The error message stays.
+// batch that is tried next.  The error message stays.  A captured graph that can
+// still be replayed (the call was refused before any buffer changed) keeps all.
 void release_scratch(aim_context *c, hipStream_t s) {
+  for (const aim_graph *g : c->graphs)
+    if (g->generation == c->generation) return;
   bool waited = false;
   for (Buf *b : all_buffers(c->own)) {
     if (!b->p) continue;
@@ -407,8 +411,6 @@ struct Fork {
 constexpr int32_t MAX_LEN_LIMIT = 1 << 20;
 constexpr int32_t SLOT_CAP = 128;  // at most this many runs per pair held before compaction
 
-
-
 int32_t len_bucket_host(int32_t L) {
   int32_t b = 0;
   while ((1 << b) < L + 1 && b < 30) ++b;
@@ -457,17 +459,6 @@ aim::Scoring wfa_scoring(const aim::Scoring &P) {
   R.unit = g;
   return R;
 }
-
-// WFA: the one-wavefront score pass (16-bit LDS ring, fused walk) when the
-// batch allows it, else the score pass with the ring in LDS; then the score
-// pass with the ring in HBM for pairs too wide for either (fused walk too);
-// then the fallback pass (full store + walk) by store-size class for pairs
-// whose origin codes did not fit.
-// `order` lists the pairs to align (nullptr: all n), `order_count` its length
-// on the device (nullptr: n).
-// WFA-adaptive: every pair through the packed wavefront kernel with its
-// ring in a global slot and a window of every diagonal the batch can reach,
-// plus the reduction step.  Wk lists the pairs (a re-run when Wk.direct).
 
 // The group pass (k_wfa_group) takes unit gap extension, and sequences whose
 // offsets and absent marks fit 16 bits.
@@ -526,6 +517,10 @@ bool wfa_small(const aim_context *c, int64_t n) { return n <= (int64_t)c->cus * 
 
 int32_t wfa_pool_share(const aim::Outs &O, int64_t n) { return (int32_t)std::min<int64_t>(O.pool_cap / n, INT32_MAX); }
 
+// WFA-adaptive: the group passes with a window that follows the wavefront, where
+// the penalties and the reduction's parameters keep it narrow; behind them (or for
+// all pairs) the class kernel with a window of every diagonal the batch can reach.
+// Wk lists the pairs (a re-run when Wk.direct: by the class kernel alone).
 aim_status run_wfa_adaptive(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                             int64_t n, int32_t L, int32_t *cnt, const aim::Work &Wk, const Tune &tu,
                             hipStream_t s) {
@@ -944,6 +939,15 @@ bool band_by_wfa(const aim_context *c, const aim::Scoring &P, const Tune &tu, co
   return tu.band_w0 == 32 && tu.band16 == 3 && (n < SPLIT_MIN_PAIRS || L > WFA_BAND_LEN) && band_to_wfa(c, P, wfa_tune, n, L);
 }
 
+// WFA.  Unit gap extension: the group passes, the wide passes and, where those do
+// not hold every pair of the batch, the widest window class; other penalties: the
+// one-wavefront pass (16-bit ring in LDS) and the window classes, or, where 16 bits
+// or LDS do not hold the batch, the score pass with its ring in LDS.  Then the score
+// pass with the ring in HBM for pairs too wide for any of them.  All walk the codes
+// they kept; pairs whose codes fitted no slot go to the full-store passes, by store
+// size, and the largest to the long pass.
+// `order` lists the pairs to align (nullptr: all n), `order_count` its length
+// on the device (nullptr: n).
 aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const aim::Scoring &Pin,
                    int64_t n, int32_t L, bool plain, int32_t *cnt, const int32_t *order,
                    const int32_t *order_count, const Tune &tu, hipStream_t s) {
@@ -1520,7 +1524,7 @@ static aim_status align_batch(aim_context *c, const aim_batch *B, int32_t alg, a
   int64_t run_bound = 2 * (int64_t)L + 1;
   const int32_t cmin = alg == AIM_GENASM ? 1 : std::min(pen.mismatch, (alg == AIM_NW_LINEAR ? 0 : pen.gap_open) + pen.gap_extend);
   if (max_score >= 0) run_bound = std::min<int64_t>(run_bound, 2 * (int64_t)(max_score / cmin) + 1);
-  // a multiple of 4 words, so the compaction reads slots with 16-byte loads
+  // (a multiple of 4 words: slots begin 16-byte aligned)
   const int32_t slot_cap =
       (int32_t)((std::max<int64_t>(1, std::min<int64_t>(run_bound, SLOT_CAP)) + 3) & ~int64_t(3));
   if (R->want_cigar && (st = ensure(c, c->sc->slot, (size_t)n * slot_cap * sizeof(uint32_t)))) return st;
@@ -1878,6 +1882,7 @@ aim_status aim_prefilter(aim_context *c, const aim_batch *B, int32_t alg, aim_pe
                                                nullptr, lower, pass, nullptr, nullptr, nullptr, nullptr, s);
     if (e != hipSuccess) st = fail(AIM_ERR_HIP, "prefilter launch: %s", hipGetErrorString(e));
   }
+  if (st == AIM_ERR_OOM) release_scratch(c, s);
   c->astream = nullptr;
   HIP_TRY(hipEventRecord(c->ev_done, s));
   c->has_done = true;

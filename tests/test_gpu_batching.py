@@ -331,6 +331,41 @@ def test_smaller_batch_after_a_refused_one(alg):
     assert refused
 
 
+def test_graph_after_a_call_refused_at_its_first_buffer():
+    # a limit that the captured batch's scratch takes whole (GenASM's does not
+    # depend on the limit): a larger batch is refused before any buffer changes, and
+    # the graph can still be replayed
+    w = synth.WORKLOADS["genasm150"]
+    b, big = synth.workload("genasm150", n=500), synth.workload("genasm150", n=3000)
+    args = w["alg"], w["pen"], w["max_score"]
+    stream = torch.cuda.Stream()
+    limit = 64 << 20
+    with torch.cuda.stream(stream):
+        for _ in range(2):
+            with aim.Context(0, scratch_limit=limit, hard_limit=True) as c:
+                want = run(c, b, *args, stream=stream)
+                limit = c.scratch_usage()[1]
+        with aim.Context(0, scratch_limit=limit, hard_limit=True) as c:
+            g, dev, outs, max_len, enc = _capture(c, b, w, stream)
+            assert c.scratch_usage()[0] == limit
+            with pytest.raises(aim.AimError) as ei:
+                run(c, big, *args, stream=stream)
+            assert ei.value.code == -3
+            assert c.scratch_usage()[0] == limit
+            for _ in range(2):
+                for t in outs:
+                    t.zero_()
+                g.launch(stream)
+                stream.synchronize()
+                assert not compare(_host(outs), want)
+            g.close()
+            # (without the graph the refused call gives the scratch back)
+            with pytest.raises(aim.AimError):
+                run(c, big, *args, stream=stream)
+            assert c.scratch_usage()[0] == 0
+            assert not compare(run(c, b, *args, stream=stream), want)
+
+
 @pytest.mark.parametrize("alg,pen,n,field", [("nw", (0, 1, 0, 1), 2048, 6), ("swg", (0, 4, 6, 2), 4096, 6),
                                              ("wfa", (0, 4, 6, 2), 64, 12)])
 def test_autotune_tries_the_built_in_choice(alg, pen, n, field):
