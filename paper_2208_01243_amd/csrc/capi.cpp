@@ -776,8 +776,15 @@ struct WidePass {
 };
 constexpr WidePass WIDE_PASS[2] = {{256, 4}, {512, 6}};
 constexpr size_t CU_LDS = 160 * 1024;
-bool wide_fits(const aim::Scoring &P, int32_t L, const WidePass &wp) {
-  return aim::wfa_wide_lds(wp.threads, wp.words, std::max(P.x, P.o + 1) + 1, (L + 31) / 32) <= CU_LDS;
+// Whether the pass takes such a batch.  The narrower one does where two of its
+// workgroups fit a CU's LDS (the ring grows with the penalties: x or o + 1 up to
+// 17): with one, the class kernel is faster unless the batch is small and its time
+// one pair's.  30,000 pairs of 200-600 bp at 8 %, this pass / the class kernel:
+// 8/12/1 13.2 / 13.0 ms, 10/16/1 18.5 / 18.8, 20/8/1 24.2 / 14.1, 30/29/1 69 / 43;
+// 2,000 such pairs 1.5 / 3.8, 2.3 / 5.3, 2.4 / 4.1 and 6.5 / 9.7.
+bool wide_fits(const aim_context *c, const aim::Scoring &P, int64_t n, int32_t L, const WidePass &wp) {
+  const size_t lds = aim::wfa_wide_lds(wp.threads, wp.words, std::max(P.x, P.o + 1) + 1, (L + 31) / 32);
+  return lds <= CU_LDS && (wp.threads > 256 || wfa_small(c, n) || 2 * lds <= CU_LDS);
 }
 // Words of codes that any pair of the pass can need, and of its walk's tokens:
 // a pair ends in some stage, as wide as its lengths or its scores make it.
@@ -861,7 +868,7 @@ ShortPlan wfa_short_plan(const aim_context *c, const aim::Scoring &P, int64_t n,
   const int32_t most = wfa_most_scores(P, L), reach = wfa_reach(P, L);
   if (most > 16000) return sp;
   for (int32_t r = passes.empty() ? 0 : passes.back().reach(); r < reach || sp.nw + passes.size() == 0; r = WIDE_PASS[sp.nw++].reach())
-    if (sp.nw == 2 || !wide_fits(P, L, WIDE_PASS[sp.nw])) return sp;
+    if (sp.nw == 2 || !wide_fits(c, P, n, L, WIDE_PASS[sp.nw])) return sp;
   if (P.want_cigar) {
     // in 16 workgroups at least (the other route would have no more)
     const int64_t least_slots = std::min<int64_t>(n, 16);
@@ -1046,7 +1053,7 @@ aim_status run_wfa(aim_context *c, const aim::Seqs &S, const aim::Outs &O, const
       const ClassTune *ctp = ct == c->class_tunes.end() ? nullptr : &ct->second;
       // the first two are k_wfa_wide's where it fits, unless the class's tune
       // names a configuration of k_wfa_lds
-      if (group && k < 2 && !(ctp && (ctp->threads > 0 || ctp->global >= 0)) && wide_fits(P, L, WIDE_PASS[k])) {
+      if (group && k < 2 && !(ctp && (ctp->threads > 0 || ctp->global >= 0)) && wide_fits(c, P, n, L, WIDE_PASS[k])) {
         const WidePass &wp = WIDE_PASS[k];
         c->last_class_bucket[cls.size()] = cb;
         cls.push_back({2 * wp.threads * wp.words, wp.threads, 0, false, wp.reach(), k});

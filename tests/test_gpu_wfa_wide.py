@@ -199,3 +199,29 @@ def test_thresholds_without_filter(alg, max_len, smax):
         assert not bad, "%d mismatches, first: %s" % (len(bad), describe(b, bad[0], got, want))
         got = run(c, b, alg, AFF, smax, want_cigar=False)
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("pen,wide", [((0, 10, 16, 1), True), ((0, 18, 0, 1), False), ((0, 20, 8, 1), False)])
+def test_large_rings(pen, wide):
+    # batches that fill the chip take the narrower window where two workgroups'
+    # rings fit a CU (x or o + 1 up to 17), else the class kernel; small ones the window
+    n, small = 4200, 200
+    rng = np.random.default_rng(n + pen[1])
+    lens = synth.log_uniform_int(rng, 300, 620, n)
+    b = synth._gen_chunk(rng, n, lens, rng.uniform(0.04, 0.1, n), None)
+    print("large rings: %s, %d pairs" % (pen, n), flush=True)
+    with aim.Context(0) as c:
+        got = run(c, b, "wfa", pen)
+        window = c.last_call_stats()["wfa_class_window"][0]
+        assert (window == 2048) == wide, window
+        part = b.subset(np.arange(small))
+        few = run(c, part, "wfa", pen)
+        assert c.last_call_stats()["wfa_class_window"][0] == 2048
+    assert not compare(few, oracle.wfa_batch(part, pen, -1))
+    end = few[3][small]
+    assert not compare((got[0][:small], got[1][:small], got[2][:end], got[3][:small + 1]), few)
+    some = b.subset(np.arange(small, n, 40))
+    want = oracle.wfa_batch(some, pen, -1)
+    for t, i in enumerate(range(small, n, 40)):
+        assert (got[0][i], got[1][i]) == (want[0][t], want[1][t]), i
+        assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][t]:want[3][t + 1]]), i
