@@ -397,6 +397,12 @@ __global__ __launch_bounds__(64, C == 4 ? 3 : 4) void k_wfa_group(WfaGroupArgs a
     rng = 0x7fff7fffu;
     wlim = 0x80008000u;
   };
+  // (adaptive) diagonals dropped of a pair that ends here, whatever its outcome
+  auto count_dropped = [&]() {
+    if (!ADAPT) return;
+    dropped += (uint32_t)gdrop;
+    dropped_hi += dropped < (uint32_t)gdrop;
+  };
   // the cost of one concrete alignment bounds the optimum: all diagonal ops
   // plus one gap run for the length difference, or gap runs over both
   auto upper = [&](int32_t o) {
@@ -445,6 +451,7 @@ __global__ __launch_bounds__(64, C == 4 ? 3 : 4) void k_wfa_group(WfaGroupArgs a
             A->O.score[gp] = -1;
             A->O.status[gp] = rej ? ST_REJECTED : ST_INVALID;
             A->O.nruns[gp] = 0;
+            count_dropped();
           }
           if (__ballot(on)) {
             int32_t to = 1;
@@ -479,10 +486,7 @@ __global__ __launch_bounds__(64, C == 4 ? 3 : 4) void k_wfa_group(WfaGroupArgs a
           A->O.score[gp] = s * A->P.unit;
           A->O.status[gp] = ST_ALIGNED;
           if (!keep) A->O.nruns[gp] = 0;
-          if (ADAPT) {
-            dropped += (uint32_t)gdrop;
-            dropped_hi += dropped < (uint32_t)gdrop;
-          }
+          count_dropped();
         }
         if (keep) {
           // one entry per finished pair, in the order of the groups

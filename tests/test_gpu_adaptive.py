@@ -172,3 +172,22 @@ def test_codes_past_the_first_slots(n, hard):
     for t, i in enumerate(some):
         assert (got[0][i], got[1][i]) == (want[0][t], want[1][t])
         assert np.array_equal(got[2][got[3][i]:got[3][i + 1]], want[2][want[3][t]:want[3][t + 1]])
+
+
+@pytest.mark.parametrize("n", [300, 5000])
+def test_dropped_count_of_rejected_pairs(n):
+    # pairs past the threshold drop diagonals too (equal lengths and no filter, so
+    # that none is rejected before its scores); from 64 lanes and from 16 or 32
+    rng = np.random.default_rng(n)
+    T = [rng.integers(0, 4, int(rng.integers(60, 190))).astype(np.uint8) for _ in range(n)]
+    P = [np.where(rng.random(len(t)) < rng.uniform(0.02, 0.3), (t + rng.integers(1, 4, len(t))) % 4, t).astype(np.uint8)
+         for t in T]
+    b = synth.from_lists(P, T)
+    adaptive, smax = (4, 5), 90
+    with aim.Context(0, prefilter=False) as c:
+        got = check(c, b, AFF, adaptive, smax)
+        st = c.last_call_stats()
+    assert 0 < (got[1] == 1).sum() < n
+    want = sum(oracle.wfa_pair(b.pattern(i), b.text(i), AFF, smax, want_cigar=False, adaptive=adaptive)[3]["dropped"]
+               for i in range(n))
+    assert st["wfa_adaptive_dropped"] == want
