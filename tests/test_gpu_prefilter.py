@@ -165,3 +165,17 @@ def test_wfa250_slice(ctx):
     st = ctx.last_call_stats()
     # the unrelated fifth is rejected up front
     assert st["prefilter_rejected"] >= 0.19 * b.n
+
+
+def test_smaller_batch_after_a_refused_one(ctx):
+    # under a hard limit that holds the smaller batch's words, flags and offsets (some
+    # 0.8 MB) but not the larger one's (2 MB)
+    big, small = synth.workload("swg150", n=20_000), synth.workload("swg150", n=8000)
+    want = gpu_lower(ctx, small, "swg", (0, 4, 6, 2), 20, enc="ascii")
+    with aim.Context(0, scratch_limit=1 << 20, hard_limit=True) as hc:
+        with pytest.raises(aim.AimError) as ei:
+            gpu_lower(hc, big, "swg", (0, 4, 6, 2), 20, enc="ascii")
+        assert ei.value.code == -3
+        got = gpu_lower(hc, small, "swg", (0, 4, 6, 2), 20, enc="ascii")
+        assert hc.scratch_usage()[1] <= 1 << 20
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))
