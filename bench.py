@@ -56,7 +56,7 @@ PEAK_HBM_GBS = 8000.0
 # and WRITE_SIZE scaled by a copy-kernel calibration), valid only for the
 # kernel source they were taken on (first 16 hex of the SHA-256 of its source
 # file and the headers it includes)
-MEASURED_TRAFFIC = {("wfa_mixed", "k_wfa_wide"): ("97ee7d64d965ec62", 1.1823e11)}
+MEASURED_TRAFFIC = {("wfa_mixed", "k_wfa_wide"): ("7a5355d8e976a96e", 1.1824e11)}
 KERNEL_SOURCE = {"k_band16<32>": ("dp_band16.hip", "aim_internal.h", "dev_util.h"),
                  "k_band<32>": ("dp_band.hip", "aim_internal.h"),
                  "k_wfa_group": ("wfa_group.hip", "aim_internal.h", "wfa_common.h", "wfa_packed.h"),
@@ -427,7 +427,7 @@ def main():
 
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py measures one GPU: this build has no multi-GPU path "
-              "(pairs are independent; sharding is described in DESIGN.md). Run with --gpus 1.",
+              "(pairs are independent; several GPUs take a process each, on their own pairs). Run with --gpus 1.",
               file=sys.stderr)
         sys.exit(2)
 
