@@ -781,10 +781,12 @@ constexpr size_t CU_LDS = 160 * 1024;
 // 17): with one, the class kernel is faster unless the batch is small and its time
 // one pair's.  30,000 pairs of 200-600 bp at 8 %, this pass / the class kernel:
 // 8/12/1 13.2 / 13.0 ms, 10/16/1 18.5 / 18.8, 20/8/1 24.2 / 14.1, 30/29/1 69 / 43;
-// 2,000 such pairs 1.5 / 3.8, 2.3 / 5.3, 2.4 / 4.1 and 6.5 / 9.7.
+// 2,000 such pairs 1.5 / 3.8, 2.3 / 5.3, 2.4 / 4.1 and 6.5 / 9.7.  Under a hard limit
+// and in the static entry it does wherever it fits: the class kernel brings all later
+// passes with it, for which scratch may have no room.
 bool wide_fits(const aim_context *c, const aim::Scoring &P, int64_t n, int32_t L, const WidePass &wp) {
   const size_t lds = aim::wfa_wide_lds(wp.threads, wp.words, std::max(P.x, P.o + 1) + 1, (L + 31) / 32);
-  return lds <= CU_LDS && (wp.threads > 256 || wfa_small(c, n) || 2 * lds <= CU_LDS);
+  return lds <= CU_LDS && (wp.threads > 256 || wfa_small(c, n) || c->strict() || c->arena || 2 * lds <= CU_LDS);
 }
 // Words of codes that any pair of the pass can need, and of its walk's tokens:
 // a pair ends in some stage, as wide as its lengths or its scores make it.

@@ -204,7 +204,8 @@ def test_thresholds_without_filter(alg, max_len, smax):
 @pytest.mark.parametrize("pen,wide", [((0, 10, 16, 1), True), ((0, 18, 0, 1), False), ((0, 20, 8, 1), False)])
 def test_large_rings(pen, wide):
     # batches that fill the chip take the narrower window where two workgroups'
-    # rings fit a CU (x or o + 1 up to 17), else the class kernel; small ones the window
+    # rings fit a CU (x or o + 1 up to 17), else the class kernel; small ones the
+    # window, and so do those under a limit that has no room for the later passes
     n, small = 4200, 200
     rng = np.random.default_rng(n + pen[1])
     lens = synth.log_uniform_int(rng, 300, 620, n)
@@ -214,6 +215,9 @@ def test_large_rings(pen, wide):
         got = run(c, b, "wfa", pen)
         window = c.last_call_stats()["wfa_class_window"][0]
         assert (window == 2048) == wide, window
+        with aim.Context(0, scratch_limit=64 << 20, hard_limit=True) as hc:
+            assert not compare(run(hc, b, "wfa", pen), got)
+            assert hc.last_call_stats()["wfa_class_window"][0] == 2048
         part = b.subset(np.arange(small))
         few = run(c, part, "wfa", pen)
         assert c.last_call_stats()["wfa_class_window"][0] == 2048
